@@ -43,7 +43,8 @@ int run_compress(const float* d_W, int64_t nrows, int64_t ncols, const uint8_t* 
                                        bases[0].d_bases, d_seed, d_exp, d_q, d_err, stream);
     return e == hipSuccess ? SEEDQ_OK : SEEDQ_EHIP;
   }
-  hipError_t e = launch_compaction(d_rung_of_block, nb, nrungs, d_workspace, d_seed, stream);
+  hipError_t e = launch_compaction(d_rung_of_block, nb, nrungs, d_workspace, d_seed,
+                                   reinterpret_cast<unsigned long long*>(d_q), stream);
   if (e != hipSuccess) return SEEDQ_EHIP;
   const int32_t* list = compaction_list(d_workspace, nb, nrungs);
   const int32_t* off = compaction_offsets(d_workspace, nb, nrungs);

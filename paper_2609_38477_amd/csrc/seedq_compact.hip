@@ -97,7 +97,7 @@ scan_kernel(const int32_t* __restrict__ counts, int64_t nchunks, int nrungs,
 __global__ void __launch_bounds__(kThreads)
 scatter_kernel(const uint8_t* __restrict__ rung, int64_t nblocks, int nrungs,
                const int32_t* __restrict__ coff, const int32_t* __restrict__ off,
-               int32_t* __restrict__ lists) {
+               int32_t* __restrict__ lists, unsigned long long* __restrict__ keys) {
   __shared__ int32_t wave_cnt[kThreads / 64];
   __shared__ int32_t running[SEEDQ_MAX_RUNGS];
   const int lane = threadIdx.x & 63;
@@ -110,6 +110,7 @@ scatter_kernel(const uint8_t* __restrict__ rung, int64_t nblocks, int nrungs,
   for (int it = 0; it < kPerThread; ++it) {
     const int64_t b = base + it * kThreads + threadIdx.x;
     const int r_b = (b < nblocks) ? int(rung[b]) : 255;
+    if (r_b < nrungs) keys[b] = ~0ull;   // no code yet (see the search's keys)
     for (int r = 0; r < nrungs; ++r) {
       const bool mine = (r_b == r);
       const uint64_t m = __ballot(mine);
@@ -144,7 +145,8 @@ const int32_t* compaction_offsets(void* d_ws, int64_t nblocks, int nrungs) {
 }
 
 hipError_t launch_compaction(const uint8_t* d_rung, int64_t nblocks, int nrungs, void* d_ws,
-                             uint32_t* d_seed_invalid, hipStream_t stream) {
+                             uint32_t* d_seed_invalid, unsigned long long* d_keys,
+                             hipStream_t stream) {
   const WsLayout L = ws_layout(nblocks, nrungs);
   char* ws = static_cast<char*>(d_ws);
   int32_t* lists = reinterpret_cast<int32_t*>(ws + L.lists);
@@ -161,7 +163,7 @@ hipError_t launch_compaction(const uint8_t* d_rung, int64_t nblocks, int nrungs,
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kThreads), 0, stream, counts, L.nchunks, nrungs,
                      coff, off);
   hipLaunchKernelGGL(scatter_kernel, dim3(unsigned(L.nchunks)), dim3(kThreads), 0, stream, d_rung,
-                     nblocks, nrungs, coff, off, lists);
+                     nblocks, nrungs, coff, off, lists, d_keys);
   return hipGetLastError();
 }
 

@@ -129,8 +129,11 @@ hipError_t launch_build_bases(int K, int P, void* d_bases, int32_t* d_U, float* 
 // Deterministic, order-preserving split of the blocks by rung:
 // lists: int32 [nblocks] (the per-rung lists back to back), meta: see .hip.
 size_t compaction_workspace_bytes(int64_t nblocks, int nrungs);
+// Also sets the search key of every block that is in a list to ~0 (d_keys, one
+// 64-bit word per block).
 hipError_t launch_compaction(const uint8_t* d_rung, int64_t nblocks, int nrungs, void* d_ws,
-                             uint32_t* d_seed_invalid, hipStream_t stream);
+                             uint32_t* d_seed_invalid, unsigned long long* d_keys,
+                             hipStream_t stream);
 // Device pointers into the workspace after launch_compaction.
 const int32_t* compaction_list(void* d_ws, int64_t nblocks, int nrungs);
 const int32_t* compaction_offsets(void* d_ws, int64_t nblocks, int nrungs);

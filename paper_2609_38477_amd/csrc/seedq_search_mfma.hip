@@ -20,35 +20,36 @@
 //
 // Survivors. Each wave queues its passing (seed, block) pairs in LDS and
 // evaluates them 64 at a time, one per lane, with the exact fp64 evaluation
-// (seedq_exact.h). In the first kernel a lane whose fold passes first stores
-// its 16 bounds as a record; records are turned into queued seeds 64 at a time
-// against the thresholds of that moment. Every block's best is its exact fp64
-// error (an atomic minimum on the bit pattern in LDS) and the smallest seed of
-// that error (record_best), so the result is the exhaustive search's, ties to
-// the smallest seed, whatever the order in which survivors are evaluated. A
-// pilot pass over the first seed tile finds, per lane, the seed with the
-// smallest bound; their exact errors start every block's best, so that the
-// walk does not begin with an infinite threshold. The final codes go through
-// the same queue.
+// (seedq_exact.h). A lane whose fold passes first stores its 16 bounds as a
+// record; records are turned into queued seeds a round at a time against the
+// thresholds of that moment. Every block's best is its exact fp64 error (an
+// atomic minimum on the bit pattern in LDS) and the smallest seed of that error
+// (record_best), so the result is the exhaustive search's, ties to the smallest
+// seed, whatever the order in which survivors are evaluated. A pilot pass over
+// the first seed tile finds, per lane, the seed with the smallest bound; their
+// exact errors start every block's best, so that the walk does not begin with
+// an infinite threshold.
 //
-// Work split. A workgroup is 4 independent waves; a wave owns 4 tiles of 32
-// blocks (128 blocks) and walks the seed tiles once, reusing each A fragment
-// for its 4 block tiles; its B fragments stay in registers for the whole walk.
-// Large rungs walk the seed tiles in sequential chunks (see "seed chunks"
-// below).
+// Work split. The rung's seed tiles are cut into ranges, its blocks into units
+// of one workgroup; a workgroup takes one unit through one range (seed_range),
+// starting from the best that other ranges have left in the block's key, and
+// offers its own best to the key at its end (merge_best). One more kernel
+// emits the codes from the keys (emit_codes_kernel). A workgroup is 4
+// independent waves; a wave owns 4 tiles of 32 blocks (128 blocks; 1 or 2 tiles
+// where that measured faster, see launch_mfma_p), reusing each A fragment for
+// all of them; its B fragments stay in registers for the whole walk.
 // Block tiles go to the matrix core in pairs (six products) before the vector
 // ALU folds them, with one branch per pair; the fold waits on its own
 // products, so it is occupancy (several waves per SIMD) that keeps the matrix
-// core busy. At P = 4 the fp64 evaluation needs more registers than the walk
-// leaves free, so a second kernel rebuilds the block data and reloads the
-// seed-tile fragments after every evaluation batch instead of keeping them
-// live across it, and runs at four waves per SIMD. (P >= 5 screens with the
-// complement projections below, whose block operand is a single fragment, and
-// stays in the first kernel.)
+// core busy. At P = 4 with many seeds the fp64 evaluation needs more registers
+// than the walk over 128 blocks leaves free, so a second kernel rebuilds the
+// block data and reloads the seed-tile fragments after every evaluation batch
+// instead of keeping them live across it, and runs at four waves per SIMD.
+// (P >= 5 screens with the complement projections below, whose block operand is
+// a single fragment, and stays in the first kernel.)
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
-#include <type_traits>
 
 #include "seedq_exact.h"
 #include "seedq_internal.h"
@@ -62,26 +63,12 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int kWaves = 4;
 constexpr int kNB = 4;               // 32-block tiles per wave
 constexpr int kSlots = kNB * 32;     // blocks per wave
-// Per-wave LDS pool of the rebuilding kernel: its queue (fewer than 64 entries
-// wait when a pair of block tiles adds its at most 2 x 1024) or, with the
-// record stage, the records, their queue and the per-slot threshold data.
-constexpr int kPoolWords = 128 + 2 * 1024;
-// P = 4 in the rebuilding kernel keeps walk survivors as records (16 bounds
-// and a meta word each) in its per-wave pool: 16 records waiting after a pair
-// of block tiles, rounds of 32 records (at most 512 queued seeds each). Only
-// from K = 13: with fewer seed tiles the per-wave set-up costs more than the
-// records save (measured on 2.1 M blocks: (8..10,4) 4-7 % slower, (11,4)
-// even, (12,4) 8 % slower, (13..16,4) 2.5-5 % faster, (20,4) 5 % faster).
-constexpr int kRecordP = 4;
-constexpr bool kRemTable = false;   // the rebuilding kernel steps the LFSR
-constexpr int kRecordMinK = 13;
+// The rebuilding kernel (P = 4): 16 records waiting after a pair of block
+// tiles, rounds of 24 records (at most 384 queued seeds each).
 constexpr int kRecFlushR = 16;
 constexpr int kRecCapR = kRecFlushR + 64;
-constexpr int kRecRound = 32;
-constexpr int kRecQueueWords = 64 + kRecRound * 16;
-static_assert(kRecQueueWords % 4 == 0, "records start 16-byte aligned");
-static_assert(kRecQueueWords + 17 * kRecCapR + 128 + 64 <= kPoolWords,
-              "the record stage fits the per-wave pool");
+constexpr int kRecRound = 24;
+constexpr int kRecQueueR = 64 + kRecRound * 16;
 constexpr int kBlocksPerWG = kWaves * kSlots;
 
 // Row and column of pair k (i <= j, row-major over the upper triangle) for
@@ -142,27 +129,39 @@ __device__ __forceinline__ half8 b_fragment(const float (&ws)[kC], int h) {
   return v;
 }
 
-struct MfmaArgs {
-  const float* W;
-  int64_t nblocks;
-  const int32_t* list;
-  const int32_t* off;
-  int rung;
-  int K;
-  uint32_t mask;
-  const uint32_t* ub;
-  const float* pinv32;
-  const double* pinv64;
-  const half8* pi16;
-  int64_t ntiles;
-  float one_minus_gamma;
-  uint32_t* seed_out;
-  uint8_t* exp_out;
-  int8_t* q_out;
-  float* err_out;
-};
-
 #define SEEDQ_INLINE __device__ __attribute__((always_inline)) inline
+
+// The seed ranges of a rung, decided here from the rung's count of blocks, which
+// the host of a multi-rung call does not know: every unit of blocks_per_wg blocks
+// goes through nranges ranges of seed tiles, one workgroup each, range by range,
+// so that the resident workgroups of a large matrix walk one range at about the
+// same time and a later range starts from the earlier ones' best.
+struct RangeRule {
+  int32_t rmin;             // at least so many ranges
+  int32_t rlong, target;    // up to rlong of them for `target` workgroups
+  int32_t rshort, fill;     // up to rshort of them for `fill` workgroups
+  int32_t first, span;  // ranges of this launch
+};
+struct SeedRange {
+  int range, nranges;
+  int64_t unit;
+};
+SEEDQ_INLINE SeedRange seed_range(const RangeRule& rule, int64_t count, int blocks_per_wg) {
+  const uint32_t units = uint32_t((count + blocks_per_wg - 1) / blocks_per_wg);
+  if (units == 0u) return {1, 1, 0};
+  // wave-uniform (the divisions are done in vector registers)
+  const int t = __builtin_amdgcn_readfirstlane(int(uint32_t(rule.target) / units));
+  const int f = __builtin_amdgcn_readfirstlane(int(uint32_t(rule.fill) / units));
+  const int nr = max(rule.rmin, max(min(t, rule.rlong), min(f, rule.rshort)));
+  const uint32_t r = uint32_t(__builtin_amdgcn_readfirstlane(int(blockIdx.x / units)));
+  if (r >= uint32_t(rule.span)) return {nr, nr, 0};
+  return {int(r) + rule.first, nr, int64_t(blockIdx.x - r * units)};
+}
+
+// First seed tile of range r of nr (wave-uniform; ntiles <= 2^19, r <= nr <= 2^16).
+SEEDQ_INLINE int range_tile(int r, int64_t ntiles, int nr) {
+  return __builtin_amdgcn_readfirstlane(int(uint64_t(r) * uint64_t(ntiles) / uint32_t(nr)));
+}
 
 SEEDQ_INLINE void load_block(const float* __restrict__ W, int64_t b, bool ok, float (&w)[kC]) {
   float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
@@ -224,52 +223,20 @@ SEEDQ_INLINE uint32_t seed_of(uint32_t seedbase, int j, int h) {
   return seedbase + 8u * uint32_t(j / 4) + 4u * uint32_t(h) + uint32_t(j % 4);
 }
 
-// Per-block best of a search: the exact fp64 error of the best code so far,
-// as its bit pattern (errors are >= 0, so the bits order like the values), in
-// LDS, and its seed, the smallest among the codes of exactly that error, in the
-// caller's seed array (12 more bytes of LDS per block cost a workgroup per CU:
-// measured 11 % slower at (16,3)). A block is only ever touched by the one wave
-// that owns it, so one evaluation batch (a candidate per lane, `mine`) updates
-// both in four steps: every lane lowers the error; if any lane tied or
-// improved, every lane reads the minimum the batch left; a lane that holds
-// that minimum while its block held a larger one before resets the seed with
-// an atomic exchange that the wave waits for (vmcnt(0): performed in L2; no
-// device-wide fence, which on this GPU writes back and invalidates the L2);
-// then every lane that holds the minimum lowers the seed to its own. Ties in
-// the exact error go to the smallest seed, and the result does not depend on
-// the order in which candidates are evaluated.
-SEEDQ_INLINE void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-SEEDQ_INLINE void record_best(unsigned long long* best, uint32_t* seed_best, int slot, int64_t b,
-                              double err, uint32_t seed, bool mine) {
-  const unsigned long long eb = mine ? (unsigned long long)__double_as_longlong(err) : 0ull;
-  unsigned long long old = 0ull;
-  if (mine) old = atomicMin(&best[slot], eb);
-  const bool cand = mine && eb <= old;
-  if (__builtin_amdgcn_ballot_w64(cand) == 0ull) return;
-  __threadfence_block();
-  const unsigned long long now = cand ? best[slot] : ~0ull;
-  const bool holds = cand && eb == now;
-  const bool reset = holds && old != now;
-  if (__builtin_amdgcn_ballot_w64(reset) != 0ull) {
-    if (reset) {
-      const uint32_t prev = __hip_atomic_exchange(&seed_best[b], seed, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("" ::"v"(prev));   // keep the returning form
-    }
-    wait_vmem();
-  }
-  if (holds) __hip_atomic_fetch_min(&seed_best[b], seed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// The same update with the seeds in LDS (sbest, one per slot of the wave),
-// for the kernels whose LDS has room for them: no global atomics and no wait
-// for them. LDS operations of one wave take effect in program order; the
-// fence waits for the reset before the minimum. (At P >= 5, where about one
-// batch in two improves some block, this measured (12..16,6) 2-11 % and
-// (13..16,5) 2-6 % faster on 2.1 M blocks.)
-SEEDQ_INLINE void record_best_lds(unsigned long long* best, uint32_t* sbest, int slot, double err,
-                                  uint32_t seed, bool mine) {
+// Per-block best of one wave's walk, in LDS: the exact fp64 error of the best
+// code so far as its bit pattern (errors are >= 0, so the bits order like the
+// values) and the smallest seed among the codes of exactly that error. The
+// slots belong to the wave, so one evaluation batch (a candidate per lane,
+// `mine`) updates both in four steps: every lane lowers the error; if any lane
+// tied or improved, every lane reads the minimum the batch left; a lane that
+// holds that minimum while its slot held a larger one before resets the seed;
+// then every lane that holds the minimum lowers the seed to its own. LDS
+// operations of one wave take effect in program order; the fence waits for the
+// reset before the minimum. Ties in the exact error go to the smallest seed,
+// and the result does not depend on the order in which candidates are
+// evaluated.
+SEEDQ_INLINE void record_best(unsigned long long* best, uint32_t* sbest, int slot, double err,
+                              uint32_t seed, bool mine) {
   const unsigned long long eb = mine ? (unsigned long long)__double_as_longlong(err) : 0ull;
   unsigned long long old = 0ull;
   if (mine) old = atomicMin(&best[slot], eb);
@@ -286,9 +253,47 @@ SEEDQ_INLINE void record_best_lds(unsigned long long* best, uint32_t* sbest, int
   if (holds) atomicMin(&sbest[slot], seed);
 }
 
-// The best seed of block b once the wave's updates are performed.
-SEEDQ_INLINE uint32_t best_seed(const uint32_t* seed_best, int64_t b) {
-  return __hip_atomic_load(&seed_best[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Per-block best over all seed ranges: one 64-bit key per block in the caller's
+// mantissa output, the exact error's bit pattern cut to its upper 40 bits (sign,
+// exponent and 28 mantissa bits) above the 24-bit seed; ~0 before the first.
+// The order of two keys is that of (exact error, seed); where their upper 40
+// bits agree, the exact error of the seed already there is computed again
+// (merge_best), so the cut loses nothing. Waves of different XCDs meet here,
+// hence the agent scope of every access.
+constexpr unsigned long long kKeySeed = 0xFFFFFFull;
+constexpr uint32_t kNoSeed = ~0u;
+
+SEEDQ_INLINE unsigned long long load_key(unsigned long long* keys, int64_t b) {
+  return __hip_atomic_load(&keys[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// An upper bound on the error behind a key, as its bit pattern (~0 stays ~0).
+SEEDQ_INLINE unsigned long long key_bound(unsigned long long key) { return key | kKeySeed; }
+
+// Offers the code (error bits eb, seed s) of block b to its key, one block per
+// lane where `mine`; exact(b, seed) is the exact error of a seed for a block.
+// Every turn of the loop either settles a lane or follows another wave's
+// successful exchange on its key, so it ends.
+template <typename Exact>
+SEEDQ_INLINE void merge_best(unsigned long long* keys, int64_t b, unsigned long long eb, uint32_t s,
+                             bool mine, Exact&& exact) {
+  const unsigned long long key = (eb & ~kKeySeed) | s;
+  unsigned long long cur = mine ? load_key(keys, b) : 0ull;
+  bool open = mine;
+  while (ballot(open) != 0ull) {
+    const bool tie = open && (cur >> 24) == (key >> 24);
+    open = open && (key >> 24) <= (cur >> 24);
+    if (ballot(tie) != 0ull) {
+      if (tie) {
+        const uint32_t s2 = uint32_t(cur & kKeySeed);
+        const unsigned long long e2 = (unsigned long long)__double_as_longlong(exact(b, s2));
+        open = eb < e2 || (eb == e2 && s < s2);
+      }
+    }
+    if (open)
+      open = !__hip_atomic_compare_exchange_strong(&keys[b], &cur, key, __ATOMIC_RELAXED,
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // Number of lanes below this one whose bit is set in mask.
@@ -304,11 +309,10 @@ SEEDQ_INLINE uint32_t lane_now() {
   return l;
 }
 
-// Queue entries: seed << 8 | final << 7 | slot (slot < 128). Seed 0 = no-op.
-constexpr uint32_t kFinal = 0x80u;
+// Queue entries: seed << 8 | slot (slot < 128). Seed 0 = no-op.
 static_assert(kSlots <= 128, "slot must fit 7 bits");
 
-// Walk survivors of this kernel are first kept as records: a lane whose fold
+// Walk survivors are first kept as records: a lane whose fold
 // passes stores its 16 bounds with the seed tile, its half and the block slot
 // (one row and one meta word in LDS; meta = tile << 8 | half << 7 | slot).
 // Records become candidates 64 at a time, each compared with its block's
@@ -327,7 +331,13 @@ template <int P>
 constexpr int kRecCap = kRecFlush<P> + 64;   // one block tile adds at most 64
 template <int P>
 constexpr int kRecRoundMin = complement_dims(P) > 0 ? 64 : 1;
-constexpr int kQCapRec = 64 + 64 * 16;        // < 64 waiting + one round of 64 records
+// records per round: 64 lanes' worth, or 56 where the quadratic form's fp32
+// records leave the queue that much less LDS (three workgroups per CU need
+// their 13 KB per wave)
+template <int P>
+constexpr int kRecTake = complement_dims(P) > 0 ? 64 : 56;
+template <int P>
+constexpr int kQCapRec = 64 + kRecTake<P> * 16;   // < 64 waiting + one round of records
 // At P >= 5 (complement screen) records hold their bounds as fp16 (16 x 2
 // bytes: two float4 of storage instead of four), which keeps the kernel's LDS
 // at 44 KB with 128 records per wave, three workgroups per CU. The values
@@ -340,32 +350,27 @@ template <int P>
 constexpr int kRecVecs = half_records(P) ? 2 : 4;
 typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
 
-template <int P>
+template <int P, int NT>
 __global__ void __launch_bounds__(kWaves * 64)
-__attribute__((amdgpu_waves_per_eu(3)))
+__attribute__((amdgpu_waves_per_eu(NT == 1 && complement_dims(P) > 0 ? 4 : 3)))
 search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* __restrict__ list,
                    const int32_t* __restrict__ off, int rung, int K, uint32_t mask,
                    const uint32_t* __restrict__ ub, const float* __restrict__ pinv32,
                    const double* __restrict__ pinv64, const half8* __restrict__ pi16,
-                   int64_t ntiles, float one_minus_gamma, uint32_t* __restrict__ seed_out,
-                   uint8_t* __restrict__ exp_out, int8_t* __restrict__ q_out,
-                   float* __restrict__ err_out, int nchunks, int chunk,
-                   unsigned long long* __restrict__ carry) {
-  __shared__ unsigned long long best_all[kWaves][kSlots];
-  __shared__ int32_t blk_all[kWaves][kSlots];
-  __shared__ float thr_base_all[kWaves][kSlots];   // ||w||^2 (1 - gamma) in accumulator units
+                   int64_t ntiles, float one_minus_gamma, RangeRule rule,
+                   unsigned long long* __restrict__ keys) {
+  constexpr int kS = NT * 32;   // blocks per wave
+  __shared__ unsigned long long best_all[kWaves][kS];
+  __shared__ uint32_t sbest_all[kWaves][kS];
+  __shared__ int32_t blk_all[kWaves][kS];
+  __shared__ float thr_base_all[kWaves][kS];   // ||w||^2 (1 - gamma) in accumulator units
   // power-of-two scaling of the block: ilogb of its largest |w_i|, down to -149
   // for fp32 subnormals, so 16 bits
-  __shared__ int16_t ex_all[kWaves][kSlots];
+  __shared__ int16_t ex_all[kWaves][kS];
   // 16 bounds per record: fp32, or fp16 at P >= 5 (see half_records)
   __shared__ float4 rec_all[kWaves][kRecCap<P>][kRecVecs<P>];
   __shared__ uint32_t meta_all[kWaves][kRecCap<P>];
-  __shared__ uint32_t queue_all[kWaves][kQCapRec];
-  // at P >= 5 the best seed of every slot lives in LDS (2 KB per workgroup;
-  // the quadratic-form kernels keep it in seed_out: three of their workgroups
-  // per CU leave no room for it) and goes to seed_out when the launch ends
-  constexpr bool kSeedsInLds = complement_dims(P) > 0;
-  __shared__ uint32_t sbest_all[kWaves][kSeedsInLds ? kSlots : 1];
+  __shared__ uint32_t queue_all[kWaves][kQCapRec<P>];
 
   const int lane = threadIdx.x & 63;
   // wave-uniform, so that the per-wave LDS addresses are scalar
@@ -386,8 +391,9 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
     begin = off[rung];
     count = int64_t(off[rung + 1]) - begin;
   }
-  const int64_t wave_base = (int64_t(blockIdx.x) * kWaves + wave) * kSlots;
-  if (wave_base >= count) return;  // wave-uniform; waves never synchronise
+  const SeedRange rg = seed_range(rule, count, kWaves * kS);
+  const int64_t wave_base = (rg.unit * kWaves + wave) * kS;
+  if (rg.range >= rg.nranges || wave_base >= count) return;  // wave-uniform; waves never synchronise
   const uint32_t nseeds = uint32_t((int64_t(1) << K) - 1);
   // quadratic form: 3 A and 3 B fragments per tile; complement screen: M A
   // fragments (one per complement vector) and one B fragment (the weights)
@@ -401,11 +407,12 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   };
 
   // ---------------------------------------------------------------- prologue
-  half8 bop[kNB][NB];
-  float thr[kNB];
-  bool active[kNB], valid[kNB];
+  half8 bop[NT][NB];
+  float thr[NT];
+  bool active[NT], valid[NT];
+  bool fresh = false;   // a block of this lane has no error yet
 #pragma unroll
-  for (int nt = 0; nt < kNB; ++nt) {
+  for (int nt = 0; nt < NT; ++nt) {
     const int64_t idx = wave_base + nt * 32 + n;
     valid[nt] = idx < count;
     const int64_t b = valid[nt] ? (list ? int64_t(list[begin + idx]) : idx) : 0;
@@ -431,14 +438,12 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
       bop[nt][1] = b_fragment<1>(ws, h);
       bop[nt][2] = b_fragment<2>(ws, h);
     }
+    // a range starts from the best that the others have left so far
+    const unsigned long long bound = valid[nt] ? key_bound(load_key(keys, b)) : ~0ull;
+    fresh |= active[nt] && bound == ~0ull;
     if (h == 0) {
-      // a later chunk starts from the best so far (error in carry, seed in
-      // seed_out); the first one from none
-      best[nt * 32 + n] = chunk > 0 && valid[nt] ? carry[b] : ~0ull;
-      if constexpr (kSeedsInLds)
-        sbest[nt * 32 + n] = chunk > 0 && valid[nt] ? seed_out[b] : ~0u;
-      else if (chunk == 0 && valid[nt])
-        seed_out[b] = ~0u;
+      best[nt * 32 + n] = bound;
+      sbest[nt * 32 + n] = kNoSeed;
       blk[nt * 32 + n] = int32_t(b);
       if constexpr (M > 0) {
         // sqrt(M) times the bound on the error of each computed projection,
@@ -459,7 +464,6 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
     }
   }
   __threadfence_block();
-  wait_vmem();   // the seed resets are performed before any update of them
 
   // Screening threshold of slot s from its best: a bound passes when it can
   // reach the block's best exact error so far (-inf before the first one).
@@ -486,10 +490,24 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   auto refresh = [&]() __attribute__((always_inline)) {
     __threadfence_block();
 #pragma unroll
-    for (int nt = 0; nt < kNB; ++nt)
+    for (int nt = 0; nt < NT; ++nt)
       if (active[nt]) thr[nt] = slot_threshold(nt * 32 + n);
   };
 
+  // Exact error of a seed for block b.
+  auto exact_error = [&](int64_t b, uint32_t seed) __attribute__((always_inline)) {
+    float w[kC];
+    load_block(W, b, true, w);
+    int qe, q[P];
+    if constexpr (M > 0)
+      return exact_eval_f32<P>(w, pinv32 + int64_t(seed - 1) * (P * kC),
+                               pinv64 + int64_t(seed - 1) * (P * kC),
+                               ub + int64_t(seed - 1) * basis_words(K, P), seed, K, mask, qe, q);
+    else
+      return exact_eval<P, false>(w, pinv64 + int64_t(seed - 1) * (P * kC),
+                                  ub + int64_t(seed - 1) * basis_words(K, P), seed, K, mask, qe,
+                                  q);
+  };
   int qcount = 0;  // wave-uniform
   // Evaluate the top min(64, qcount) candidates, one per lane, until fewer
   // than min_batch remain.
@@ -501,52 +519,24 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
       bool mine = false;
       uint32_t seed = 0u;
       int slot = 0;
-      int64_t b = 0;
       double err = 0.0;
       if (lane < e) {
         const uint32_t ent = queue[base + lane];
         seed = ent >> 8;
         slot = int(ent & 0x7Fu);
         if (seed != 0u) {
-          b = blk[slot];
-          float w[kC];
-          load_block(W, b, true, w);
-          int qe, q[P];
-          if constexpr (M > 0)
-            err = exact_eval_f32<P>(w, pinv32 + int64_t(seed - 1) * (P * kC),
-                                    pinv64 + int64_t(seed - 1) * (P * kC),
-                                    ub + int64_t(seed - 1) * basis_words(K, P), seed, K, mask, qe,
-                                    q);
-          else
-            err = exact_eval<P, false>(w, pinv64 + int64_t(seed - 1) * (P * kC),
-                                       ub + int64_t(seed - 1) * basis_words(K, P), seed, K, mask,
-                                       qe, q);
-          if (ent & kFinal) {
-            seed_out[b] = seed;
-            exp_out[b] = uint8_t(qe);
-            uint32_t lo = 0, hi = 0;
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-              const uint32_t byte = uint32_t(uint8_t(int8_t(q[p])));
-              if (p < 4) lo |= byte << (8 * p);
-              else hi |= byte << (8 * (p - 4));
-            }
-            reinterpret_cast<uint2*>(q_out)[b] = make_uint2(lo, hi);
-            if (err_out) err_out[b] = float(err);
-          } else {
-            mine = true;
-          }
+          err = exact_error(blk[slot], seed);
+          mine = true;
         }
       }
-      if constexpr (kSeedsInLds) record_best_lds(best, sbest, slot, err, seed, mine);
-      else record_best(best, seed_out, slot, b, err, seed, mine);
+      record_best(best, sbest, slot, err, seed, mine);
       qcount = base;
     }
     __threadfence_block();
   };
 
   int nrec = 0;  // wave-uniform
-  // Records -> candidates: lane l takes record base + l of the top 64 and
+  // Records -> candidates: lane l takes record base + l of the top kRecTake and
   // compares its 16 bounds with the block's current threshold; the passing
   // seeds are queued. Rounds run while at least min_round records wait. Full
   // batches are evaluated after each round of records; the walk's thresholds
@@ -554,7 +544,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   auto process = [&](int min_round) __attribute__((always_inline)) {
     __threadfence_block();
     while (nrec >= min_round && nrec > 0) {
-      const int e = nrec < 64 ? nrec : 64;
+      const int e = nrec < kRecTake<P> ? nrec : kRecTake<P>;
       const int base = nrec - e;
       const bool live = lane < e;
       uint32_t m = 0u;
@@ -642,27 +632,31 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
 
   const half8* A = pi16;
 
+  // The walk of this range: seed tiles [T0, T1), at least 8 of them.
+  const int64_t T0 = range_tile(rg.range, ntiles, rg.nranges);
+  const int64_t T1 = range_tile(rg.range + 1, ntiles, rg.nranges);
+
   // ---------------------------------------------------------------- pilot
-  // Over the first tile each lane tracks its seed of smallest bound; their
-  // exact errors start every block's best. (Longer pilots cost more matrix
-  // time than the survivors they save.) Later chunks start from the best so far
-  // instead.
-  if (chunk > 0) {
+  // Over the range's first tile each lane tracks its seed of smallest bound;
+  // their exact errors start the best of every block that has none yet. (Longer
+  // pilots cost more matrix time than the survivors they save.)
+  if (ballot(fresh) == 0ull) {
     refresh();
   } else {
     half8 a[NA];
 #pragma unroll
-    for (int t = 0; t < NA; ++t) a[t] = A[64 * t + lane];
+    for (int t = 0; t < NA; ++t) a[t] = A[T0 * kTileFrags + 64 * t + lane];
 #pragma unroll
-    for (int nt = 0; nt < kNB; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
       const floatx16 acc = screen(a, bop[nt]);
       const float mx = fold_max(acc);
       int jb = 15;
 #pragma unroll
       for (int j = 14; j >= 0; --j)
         if (acc[j] == mx) jb = j;
-      // seeds 1..32 all exist (K >= 8)
-      const uint32_t sd = seed_of(1u, jb, h);
+      // every seed of the tile exists: only the last tile of the rung is short,
+      // and no range starts there (K >= 8)
+      const uint32_t sd = seed_of(uint32_t(T0) * 32u + 1u, jb, h);
       const bool put = active[nt];
       const uint64_t mk = ballot(put);
       if (put) queue[qcount + lanes_below(mk)] = (sd << 8) | uint32_t(nt * 32 + n);
@@ -698,15 +692,25 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
     }
     nrec += __popcll(mk);
   };
-  static_assert(kNB == 4, "the walk below unrolls four block tiles");
+  static_assert(NT == 1 || NT == 2 || NT == 4, "one block tile or pairs of them");
 
-  // One seed tile against the four block tiles: two block tiles at a time,
-  // six products to the matrix core, then the folds, one branch per pair.
-  // Before each block tile's records at most kRecCap - 64 are waiting.
+  // One seed tile against the block tiles: two block tiles at a time, six
+  // products to the matrix core, then the folds, one branch per pair. Before
+  // each block tile's records at most kRecCap - 64 are waiting.
   auto tile = [&](const half8 (&a)[NA], int64_t T) __attribute__((always_inline)) {
     const uint32_t t32 = uint32_t(T);
+    if constexpr (NT == 1) {
+      const floatx16 acc = screen(a, bop[0]);
+      const bool p = fold_max(acc) >= thr[0];
+      const uint64_t m = ballot(p);
+      if (m != 0ull) {
+        record(0, acc, p, m, t32);
+        if (nrec >= kRecFlush<P>) process(kRecRoundMin<P>);
+      }
+      return;
+    }
 #pragma unroll
-    for (int pr = 0; pr < 2; ++pr) {
+    for (int pr = 0; pr < NT / 2; ++pr) {
       // raised issue priority while this wave feeds the matrix core, so that
       // its products start ahead of the other waves' folds (measured +0.5 to
       // +1.1 % at (16,3); the rebuilding kernel measured slower with it)
@@ -729,8 +733,6 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   // loaded while the other tile is screened. The loads are unconditional (the
   // index is clamped to the last tile) so that the wait before each tile
   // covers only that tile's own loads.
-  // Chunk `chunk` walks tiles [T0, T1) (at least 8 of them).
-  const int64_t T0 = int64_t(chunk) * ntiles / nchunks, T1 = int64_t(chunk + 1) * ntiles / nchunks;
   const int64_t last = T1 - 1;
   half8 x[NA], y[NA];
 #pragma unroll
@@ -753,90 +755,59 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   evaluate(1);
 
   // ---------------------------------------------------------------- results
-  // A chunk before the last hands its best errors on to the next launch (the
-  // seeds are in seed_out already); the last one emits the codes.
-  if (chunk + 1 < nchunks) {
-#pragma unroll
-    for (int nt = 0; nt < kNB; ++nt)
-      if (h == 0 && valid[nt]) {
-        carry[blk[nt * 32 + n]] = best[nt * 32 + n];
-        if constexpr (kSeedsInLds) seed_out[blk[nt * 32 + n]] = sbest[nt * 32 + n];
-      }
-    return;
+  for (int i = 0; i < kS; i += 64) {
+    const bool mine = i + lane < kS && sbest[i + lane] != kNoSeed;
+    const int slot = mine ? i + lane : 0;
+    merge_best(keys, blk[slot], best[slot], sbest[slot], mine, exact_error);
   }
-  wait_vmem();   // every seed update of this wave is performed
-  // the winning seed of every block, evaluated once more to emit its code
-#pragma unroll
-  for (int nt = 0; nt < kNB; ++nt) {
-    const bool put = h == 0 && active[nt];
-    const uint64_t mk = ballot(put);
-    if (put) {
-      // every active block has a best after the pilot; seed 1 is a guard
-      uint32_t seed = 1u;
-      if (best[nt * 32 + n] != ~0ull) {
-        if constexpr (kSeedsInLds) seed = sbest[nt * 32 + n];
-        else seed = best_seed(seed_out, blk[nt * 32 + n]);
-      }
-      queue[qcount + lanes_below(mk)] = (seed << 8) | kFinal | uint32_t(nt * 32 + n);
-    }
-    qcount += __popcll(mk);
-    if (h == 0 && valid[nt] && !active[nt]) {
-      // all-zero block: every seed ties, the smallest one wins
-      const int64_t b = blk[nt * 32 + n];
-      seed_out[b] = 1u;
-      exp_out[b] = 15;
-      reinterpret_cast<uint2*>(q_out)[b] = make_uint2(0u, 0u);
-      if (err_out) err_out[b] = 0.f;
-    }
-  }
-  evaluate(1);
 }
 
-// The same search at P = 4, where the fp64 evaluation needs more registers:
+// The same search at P = 4 and many seeds, where the fp64 evaluation needs more
+// registers than the walk of four block tiles leaves:
 // the block data (B fragments and thresholds) and the seed-tile fragments are
 // rebuilt from W, the keys and the projector stack after every evaluation
 // batch, so none of it is live across that code and the kernel fits four waves
 // per SIMD.
-template <int P, bool kRec>
+template <int P>
 __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
 search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* __restrict__ list,
                    const int32_t* __restrict__ off, int rung, int K, uint32_t mask,
-                   const uint32_t* __restrict__ ub,
+                   const uint32_t* __restrict__ ub, const float* __restrict__,
                    const double* __restrict__ pinv64, const half8* __restrict__ pi16,
-                   int64_t ntiles, float one_minus_gamma,
-                   uint32_t* __restrict__ seed_out, uint8_t* __restrict__ exp_out,
-                   int8_t* __restrict__ q_out, float* __restrict__ err_out, int nchunks,
-                   int chunk, unsigned long long* __restrict__ carry) {
-  // With the record stage (kRec, P = 4 only) the per-wave pool holds the
-  // candidate queue, the records (16 bounds and a meta word each) and the
-  // per-slot threshold data; otherwise it is the queue alone.
-  static_assert(!kRec || P == kRecordP, "records only at P = 4");
+                   int64_t ntiles, float one_minus_gamma, RangeRule rule,
+                   unsigned long long* __restrict__ keys) {
+  // 40 KB in all: four workgroups per CU
   __shared__ unsigned long long best_all[kWaves][kSlots];
+  __shared__ uint32_t sbest_all[kWaves][kSlots];
   __shared__ int32_t blk_all[kWaves][kSlots];
-  __shared__ __attribute__((aligned(16))) uint32_t pool_all[kWaves][kPoolWords];
+  __shared__ float thr_base_all[kWaves][kSlots];
+  __shared__ int16_t ex_all[kWaves][kSlots];   // ilogb, down to -149
+  __shared__ float4 rec_all[kWaves][kRecCapR][4];
+  __shared__ uint32_t meta_all[kWaves][kRecCapR];
+  __shared__ uint32_t queue_all[kWaves][kRecQueueR];
 
   const int lane = threadIdx.x & 63;
   // wave-uniform, so that the per-wave LDS addresses are scalar
-  // (the other variants measured faster without it)
-  const int wave = kRec ? __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)) : int(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const int n = lane & 31;   // block column of the MFMA tile
   const int h = lane >> 5;   // which half of the rows / reduction this lane holds
   unsigned long long* best = best_all[wave];
+  uint32_t* sbest = sbest_all[wave];
   int32_t* blk = blk_all[wave];
-  uint32_t* pool = pool_all[wave];
-  uint32_t* queue = pool;
-  float4 (*rec)[4] = reinterpret_cast<float4 (*)[4]>(pool + kRecQueueWords);
-  uint32_t* meta = pool + kRecQueueWords + 16 * kRecCapR;
-  float* slot_thr = reinterpret_cast<float*>(meta + kRecCapR);
-  int16_t* slot_ex = reinterpret_cast<int16_t*>(slot_thr + kSlots);   // ilogb, down to -149
+  float* slot_thr = thr_base_all[wave];
+  int16_t* slot_ex = ex_all[wave];
+  float4 (*rec)[4] = rec_all[wave];
+  uint32_t* meta = meta_all[wave];
+  uint32_t* queue = queue_all[wave];
 
   int64_t begin = 0, count = nblocks;
   if (list) {
     begin = off[rung];
     count = int64_t(off[rung + 1]) - begin;
   }
-  const int64_t wave_base = (int64_t(blockIdx.x) * kWaves + wave) * kSlots;
-  if (wave_base >= count) return;  // wave-uniform; waves never synchronise
+  const SeedRange rg = seed_range(rule, count, kBlocksPerWG);
+  const int64_t wave_base = (rg.unit * kWaves + wave) * kSlots;
+  if (rg.range >= rg.nranges || wave_base >= count) return;  // wave-uniform; waves never synchronise
   const uint32_t nseeds = uint32_t((int64_t(1) << K) - 1);
 
   // ---------------------------------------------------------------- prologue
@@ -845,34 +816,30 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
     const int64_t idx = wave_base + nt * 32 + n;
     const int64_t b = idx < count ? (list ? int64_t(list[begin + idx]) : idx) : 0;
     if (h == 0) {
-      // a later chunk starts from the best so far (its seed is already in
-      // seed_out); the first one from none
-      best[nt * 32 + n] = chunk > 0 && idx < count ? carry[b] : ~0ull;
-      if (chunk == 0 && idx < count) seed_out[b] = ~0u;
+      // a range starts from the best that the others have left so far
+      best[nt * 32 + n] = idx < count ? key_bound(load_key(keys, b)) : ~0ull;
+      sbest[nt * 32 + n] = kNoSeed;
       blk[nt * 32 + n] = int32_t(b);
     }
-    if constexpr (kRec) {
-      if (h == 0) {
-        const bool valid = idx < count;
-        float w[kC];
-        load_block(W, b, valid, w);
-        float amax = 0.f;
+    if (h == 0) {
+      const bool valid = idx < count;
+      float w[kC];
+      load_block(W, b, valid, w);
+      float amax = 0.f;
 #pragma unroll
-        for (int i = 0; i < kC; ++i) amax = fmaxf(amax, fabsf(w[i]));
-        const int ex = valid && amax > 0.f ? ilogbf(amax) : 0;
-        float ww = 0.f;
+      for (int i = 0; i < kC; ++i) amax = fmaxf(amax, fabsf(w[i]));
+      const int ex = valid && amax > 0.f ? ilogbf(amax) : 0;
+      float ww = 0.f;
 #pragma unroll
-        for (int i = 0; i < kC; ++i) {
-          const float ws = ldexpf(w[i], -ex);
-          ww = fmaf(ws, ws, ww);
-        }
-        slot_thr[nt * 32 + n] = ww * one_minus_gamma * (kOperandScale * kOperandScale);
-        slot_ex[nt * 32 + n] = int16_t(ex);
+      for (int i = 0; i < kC; ++i) {
+        const float ws = ldexpf(w[i], -ex);
+        ww = fmaf(ws, ws, ww);
       }
+      slot_thr[nt * 32 + n] = ww * one_minus_gamma * (kOperandScale * kOperandScale);
+      slot_ex[nt * 32 + n] = int16_t(ex);
     }
   }
   __threadfence_block();
-  wait_vmem();   // the seed resets are performed before any update of them
 
   // Per-lane block data: the B fragments (2^12-scaled pair products of the
   // block scaled by a power of two so that max |w_i| lies in [1, 2)) and the
@@ -910,10 +877,19 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
     }
   };
 
+  // Exact error of a seed for block b.
+  auto exact_error = [&](int64_t b, uint32_t seed) __attribute__((always_inline)) {
+    float w[kC];
+    load_block(W, b, true, w);
+    int qe, q[P];
+    return exact_eval<P, false>(w, pinv64 + int64_t(seed - 1) * (P * kC),
+                                    ub + int64_t(seed - 1) * basis_words(K, P), seed, K, mask, qe,
+                                    q);
+  };
   int qcount = 0;  // wave-uniform
   // Evaluate the top min(64, qcount) queued entries, one per lane, until fewer
-  // than min_batch remain; after any evaluation rebuild the block data and
-  // thresholds. Returns whether it evaluated (wave-uniform).
+  // than min_batch remain; after any evaluation rebuild what is needed of the
+  // block data, the thresholds and the fragments.
   auto exact_with = [&](int min_batch, auto&& rebuild) __attribute__((always_inline)) {
     bool ran = false;
     while (qcount >= min_batch && qcount > 0) {
@@ -922,38 +898,17 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
       bool mine = false;
       uint32_t seed = 0u;
       int slot = 0;
-      int64_t b = 0;
       double err = 0.0;
       if (lane < e) {
         const uint32_t ent = queue[base + lane];
         seed = ent >> 8;
         slot = int(ent & 0x7Fu);
         if (seed != 0u) {
-          b = blk[slot];
-          float w[kC];
-          load_block(W, b, true, w);
-          int qe, q[P];
-          err = exact_eval<P, kRemTable>(w, pinv64 + int64_t(seed - 1) * (P * kC),
-                                         ub + int64_t(seed - 1) * basis_words(K, P), seed, K,
-                                         mask, qe, q);
-          if (ent & kFinal) {
-            seed_out[b] = seed;
-            exp_out[b] = uint8_t(qe);
-            uint32_t lo = 0, hi = 0;
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-              const uint32_t byte = uint32_t(uint8_t(int8_t(q[p])));
-              if (p < 4) lo |= byte << (8 * p);
-              else hi |= byte << (8 * (p - 4));
-            }
-            reinterpret_cast<uint2*>(q_out)[b] = make_uint2(lo, hi);
-            if (err_out) err_out[b] = float(err);
-          } else {
-            mine = true;
-          }
+          err = exact_error(blk[slot], seed);
+          mine = true;
         }
       }
-      record_best(best, seed_out, slot, b, err, seed, mine);
+      record_best(best, sbest, slot, err, seed, mine);
       qcount = base;
       ran = true;
     }
@@ -961,9 +916,7 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
       __threadfence_block();
       rebuild();
     }
-    return ran;
   };
-  auto exact = [&](int min_batch) __attribute__((always_inline)) { return exact_with(min_batch, setup); };
 
   // Records -> queued seeds (P = 4): lane l < 32 takes record base + l of the
   // top 32 and compares its 16 bounds with the block's current threshold; one
@@ -1034,13 +987,23 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
   const half8* A = pi16;
   setup();
 
+  // The walk of this range: seed tiles [T0, T1), at least 8 of them (32-bit
+  // tile indices, ntiles < 2^19, kept scalar).
+  const int T0 = range_tile(rg.range, ntiles, rg.nranges);
+  const int T1 = range_tile(rg.range + 1, ntiles, rg.nranges);
+  const int last = T1 - 1;
+
   // ---------------------------------------------------------------- pilot
-  // Over the first tile each lane takes its seed of smallest bound; their exact
-  // errors start every block's best. (Longer pilots cost more matrix time than
-  // the survivors they save.) Later chunks start from the best so far (setup()
-  // above has turned it into thresholds).
-  if (chunk == 0) {
-    const half8 a0 = A[lane], a1 = A[64 + lane], a2 = A[128 + lane];
+  // Over the range's first tile each lane takes its seed of smallest bound;
+  // their exact errors start the best of every block that has none yet (setup()
+  // has given those the threshold -inf). (Longer pilots cost more matrix time
+  // than the survivors they save.)
+  bool fresh = false;
+#pragma unroll
+  for (int nt = 0; nt < kNB; ++nt) fresh |= thr[nt] == -INFINITY;
+  if (ballot(fresh) != 0ull) {
+    const half8* At = A + T0 * 192;
+    const half8 a0 = At[lane], a1 = At[64 + lane], a2 = At[128 + lane];
 #pragma unroll
     for (int nt = 0; nt < kNB; ++nt) {
       const floatx16 acc = bounds(a0, a1, a2, bop[nt]);
@@ -1049,59 +1012,27 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
 #pragma unroll
       for (int j = 14; j >= 0; --j)
         if (acc[j] == m) jb = j;
-      // seeds 1..32 all exist (K >= 8)
-      const uint32_t sd = seed_of(1u, jb, h);
+      // every seed of the tile exists: only the last tile of the rung is short,
+      // and no range starts there (K >= 8)
+      const uint32_t sd = seed_of(uint32_t(T0) * 32u + 1u, jb, h);
       const bool put = thr[nt] != INFINITY;
       const uint64_t mk = ballot(put);
       if (put) queue[qcount + lanes_below(mk)] = (sd << 8) | uint32_t(nt * 32 + n);
       qcount += __popcll(mk);
     }
-    exact(1);
+    exact_with(1, setup);
   }
 
   // ---------------------------------------------------------------- seed walk
-  // Queue the candidates of block tile nt whose bound passes, one ballot per
-  // seed. At most 1024 per block tile; fewer than 64 are queued before a pair
-  // of block tiles, so the 2 x 1024 of one pair always fit.
-  auto check = [&](auto ntc, const floatx16& acc, bool any, uint32_t seedbase)
-                   __attribute__((always_inline)) {
-    constexpr int nt = decltype(ntc)::value;
-    if (ballot(any) == 0ull) return;
-    // half and slot recomputed here, so that the 16 seed offsets and the slot
-    // are not hoisted out of the walk and kept live (or spilled) across it
-    const uint32_t l = lane_now();
-    const int hh = int(l >> 5);
-    const uint32_t slot = uint32_t(nt * 32) + (l & 31u);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const bool pass = acc[j] >= thr[nt];
-      const uint64_t mk = ballot(pass);
-      if (mk != 0ull) {
-        if (pass) {
-          const uint32_t seed = seed_of(seedbase, j, hh);
-          queue[qcount + lanes_below(mk)] = ((seed <= nseeds ? seed : 0u) << 8) | slot;
-        }
-        qcount += __popcll(mk);
-      }
-    }
-  };
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
   static_assert(kNB == 4, "the walk below unrolls four block tiles");
 
   // Seed-tile fragments; the index is clamped to the last tile so that every
   // load is unconditional and each wait covers only the tile it is for.
-  // Chunk `chunk` walks tiles [T0, T1) (at least 8 of them).
-  const int T0 = int(int64_t(chunk) * ntiles / nchunks), T1 = int(int64_t(chunk + 1) * ntiles / nchunks);
-  const int last = T1 - 1;   // 32-bit tile indices (ntiles < 2^19), kept scalar
   auto load_tile = [&](int T, half8 (&f)[3]) __attribute__((always_inline)) {
-    // without records the lane's offset is recomputed here, so that no 64-bit
-    // per-lane address stays live (or spilled) across the walk (with records
-    // the same change makes the allocator spill elsewhere)
+    // the lane's offset is recomputed here, so that no 64-bit per-lane address
+    // stays live (or spilled) across the walk
     const half8* At = A + (T < last ? T : last) * 192;
-    const uint32_t l = kRec ? uint32_t(lane) : lane_now();
+    const uint32_t l = lane_now();
     f[0] = At[l];
     f[1] = At[64 + l];
     f[2] = At[128 + l];
@@ -1113,55 +1044,23 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
   // tile's fragments and those of the other set (tile To, in o).
   auto tile = [&](half8 (&c)[3], int T, half8 (&o)[3], int To)
                   __attribute__((always_inline)) {
-    const uint32_t seedbase = uint32_t(T) * 32u + 1u;
-    {
-      const floatx16 acc0 = bounds(c[0], c[1], c[2], bop[0]);
-      const floatx16 acc1 = bounds(c[0], c[1], c[2], bop[1]);
-      const bool p0 = fold_max(acc0) >= thr[0];
-      const bool p1 = fold_max(acc1) >= thr[1];
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {
+      const floatx16 acc0 = bounds(c[0], c[1], c[2], bop[2 * pr]);
+      const floatx16 acc1 = bounds(c[0], c[1], c[2], bop[2 * pr + 1]);
+      const bool p0 = fold_max(acc0) >= thr[2 * pr];
+      const bool p1 = fold_max(acc1) >= thr[2 * pr + 1];
       const uint64_t m0 = ballot(p0), m1 = ballot(p1);
       if ((m0 | m1) != 0ull) {
-        if constexpr (kRec) {
-          auto rebuild = [&]() __attribute__((always_inline)) {
-            setup();
-            load_tile(T, c);
-            load_tile(To, o);
-          };
-          record(0, acc0, p0, m0, uint32_t(T));
-          if (nrec > kRecCapR - 64) process(rebuild);
-          record(1, acc1, p1, m1, uint32_t(T));
-          if (nrec >= kRecFlushR) process(rebuild);
-        } else {
-          check(I0{}, acc0, p0, seedbase);
-          check(I1{}, acc1, p1, seedbase);
-          if (qcount >= 64 && exact(64)) {
-            load_tile(T, c);
-            load_tile(To, o);
-          }
-        }
-      }
-    }
-    {
-      const floatx16 acc2 = bounds(c[0], c[1], c[2], bop[2]);
-      const floatx16 acc3 = bounds(c[0], c[1], c[2], bop[3]);
-      const bool p2 = fold_max(acc2) >= thr[2];
-      const bool p3 = fold_max(acc3) >= thr[3];
-      const uint64_t m2 = ballot(p2), m3 = ballot(p3);
-      if ((m2 | m3) != 0ull) {
-        if constexpr (kRec) {
-          auto rebuild = [&]() __attribute__((always_inline)) {
-            setup();
-            load_tile(To, o);
-          };
-          record(2, acc2, p2, m2, uint32_t(T));
-          if (nrec > kRecCapR - 64) process(rebuild);
-          record(3, acc3, p3, m3, uint32_t(T));
-          if (nrec >= kRecFlushR) process(rebuild);
-        } else {
-          check(I2{}, acc2, p2, seedbase);
-          check(I3{}, acc3, p3, seedbase);
-          if (qcount >= 64 && exact(64)) load_tile(To, o);
-        }
+        auto rebuild = [&]() __attribute__((always_inline)) {
+          setup();
+          if (pr == 0) load_tile(T, c);
+          load_tile(To, o);
+        };
+        record(2 * pr, acc0, p0, m0, uint32_t(T));
+        if (nrec > kRecCapR - 64) process(rebuild);
+        record(2 * pr + 1, acc1, p1, m1, uint32_t(T));
+        if (nrec >= kRecFlushR) process(rebuild);
       }
     }
   };
@@ -1175,54 +1074,113 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
     load_tile(T + 2, x);
     if (T + 1 < T1) tile(y, T + 1, x, T + 2);
   }
-  if constexpr (kRec) process(setup);
-  exact(1);
+  process(setup);
+  exact_with(1, [] {});
 
   // ---------------------------------------------------------------- results
-  // A chunk before the last hands its best errors on to the next launch (the
-  // seeds are in seed_out already); the last one emits the codes.
-  if (chunk + 1 < nchunks) {
-#pragma unroll
-    for (int nt = 0; nt < kNB; ++nt)
-      if (h == 0 && wave_base + nt * 32 + n < count) carry[blk[nt * 32 + n]] = best[nt * 32 + n];
-    return;
+  for (int i = 0; i < kSlots; i += 64) {
+    const int slot = i + int(lane_now());
+    const uint32_t seed = sbest[slot];
+    merge_best(keys, blk[slot], best[slot], seed, seed != kNoSeed, exact_error);
   }
-  wait_vmem();   // every seed update of this wave is performed
-  // The winning seed of every block, evaluated once more to emit its code.
-  // Every searched block holds a best after the pilot; a valid block without
-  // one is all zero, where every seed ties and the smallest wins.
-#pragma unroll
-  for (int nt = 0; nt < kNB; ++nt) {
-    const bool valid = wave_base + nt * 32 + n < count;
-    const unsigned long long key = best[nt * 32 + n];
-    const bool put = h == 0 && valid && key != ~0ull;
-    const uint64_t mk = ballot(put);
-    if (put)
-      queue[qcount + lanes_below(mk)] =
-          (best_seed(seed_out, blk[nt * 32 + n]) << 8) | kFinal | uint32_t(nt * 32 + n);
-    qcount += __popcll(mk);
-    if (h == 0 && valid && key == ~0ull) {
-      const int64_t b = blk[nt * 32 + n];
-      seed_out[b] = 1u;
-      exp_out[b] = 15;
-      reinterpret_cast<uint2*>(q_out)[b] = make_uint2(0u, 0u);
-      if (err_out) err_out[b] = 0.f;
-    }
-  }
-  exact(1);
 }
 
-// ---------------------------------------------------------------- seed chunks
-// The seed tiles of a large rung are walked in sequential chunks, one launch
-// per chunk of kChunkTiles tiles, so that every wave walks the same 6 MB of
-// projector fragments at about the same time and they stay in L2 (one walk
-// over a 101 MB stack at K = 20 missed L2 on most requests). Each block stays
-// with the same wave position in every launch; a chunk before the last leaves
-// the block's best exact error in the caller's mantissa output (8 bytes per
-// block, 8-byte aligned) and its seed in the seed output, and the next launch
-// starts from them, so only the first runs the pilot and the thresholds are as
-// tight as in one walk. The last chunk emits the codes.
-constexpr int64_t kChunkTiles = 2048;
+// ---------------------------------------------------------------- codes
+// Keys of a single-rung search before its walk (a multi-rung call's keys are
+// cleared by its compaction).
+__global__ void __launch_bounds__(kWaves * 64)
+clear_keys_kernel(unsigned long long* __restrict__ keys, int64_t nblocks) {
+  const int64_t b = int64_t(blockIdx.x) * (kWaves * 64) + threadIdx.x;
+  if (b < nblocks) keys[b] = ~0ull;
+}
+
+// The winning seed of every block of the rung, evaluated once more to emit its
+// code (one block per thread). A block without a key is all zero: every seed
+// ties and the smallest wins, whose evaluation gives e = 15, q = 0 and error 0.
+template <int P>
+__global__ void __launch_bounds__(kWaves * 64)
+emit_codes_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* __restrict__ list,
+                  const int32_t* __restrict__ off, int rung, int K, uint32_t mask,
+                  const uint32_t* __restrict__ ub, const float* __restrict__ pinv32,
+                  const double* __restrict__ pinv64, uint32_t* __restrict__ seed_out,
+                  uint8_t* __restrict__ exp_out, unsigned long long* __restrict__ keys,
+                  float* __restrict__ err_out) {
+  int64_t begin = 0, count = nblocks;
+  if (list) {
+    begin = off[rung];
+    count = int64_t(off[rung + 1]) - begin;
+  }
+  const int64_t i = int64_t(blockIdx.x) * (kWaves * 64) + threadIdx.x;
+  if (i >= count) return;
+  const int64_t b = list ? int64_t(list[begin + i]) : i;
+  const unsigned long long key = keys[b];
+  const uint32_t seed = key == ~0ull ? 1u : uint32_t(key & kKeySeed);
+  float w[kC];
+  load_block(W, b, true, w);
+  int qe, q[P];
+  double err;
+  const double* A = pinv64 + int64_t(seed - 1) * (P * kC);
+  const uint32_t* Ub = ub + int64_t(seed - 1) * basis_words(K, P);
+  if constexpr (complement_dims(P) > 0)
+    err = exact_eval_f32<P>(w, pinv32 + int64_t(seed - 1) * (P * kC), A, Ub, seed, K, mask, qe, q);
+  else
+    err = exact_eval<P, false>(w, A, Ub, seed, K, mask, qe, q);
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const uint32_t byte = uint32_t(uint8_t(int8_t(q[p])));
+    if (p < 4) lo |= byte << (8 * p);
+    else hi |= byte << (8 * (p - 4));
+  }
+  seed_out[b] = seed;
+  exp_out[b] = uint8_t(qe);
+  keys[b] = uint64_t(lo) | uint64_t(hi) << 32;   // the mantissa output, q_0 first
+  if (err_out) err_out[b] = float(err);
+}
+
+// ---------------------------------------------------------------- launch
+// The number of seed ranges of a rung (per unit of blocks; see RangeRule).
+// Bound: a small tensor leaves the chip idle, not the matrix core busy. With one
+// range per block, 1024 x 4096 weights at (12,2)/(16,3)/(20,4) put 250
+// workgroups of the (20,4) rung on 1024 places and took 18.9 ms; 16 016 blocks of
+// that rung took one wave's walk, 18 ms, whatever else the chip could have done.
+// - rmin: never a range longer than kRangeTiles (K >= 17). 2048 tiles are the
+//   6 MB of fragments that a K = 16 walk covers; the workgroups of one range run
+//   together and their L2s keep it, where one walk over the 101 MB of (20,4)
+//   missed on 59 % of its requests. 512 to 4096 tiles measure within 0.2 % on
+//   4096 x 14336 (171.0-171.3 ms).
+// - up to kTargetWorkgroups, ranges of kLongTiles or more: about 12 rounds of
+//   the 1024 places even out the last round. 1024 x 4096, three rungs: 14.0,
+//   13.5, 13.0, 12.8 ms at targets of 1024, 4096, 8192, 12288 (18.9 ms with one
+//   launch per 2048 tiles before); 1023 x 4096 (16,5) 6.4, 5.2, 5.2, 5.2 ms.
+//   Ranges of 32 or 128 tiles instead of 64 are 0-4 % slower ((12,2) on 2.1 M
+//   blocks 1.19 -> 1.21 ms at 32: every range has its own prologue, pilot and
+//   first survivors).
+// - up to kFillWorkgroups, ranges of 8 or more: with fewer workgroups than
+//   places even a short range pays (256 to 1536 measure within 15 %).
+constexpr int64_t kRangeTiles = 2048;
+constexpr int64_t kLongTiles = 64;
+constexpr int kTargetWorkgroups = 12288;
+constexpr int kFillWorkgroups = 768;
+// Launches above this many workgroups are cut (HIP grids hold 2^32 threads).
+constexpr int64_t kMaxGrid = int64_t(1) << 23;
+
+// Block tiles per wave: 4 share each seed-tile fragment and its load. Fewer:
+// - 1, when units of 512 blocks times all the ranges of 8 tiles would not make
+//   kFewWorkgroups: (12,4) on 32 768 blocks 156 -> 68 us, (12,3) on 131 072
+//   156 -> 137 us, (8,6) on 262 144 144 -> 117 us, (10,2) on 524 288 190 us
+//   either way.
+// - 2, at P = 4 below K = 15 ((11,4) on 524 288 blocks 415 -> 335 us, (12,4) on
+//   1 M 1122 -> 950 us, (14,4) 2382 -> 2293 us; (15,4) 3943 -> 3962 us, (16,4)
+//   +2 %, (20,4) +5 % against the rebuilding kernel), at P = 6 ((14,6) 3393 ->
+//   3218 us, (16,6) 8450 -> 8316 us on 524 288 blocks) and at P = 5 below K = 14
+//   ((12,5) on 524 288 blocks 704 -> 596 us; (16,5) +4 %): there the survivors'
+//   registers and not the fragments' loads bound the walk. At P <= 3 two tiles
+//   are 4-14 % slower.
+constexpr int64_t kFewWorkgroups = 6144;
+constexpr bool two_tiles(int K, int P) {
+  return P == 6 || (P == 5 && K < 14) || (P == 4 && K < 15);
+}
 
 int64_t env_int(const char* name, int64_t fallback) {
   if (const char* env = std::getenv(name)) {
@@ -1240,51 +1198,70 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
                          hipStream_t stream) {
   const BasesLayout L = bases_layout(K, P);
   const char* base = static_cast<const char*>(d_bases);
-  const int64_t blocks = (nblocks + kBlocksPerWG - 1) / kBlocksPerWG;
-  if (blocks == 0) return hipSuccess;
-  MfmaArgs a;
-  a.W = d_W;
-  a.nblocks = nblocks;
-  a.list = d_list;
-  a.off = d_off;
-  a.rung = rung;
-  a.K = K;
-  a.mask = lfsr_mask(K);
-  a.ub = reinterpret_cast<const uint32_t*>(base + L.off_ub);
-  a.pinv64 = reinterpret_cast<const double*>(base + L.off_pinv64);
-  a.pinv32 = complement_dims(P) > 0 ? reinterpret_cast<const float*>(base + L.off_pinv32) : nullptr;
-  a.pi16 = reinterpret_cast<const half8*>(base + (complement_dims(P) > 0 ? L.off_nc16 : L.off_pi16));
-  a.ntiles = L.ntiles;
+  if (nblocks == 0) return hipSuccess;
+  const uint32_t mask = lfsr_mask(K);
+  const uint32_t* ub = reinterpret_cast<const uint32_t*>(base + L.off_ub);
+  const double* pinv64 = reinterpret_cast<const double*>(base + L.off_pinv64);
+  const float* pinv32 =
+      complement_dims(P) > 0 ? reinterpret_cast<const float*>(base + L.off_pinv32) : nullptr;
+  const half8* pi16 =
+      reinterpret_cast<const half8*>(base + (complement_dims(P) > 0 ? L.off_nc16 : L.off_pi16));
   const double gamma = std::sqrt(double(P)) * 0x1p-10 * (1.0 + 0x1p-6) + 0x1p-14;
-  a.one_minus_gamma = float(1.0 - gamma);
-  a.seed_out = d_seed;
-  a.exp_out = d_exp;
-  a.q_out = d_q;
-  a.err_out = d_err;
-  // Sequential chunks of the seed tiles (SEEDQ_SEED_CHUNK_TILES overrides the
-  // chunk length; 0 = one chunk; at least 8 tiles per chunk).
-  const int64_t chunk_tiles = env_int("SEEDQ_SEED_CHUNK_TILES", kChunkTiles);
-  const int64_t nseq =
-      chunk_tiles > 0 ? std::max<int64_t>(1, std::min<int64_t>(L.ntiles / 8, L.ntiles / chunk_tiles)) : 1;
-  unsigned long long* carry = reinterpret_cast<unsigned long long*>(d_q);
-  const dim3 grid = dim3(unsigned(blocks), 1u, 1u);
-  for (int64_t c = 0; c < nseq; ++c) {
-    if constexpr (P == 4) {
-      auto kern = search_mfma_remat_kernel<P, false>;
-      if constexpr (P == kRecordP)
-        if (K >= kRecordMinK) kern = search_mfma_remat_kernel<P, true>;
-      hipLaunchKernelGGL(kern, grid, dim3(kWaves * 64), 0,
-                         stream, a.W, a.nblocks, a.list, a.off, a.rung, a.K, a.mask, a.ub, a.pinv64,
-                         a.pi16, a.ntiles, a.one_minus_gamma, a.seed_out, a.exp_out, a.q_out,
-                         a.err_out, int(nseq), int(c), carry);
-    } else {
-      hipLaunchKernelGGL(search_mfma_kernel<P>, grid, dim3(kWaves * 64), 0, stream,
-                         a.W, a.nblocks, a.list, a.off, a.rung, a.K, a.mask, a.ub, a.pinv32,
-                         a.pinv64, a.pi16,
-                         a.ntiles, a.one_minus_gamma, a.seed_out, a.exp_out, a.q_out, a.err_out,
-                         int(nseq), int(c), carry);
-    }
+  const float one_minus_gamma = float(1.0 - gamma);
+  unsigned long long* keys = reinterpret_cast<unsigned long long*>(d_q);
+  const unsigned threads = kWaves * 64;
+  const unsigned per_block = unsigned((nblocks + threads - 1) / threads);
+  if (!d_list)
+    hipLaunchKernelGGL(clear_keys_kernel, dim3(per_block), dim3(threads), 0, stream, keys, nblocks);
+  // SEEDQ_SEED_CHUNK_TILES fixes the range length (0 = one range; at least 8
+  // tiles per range) for testing: the codes are the same for every length.
+  const int64_t tiles = env_int("SEEDQ_SEED_CHUNK_TILES", -1);
+  const int64_t most = std::max<int64_t>(1, L.ntiles / 8);
+  const int nt = (nblocks + kBlocksPerWG - 1) / kBlocksPerWG * most < kFewWorkgroups ? 1
+                 : two_tiles(K, P)                                                  ? 2
+                                                                                    : kNB;
+  const int64_t units = (nblocks + kWaves * 32 * nt - 1) / (kWaves * 32 * nt);
+  RangeRule rule;
+  rule.first = 0;
+  rule.target = rule.fill = 0;
+  rule.rlong = rule.rshort = 1;
+  if (tiles >= 0) {
+    rule.rmin = int32_t(tiles > 0 ? std::max<int64_t>(1, std::min(most, L.ntiles / tiles)) : 1);
+  } else {
+    rule.rmin = int32_t(std::max<int64_t>(1, L.ntiles / kRangeTiles));
+    rule.rlong = int32_t(std::max<int64_t>(1, L.ntiles / kLongTiles));
+    rule.target = kTargetWorkgroups;
+    rule.rshort = int32_t(most);
+    rule.fill = kFillWorkgroups;
   }
+  // a multi-rung call does not know its count of blocks here: the grid holds
+  // every choice that the rule can make, and the workgroups past it return
+  int64_t grid = std::max<int64_t>({units * rule.rmin, rule.target, rule.fill});
+  int64_t step = rule.rmin;
+  rule.span = INT32_MAX;
+  if (grid > kMaxGrid) {   // too many workgroups for one launch: ranges in turn
+    rule.target = rule.fill = 0;
+    step = std::max<int64_t>(1, kMaxGrid / units);
+    rule.span = int32_t(step);
+    grid = units * step;
+  }
+  auto walk = [&](auto kern) {
+    for (; rule.first < rule.rmin; rule.first += int32_t(step))
+      hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(threads), 0, stream, d_W, nblocks, d_list,
+                         d_off, rung, K, mask, ub, pinv32, pinv64, pi16, L.ntiles, one_minus_gamma,
+                         rule, keys);
+  };
+  if (nt == 1) {
+    walk(search_mfma_kernel<P, 1>);
+  } else if (nt == 2) {
+    if constexpr (P >= 4) walk(search_mfma_kernel<P, 2>);
+  } else if constexpr (P == 4) {
+    walk(search_mfma_remat_kernel<P>);
+  } else {
+    if constexpr (P != 6) walk(search_mfma_kernel<P, kNB>);
+  }
+  hipLaunchKernelGGL(emit_codes_kernel<P>, dim3(per_block), dim3(threads), 0, stream, d_W, nblocks,
+                     d_list, d_off, rung, K, mask, ub, pinv32, pinv64, d_seed, d_exp, keys, d_err);
   return hipGetLastError();
 }
 
