@@ -17,8 +17,8 @@
 // range basis and the vectors already chosen (twice, in fp64), the one with
 // the largest remainder taken each time (at least sqrt(remaining dims / 8)).
 // For a rank-deficient seed they span only part of the complement, which
-// keeps the screen's bound valid (a partial sum of its squares). These rungs
-// also get pinv rounded to fp32 (see BasesLayout).
+// keeps the screen's bound valid (a partial sum of its squares). Rungs with many
+// survivors also get pinv rounded to fp32 (see BasesLayout).
 #include "seedq_internal.h"
 
 namespace seedq {
@@ -140,7 +140,7 @@ build_bases_kernel(int K, uint32_t mask, int64_t nseeds, double* __restrict__ pi
   }
 
   // projector Pi = sum over kept j of u_j u_j^T, 2^12-scaled fp16 fragments
-  // (P <= 4; P >= 5 screens with the complement vectors below instead)
+  // (the complement vectors below instead from kComplementMinP on)
   {
     double Un[kC][P];
 #pragma unroll
@@ -148,6 +148,7 @@ build_bases_kernel(int K, uint32_t mask, int64_t nseeds, double* __restrict__ pi
 #pragma unroll
       for (int j = 0; j < P; ++j) Un[i][j] = A[i][j] * inv1[j];
     if constexpr (M == 0) {
+      float E[kC][kC];
 #pragma unroll
       for (int i = 0; i < kC; ++i) {
 #pragma unroll
@@ -155,10 +156,29 @@ build_bases_kernel(int K, uint32_t mask, int64_t nseeds, double* __restrict__ pi
           double v = 0.0;
 #pragma unroll
           for (int j = 0; j < P; ++j) v = fma(Un[i][j], Un[j2][j], v);
-          *pi_at(pair_index(i, j2)) = _Float16(float(v * double(kOperandScale)));
+          v *= double(kOperandScale);
+          const _Float16 r = _Float16(float(v));
+          *pi_at(pair_index(i, j2)) = r;
+          E[i][j2] = E[j2][i] = float(double(r) - v);
         }
       }
-      for (int k = kPairs; k < kPairsPadded; ++k) *pi_at(k) = _Float16(0.0f);
+      // The rounding E of the projector lowers the form of any w by at most
+      // ||E||_2 ||w||^2 <= sqrt(||E^2||_F) ||w||^2, about 0.7 of ||E||_F (in
+      // operand units; fp32, far above its underflow). (1 + 2^-9) covers the
+      // roundings of this sum and of both operands of the margin pair.
+      float s4 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < kC; ++i)
+#pragma unroll
+        for (int j2 = i; j2 < kC; ++j2) {
+          float v = 0.0f;
+#pragma unroll
+          for (int j = 0; j < kC; ++j) v = fmaf(E[i][j], E[j][j2], v);
+          s4 = fmaf(i == j2 ? v : v + v, v, s4);
+        }
+      const float eps = sqrtf(sqrtf(s4)) * (1.0f / kOperandScale);
+      *pi_at(kMarginPair) = _Float16(fmaf(eps * kMarginSeedScale, 1.0f + 0x1p-9f, 0x1p-24f));
+      for (int k = kMarginPair + 1; k < kPairsPadded; ++k) *pi_at(k) = _Float16(0.0f);
     }
 
     if constexpr (M > 0) {
@@ -229,7 +249,7 @@ build_bases_kernel(int K, uint32_t mask, int64_t nseeds, double* __restrict__ pi
 #pragma unroll
       for (int j = 0; j < P; ++j) v = fma(V[p][j] * inv2[j], A[i][j], v);
       P64[p * kC + i] = v;
-      if constexpr (M > 0) pinv32[idx * (P * kC) + p * kC + i] = float(v);
+      if constexpr (many_survivors(P)) pinv32[idx * (P * kC) + p * kC + i] = float(v);
       if (pinv_out) pinv_out[(int64_t(p) * nseeds + idx) * kC + i] = float(v);
     }
   }

@@ -49,6 +49,12 @@ constexpr int kPairs = 36;
 constexpr int kPairsPadded = 48;
 constexpr int kSeedTile = 32;                   // seeds per MFMA tile (rows)
 constexpr float kOperandScale = 4096.0f;        // 2^12 on both fp16 operands
+// One padding pair carries the seed's own margin: the fp16 rounding of its
+// projector can lower the form by at most eps_s ||w||^2, so A holds 2^14 eps_s
+// (rounded up) and B 2^10 ||w||^2 there, and the form comes out that much larger.
+constexpr int kMarginPair = kPairs;
+constexpr float kMarginScale = 1024.0f;             // on ||w||^2 (< 32)
+constexpr float kMarginSeedScale = 16384.0f;        // on eps_s; their product is 2^24
 constexpr int kTileBytes = kPairsPadded * kSeedTile * 2;   // 3 KB per seed tile
 
 // Pair index k of (i, j), i <= j, row-major over the upper triangle.
@@ -56,10 +62,14 @@ __host__ __device__ constexpr int pair_index(int i, int j) { return i * kC - i *
 
 // Rungs whose screen projects blocks onto an orthonormal basis of the
 // complement of range(U(s)) (8 - P vectors per seed) instead of forming the
-// quadratic form w^T Pi_s w: for large P that complement is small, and its
+// quadratic form w^T Pi_s w: at P = 6 that complement is small, and its
 // projection gives the least-squares residual without cancellation.
-constexpr int kComplementMinP = 5;
+constexpr int kComplementMinP = 6;
 __host__ __device__ constexpr int complement_dims(int P) { return P >= kComplementMinP ? kC - P : 0; }
+// Rungs where tens to hundreds of seeds per block pass the screen: their
+// evaluations decide from an fp32 copy of the pseudo-inverse and read the
+// integer basis from the stack.
+__host__ __device__ constexpr bool many_survivors(int P) { return P >= 5; }
 // 2^4 on the complement operand: the squared projections of a block scaled to
 // max |w_i| in [1, 2) stay below 2^13, inside fp16's range (the P = 6 records)
 constexpr float kComplementScale = 16.0f;
@@ -74,14 +84,14 @@ constexpr float kComplementScale = 16.0f;
 //   pi16:   fp16 [ntiles][3][64][8] (empty from kComplementMinP on) 2^12 Pi_s[k]
 //           as MFMA A-operand fragments:
 //           tile T holds seeds 32T+1 .. 32T+32; fragment t, lane l, element e
-//           is pair k = 16t + 8(l/32) + e of seed 32T + (l%32) + 1 (zero for
-//           k >= 36 and for seeds beyond 2^K - 1)
+//           is pair k = 16t + 8(l/32) + e of seed 32T + (l%32) + 1 (k = 36: the
+//           seed's margin, kMarginPair; zero above and for seeds beyond 2^K - 1)
 //   nc16:   fp16 [ntiles][M][64][8], M = complement_dims(P) (empty below
 //           kComplementMinP): MFMA A fragments of the complement basis n_c of
 //           range(U(s)), c < M; fragment c of tile T, lane l, element e is
 //           hi(2^4 n_c[e]) for l < 32 and lo(2^4 n_c[e]) = fp16(2^4 n_c[e] -
 //           hi) for l >= 32, of seed 32T + (l % 32) + 1 (zero beyond 2^K - 1)
-//   pinv32: float [S][P][8] (empty below kComplementMinP): pinv64 rounded to
+//   pinv32: float [S][P][8] (empty unless many_survivors(P)): pinv64 rounded to
 //           fp32, from which the many evaluations of these rungs decide their
 //           exponent and mantissas when the rounding provably cannot matter
 // Widest LFSR whose centred states fit int16 (|x - 2^(K-1)| <= 2^(K-1)).
@@ -107,7 +117,7 @@ inline BasesLayout bases_layout(int K, int P) {
   L.off_nc16 = align256(L.off_pi16 + (complement_dims(P) > 0 ? 0 : size_t(L.ntiles) * kTileBytes));
   L.off_pinv32 = align256(L.off_nc16 + size_t(L.ntiles) * complement_dims(P) * 64 * kC * 2);
   L.total = align256(L.off_pinv32 +
-                     (complement_dims(P) > 0 ? size_t(L.nseeds) * P * kC * sizeof(float) : 0));
+                     (many_survivors(P) ? size_t(L.nseeds) * P * kC * sizeof(float) : 0));
   return L;
 }
 
@@ -162,8 +172,7 @@ hipError_t launch_decompress(const uint32_t* d_seed, const uint8_t* d_exp, const
                              float* d_W_hat, int32_t* d_acc, hipStream_t stream);
 
 // Code stream (seedq_stream.hip). The workspace holds one int64 per chunk of
-// 2048 blocks plus one.
-int64_t stream_chunks(int64_t nblocks);
+// 2048 blocks or per row, whichever is more, plus one.
 size_t stream_workspace_bytes(int64_t nblocks, int64_t nrows);
 hipError_t launch_pack(const uint32_t* d_seed, const uint8_t* d_exp, const int8_t* d_q,
                        const uint8_t* d_rung, const RungTable& rt, int64_t nblocks,

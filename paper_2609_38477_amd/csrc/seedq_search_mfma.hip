@@ -10,13 +10,20 @@
 // v_mfma_f32_32x32x16_f16 with fp16 operands (2^12-scaled projector entries
 // from the basis stack, 2^12-scaled pair products of the block) and fp32
 // accumulation. A candidate passes when its bound can be at most the block's
-// best error so far; the fp16 rounding of the operands is covered by the
-// margin gamma = sqrt(P) 2^-10 (1 + 2^-6) + 2^-14 (relative to ||w||^2), so no
-// candidate that could win is ever skipped. That margin is relative to
-// ||w||^2, while the bound itself is a difference: at P >= 5, where the best
-// errors are small beside ||w||^2, the screen instead computes r_LS directly as
-// the squared projections of w on 8 - P orthonormal vectors orthogonal to
-// range(U(s)) (complement_screen), whose rounding margin is relative to r_LS.
+// best error so far. The fp16 rounding of the operands is covered by a margin
+// that is computed, not assumed: each seed carries a bound on what the rounding
+// of its own projector can take off the form (in one of the padding pairs, so
+// the matrix core adds it), each block one for the rounding of its own pair
+// products (threshold_base). No candidate that could win is ever skipped, and
+// against the worst case of both, sqrt(P) 2^-10 ||w||^2, the margin is about a
+// third: where best errors are near it, the survivors fall by as much (4096 x
+// 14336 at three rungs 167.5 -> 161.5 ms, (16,4) on 524 288 blocks 3.47 -> 3.32
+// ms), and P = 5 can use the form too ((16,5) on 523 776 blocks 5.4 -> 4.3 ms
+// against the complement screen below, whose squares take 48 vector operations a
+// tile). At P = 6, where the best errors are a tenth of the margin's size, the
+// screen computes r_LS directly as the squared projections of w on 2 orthonormal
+// vectors orthogonal to range(U(s)) (complement_screen), whose rounding margin is
+// relative to r_LS.
 //
 // Survivors. Each wave queues its passing (seed, block) pairs in LDS and
 // evaluates them 64 at a time, one per lane, with the exact fp64 evaluation
@@ -45,8 +52,8 @@
 // than the walk over 128 blocks leaves free, so a second kernel rebuilds the
 // block data and reloads the seed-tile fragments after every evaluation batch
 // instead of keeping them live across it, and runs at four waves per SIMD.
-// (P >= 5 screens with the complement projections below, whose block operand is
-// a single fragment, and stays in the first kernel.)
+// (At P >= 5, with many survivors, the evaluations decide from an fp32 copy of
+// the pseudo-inverse, whose registers fit beside the walk of two block tiles.)
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -108,25 +115,64 @@ __device__ __forceinline__ float pair_value(const float (&ws)[kC]) {
   }
 }
 
+// What a block's fp16 operand differs from its pair products, as a symmetric
+// matrix D (its off-diagonal entries are half a pair's difference): the squared
+// Frobenius norm and the trace of the part that this lane rounds, in operand
+// units.
+struct Rounding {
+  float f2 = 0.f, tr = 0.f;
+};
+
 template <int T, int E>
-__device__ __forceinline__ _Float16 b_element(const float (&ws)[kC], int h) {
-  const float z0 = pair_value<16 * T + E>(ws);
-  const float z1 = pair_value<16 * T + 8 + E>(ws);
-  return _Float16(h ? z1 : z0);
+__device__ __forceinline__ _Float16 b_element(const float (&ws)[kC], float ww, int h, Rounding& rd) {
+  constexpr int k0 = 16 * T + E, k1 = k0 + 8;
+  if constexpr (k0 == kMarginPair) {
+    static_assert(kPairTable.i[k1] < 0, "padding in the other half");
+    return _Float16(h ? 0.f : ww * kMarginScale);
+  } else {
+    const float z0 = pair_value<k0>(ws);
+    const float z1 = pair_value<k1>(ws);
+    const float z = h ? z1 : z0;
+    const _Float16 v = _Float16(z);
+    const float d = float(v) - z;
+    constexpr bool g0 = kPairTable.i[k0] == kPairTable.j[k0], g1 = kPairTable.i[k1] == kPairTable.j[k1];
+    const bool g = h ? g1 : g0;
+    rd.f2 = fmaf(d * d, g ? 1.f : 0.5f, rd.f2);
+    if constexpr (g0 || g1) rd.tr += g ? d : 0.f;
+    return v;
+  }
 }
 
 template <int T>
-__device__ __forceinline__ half8 b_fragment(const float (&ws)[kC], int h) {
+__device__ __forceinline__ half8 b_fragment(const float (&ws)[kC], float ww, int h, Rounding& rd) {
   half8 v;
-  v[0] = b_element<T, 0>(ws, h);
-  v[1] = b_element<T, 1>(ws, h);
-  v[2] = b_element<T, 2>(ws, h);
-  v[3] = b_element<T, 3>(ws, h);
-  v[4] = b_element<T, 4>(ws, h);
-  v[5] = b_element<T, 5>(ws, h);
-  v[6] = b_element<T, 6>(ws, h);
-  v[7] = b_element<T, 7>(ws, h);
+  v[0] = b_element<T, 0>(ws, ww, h, rd);
+  v[1] = b_element<T, 1>(ws, ww, h, rd);
+  v[2] = b_element<T, 2>(ws, ww, h, rd);
+  v[3] = b_element<T, 3>(ws, ww, h, rd);
+  v[4] = b_element<T, 4>(ws, ww, h, rd);
+  v[5] = b_element<T, 5>(ws, ww, h, rd);
+  v[6] = b_element<T, 6>(ws, ww, h, rd);
+  v[7] = b_element<T, 7>(ws, ww, h, rd);
   return v;
+}
+
+// ||w||^2 less the block's share of the screen's margin, in accumulator units:
+// what a seed's form must reach with the block's best error subtracted. The
+// rounding D of the block's operand changes the form of a projector Pi of rank
+// r <= P by <Pi, D> = (r/8) tr D + <Pi - (r/8) I, D>, at least
+// min(0, P/8 tr D) - c ||D||_F with c = max over r <= P of sqrt(r - r^2/8) (the
+// Frobenius norm of Pi - (r/8) I). (1 - 2^-15) covers the rest: the fp32 sum of
+// the 48 products, the fp32 roundings of ww, of the pair products (2^-24
+// each), of the threshold itself, and the product of both operands' roundings
+// (2^-20 ||w||^2). Both halves of the wave hold half of the block's pairs.
+template <int P>
+__device__ __forceinline__ float threshold_base(float ww, Rounding rd) {
+  constexpr float c = P == 1 ? 0.9355f : P == 2 ? 1.2248f : P == 3 ? 1.3694f : 1.4143f;
+  rd.f2 += __shfl_xor(rd.f2, 32, 64);
+  rd.tr += __shfl_xor(rd.tr, 32, 64);
+  const float m = fmaf(c * (1.f + 0x1p-10f), sqrtf(rd.f2), fmaxf(0.f, -float(P) / 8.f * rd.tr));
+  return ww * (1.f - 0x1p-15f) * (kOperandScale * kOperandScale) - m * kOperandScale;
 }
 
 #define SEEDQ_INLINE __device__ __attribute__((always_inline)) inline
@@ -197,7 +243,7 @@ SEEDQ_INLINE floatx16 bounds(const half8& a0, const half8& a1, const half8& a2, 
   return acc;
 }
 
-// Complement screen (P >= kComplementMinP): the projections d_c = 2^4 n_c^T w
+// Complement screen (P >= kComplementMinP = 6): the projections d_c = 2^4 n_c^T w
 // of a block on the M complement vectors of 32 seeds are M products with K =
 // 16 (the hi and lo parts of 2^4 n_c against the block's fp16 weights, given
 // twice), and -sum_c d_c^2 is returned so that the max-fold, the records and
@@ -271,7 +317,7 @@ SEEDQ_INLINE unsigned long long load_key(unsigned long long* keys, int64_t b) {
 SEEDQ_INLINE unsigned long long key_bound(unsigned long long key) { return key | kKeySeed; }
 
 // Offers the code (error bits eb, seed s) of block b to its key, one block per
-// lane where `mine`; exact(b, seed) is the exact error of a seed for a block.
+// lane where `mine`; exact(seed) is the exact error of a seed for that block.
 // Every turn of the loop either settles a lane or follows another wave's
 // successful exchange on its key, so it ends.
 template <typename Exact>
@@ -286,7 +332,7 @@ SEEDQ_INLINE void merge_best(unsigned long long* keys, int64_t b, unsigned long 
     if (ballot(tie) != 0ull) {
       if (tie) {
         const uint32_t s2 = uint32_t(cur & kKeySeed);
-        const unsigned long long e2 = (unsigned long long)__double_as_longlong(exact(b, s2));
+        const unsigned long long e2 = (unsigned long long)__double_as_longlong(exact(s2));
         open = eb < e2 || (eb == e2 && s < s2);
       }
     }
@@ -319,28 +365,27 @@ static_assert(kSlots <= 128, "slot must fit 7 bits");
 // threshold of that moment, so the per-seed ballots run once per 64 records
 // instead of once per passing block tile, and records whose block has
 // meanwhile found a better code drop out before the exact evaluation.
-// At P >= 5, where several hundred seeds per block survive the screen, the
-// records wait until 64 of them fill a round (kRecRoundMin; the rest wait for
-// the next call) and a round's passing bounds are compacted by a prefix sum
-// over the lanes instead of one ballot and branch per seed row (measured on
-// 2.1 M blocks: (16,6) 9-10 % and (13..16,5) 6-10 % faster than per-row
-// ballots over rounds of 32-64).
+// At P >= 5, where tens to hundreds of seeds per block survive the screen, the
+// records wait until they fill a round (kRecRoundMin; the rest wait for the next
+// call) and a round's passing bounds are compacted by a prefix sum over the
+// lanes instead of one ballot and branch per seed row (measured on 2.1 M blocks
+// with the complement screen: (16,6) 9-10 % and (13..16,5) 6-10 % faster than
+// per-row ballots over rounds of 32-64).
 template <int P>
 constexpr int kRecFlush = complement_dims(P) > 0 ? 64 : 32;   // records waiting after a pair
 template <int P>
 constexpr int kRecCap = kRecFlush<P> + 64;   // one block tile adds at most 64
 template <int P>
-constexpr int kRecRoundMin = complement_dims(P) > 0 ? 64 : 1;
-// records per round: 64 lanes' worth, or 56 where the quadratic form's fp32
-// records leave the queue that much less LDS (three workgroups per CU need
-// their 13 KB per wave)
+constexpr int kRecRoundMin = complement_dims(P) > 0 ? 64 : many_survivors(P) ? 32 : 1;
+// Records per round: 64 lanes' worth, or fewer where fp32 records, and at P = 5
+// the blocks' weights, leave the queue less LDS (three workgroups per CU need
+// their 13 KB per wave).
 template <int P>
-constexpr int kRecTake = complement_dims(P) > 0 ? 64 : 56;
+constexpr int kRecTake = complement_dims(P) > 0 ? 64 : many_survivors(P) ? 48 : 56;
 template <int P>
 constexpr int kQCapRec = 64 + kRecTake<P> * 16;   // < 64 waiting + one round of records
-// At P >= 5 (complement screen) records hold their bounds as fp16 (16 x 2
-// bytes: two float4 of storage instead of four), which keeps the kernel's LDS
-// at 44 KB with 128 records per wave, three workgroups per CU. The values
+// With the complement screen (P = 6) records hold their bounds as fp16 (16 x 2
+// bytes: two float4 of storage instead of four). The values
 // -sum d^2 lie in fp16's range (sum d^2 <= 2^8 ||w||^2 < 2^13: the complement
 // operand carries 2^4 and the block's power-of-two scaling leaves every |w_i|
 // below 2) and are rounded toward zero, i.e. up, so that a stored bound is
@@ -352,12 +397,12 @@ typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
 
 template <int P, int NT>
 __global__ void __launch_bounds__(kWaves * 64)
-__attribute__((amdgpu_waves_per_eu(NT == 1 && complement_dims(P) > 0 ? 4 : 3)))
+__attribute__((amdgpu_waves_per_eu(3)))
 search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* __restrict__ list,
                    const int32_t* __restrict__ off, int rung, int K, uint32_t mask,
                    const uint32_t* __restrict__ ub, const float* __restrict__ pinv32,
                    const double* __restrict__ pinv64, const half8* __restrict__ pi16,
-                   int64_t ntiles, float one_minus_gamma, RangeRule rule,
+                   int64_t ntiles, RangeRule rule,
                    unsigned long long* __restrict__ keys) {
   constexpr int kS = NT * 32;   // blocks per wave
   __shared__ unsigned long long best_all[kWaves][kS];
@@ -367,10 +412,13 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   // power-of-two scaling of the block: ilogb of its largest |w_i|, down to -149
   // for fp32 subnormals, so 16 bits
   __shared__ int16_t ex_all[kWaves][kS];
-  // 16 bounds per record: fp32, or fp16 at P >= 5 (see half_records)
+  // 16 bounds per record: fp32, or fp16 at P = 6 (see half_records)
   __shared__ float4 rec_all[kWaves][kRecCap<P>][kRecVecs<P>];
   __shared__ uint32_t meta_all[kWaves][kRecCap<P>];
   __shared__ uint32_t queue_all[kWaves][kQCapRec<P>];
+  // the weights of the blocks, where evaluations are many: a gather of 32 bytes
+  // a candidate less (rungs of P = 6 2-10 % faster, P = 5 1 %)
+  __shared__ float4 w_all[kWaves][many_survivors(P) ? kS : 1][2];
 
   const int lane = threadIdx.x & 63;
   // wave-uniform, so that the per-wave LDS addresses are scalar
@@ -430,13 +478,16 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
       ww = fmaf(ws[i], ws[i], ww);
     }
     thr[nt] = active[nt] ? -INFINITY : INFINITY;
+    float base = 0.f;
     if constexpr (M > 0) {
 #pragma unroll
       for (int e = 0; e < kC; ++e) bop[nt][0][e] = _Float16(ws[e]);
     } else {
-      bop[nt][0] = b_fragment<0>(ws, h);
-      bop[nt][1] = b_fragment<1>(ws, h);
-      bop[nt][2] = b_fragment<2>(ws, h);
+      Rounding rd;
+      bop[nt][0] = b_fragment<0>(ws, ww, h, rd);
+      bop[nt][1] = b_fragment<1>(ws, ww, h, rd);
+      bop[nt][2] = b_fragment<2>(ws, ww, h, rd);
+      base = threshold_base<P>(ww, rd);
     }
     // a range starts from the best that the others have left so far
     const unsigned long long bound = valid[nt] ? key_bound(load_key(keys, b)) : ~0ull;
@@ -445,6 +496,10 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
       best[nt * 32 + n] = bound;
       sbest[nt * 32 + n] = kNoSeed;
       blk[nt * 32 + n] = int32_t(b);
+      if constexpr (many_survivors(P)) {
+        w_all[wave][nt * 32 + n][0] = make_float4(w[0], w[1], w[2], w[3]);
+        w_all[wave][nt * 32 + n][1] = make_float4(w[4], w[5], w[6], w[7]);
+      }
       if constexpr (M > 0) {
         // sqrt(M) times the bound on the error of each computed projection,
         // in accumulator units (kComplementScale): fp16 rounding of the
@@ -458,7 +513,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
                                 (0x1p-11f * (1.0f + 0x1p-7f) * norm + 0x1p-20f);
       } else {
         // thresholds live in accumulator units (both operands carry 2^12)
-        slot_thr[nt * 32 + n] = ww * one_minus_gamma * (kOperandScale * kOperandScale);
+        slot_thr[nt * 32 + n] = base;
       }
       slot_ex[nt * 32 + n] = int16_t(ex);
     }
@@ -494,12 +549,18 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
       if (active[nt]) thr[nt] = slot_threshold(nt * 32 + n);
   };
 
-  // Exact error of a seed for block b.
-  auto exact_error = [&](int64_t b, uint32_t seed) __attribute__((always_inline)) {
+  // Exact error of a seed for the block of a slot.
+  auto exact_error = [&](int slot, uint32_t seed) __attribute__((always_inline)) {
     float w[kC];
-    load_block(W, b, true, w);
+    if constexpr (many_survivors(P)) {
+      const float4 lo = w_all[wave][slot][0], hi = w_all[wave][slot][1];
+      w[0] = lo.x; w[1] = lo.y; w[2] = lo.z; w[3] = lo.w;
+      w[4] = hi.x; w[5] = hi.y; w[6] = hi.z; w[7] = hi.w;
+    } else {
+      load_block(W, blk[slot], true, w);
+    }
     int qe, q[P];
-    if constexpr (M > 0)
+    if constexpr (many_survivors(P))
       return exact_eval_f32<P>(w, pinv32 + int64_t(seed - 1) * (P * kC),
                                pinv64 + int64_t(seed - 1) * (P * kC),
                                ub + int64_t(seed - 1) * basis_words(K, P), seed, K, mask, qe, q);
@@ -525,7 +586,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
         seed = ent >> 8;
         slot = int(ent & 0x7Fu);
         if (seed != 0u) {
-          err = exact_error(blk[slot], seed);
+          err = exact_error(slot, seed);
           mine = true;
         }
       }
@@ -583,7 +644,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
       const uint32_t seedbase = (m >> 8) * 32u + 1u;
       const int hh = int((m >> 7) & 1u);
       const uint32_t slot = m & 0x7Fu;
-      if constexpr (M > 0) {
+      if constexpr (many_survivors(P)) {
         // the lane's passing bounds as a mask (t = +inf on lanes without a
         // record), the exclusive prefix sum of their counts over the wave (by
         // the counts' five bit planes), then one queued seed per lane and step
@@ -758,7 +819,8 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   for (int i = 0; i < kS; i += 64) {
     const bool mine = i + lane < kS && sbest[i + lane] != kNoSeed;
     const int slot = mine ? i + lane : 0;
-    merge_best(keys, blk[slot], best[slot], sbest[slot], mine, exact_error);
+    merge_best(keys, blk[slot], best[slot], sbest[slot], mine,
+               [&](uint32_t s2) __attribute__((always_inline)) { return exact_error(slot, s2); });
   }
 }
 
@@ -774,7 +836,7 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
                    const int32_t* __restrict__ off, int rung, int K, uint32_t mask,
                    const uint32_t* __restrict__ ub, const float* __restrict__,
                    const double* __restrict__ pinv64, const half8* __restrict__ pi16,
-                   int64_t ntiles, float one_minus_gamma, RangeRule rule,
+                   int64_t ntiles, RangeRule rule,
                    unsigned long long* __restrict__ keys) {
   // 40 KB in all: four workgroups per CU
   __shared__ unsigned long long best_all[kWaves][kSlots];
@@ -821,21 +883,26 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
       sbest[nt * 32 + n] = kNoSeed;
       blk[nt * 32 + n] = int32_t(b);
     }
+    const bool valid = idx < count;
+    float w[kC];
+    load_block(W, b, valid, w);
+    float amax = 0.f;
+#pragma unroll
+    for (int i = 0; i < kC; ++i) amax = fmaxf(amax, fabsf(w[i]));
+    const int ex = valid && amax > 0.f ? ilogbf(amax) : 0;
+    float ws[kC], ww = 0.f;
+#pragma unroll
+    for (int i = 0; i < kC; ++i) {
+      ws[i] = ldexpf(w[i], -ex);
+      ww = fmaf(ws[i], ws[i], ww);
+    }
+    Rounding rd;
+    b_fragment<0>(ws, ww, h, rd);
+    b_fragment<1>(ws, ww, h, rd);
+    b_fragment<2>(ws, ww, h, rd);
+    const float base = threshold_base<P>(ww, rd);
     if (h == 0) {
-      const bool valid = idx < count;
-      float w[kC];
-      load_block(W, b, valid, w);
-      float amax = 0.f;
-#pragma unroll
-      for (int i = 0; i < kC; ++i) amax = fmaxf(amax, fabsf(w[i]));
-      const int ex = valid && amax > 0.f ? ilogbf(amax) : 0;
-      float ww = 0.f;
-#pragma unroll
-      for (int i = 0; i < kC; ++i) {
-        const float ws = ldexpf(w[i], -ex);
-        ww = fmaf(ws, ws, ww);
-      }
-      slot_thr[nt * 32 + n] = ww * one_minus_gamma * (kOperandScale * kOperandScale);
+      slot_thr[nt * 32 + n] = base;
       slot_ex[nt * 32 + n] = int16_t(ex);
     }
   }
@@ -864,16 +931,16 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
         ws[i] = ldexpf(w[i], -ex);
         ww = fmaf(ws[i], ws[i], ww);
       }
-      bop[nt][0] = b_fragment<0>(ws, h);
-      bop[nt][1] = b_fragment<1>(ws, h);
-      bop[nt][2] = b_fragment<2>(ws, h);
+      Rounding rd;   // (its threshold is in LDS)
+      bop[nt][0] = b_fragment<0>(ws, ww, h, rd);
+      bop[nt][1] = b_fragment<1>(ws, ww, h, rd);
+      bop[nt][2] = b_fragment<2>(ws, ww, h, rd);
       // -inf before a block's first exact error, +inf for blocks not searched
       const unsigned long long key = best[nt * 32 + n];
-      const float thr_base = ww * one_minus_gamma * (kOperandScale * kOperandScale);
       thr[nt] = !active ? INFINITY
                 : key == ~0ull ? -INFINITY
-                : thr_base - __double2float_ru(ldexp(__longlong_as_double((long long)key),
-                                                     24 - 2 * ex));
+                : slot_thr[nt * 32 + n] -
+                      __double2float_ru(ldexp(__longlong_as_double((long long)key), 24 - 2 * ex));
     }
   };
 
@@ -1081,7 +1148,8 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
   for (int i = 0; i < kSlots; i += 64) {
     const int slot = i + int(lane_now());
     const uint32_t seed = sbest[slot];
-    merge_best(keys, blk[slot], best[slot], seed, seed != kNoSeed, exact_error);
+    merge_best(keys, blk[slot], best[slot], seed, seed != kNoSeed, [&](uint32_t s2)
+                   __attribute__((always_inline)) { return exact_error(blk[slot], s2); });
   }
 }
 
@@ -1121,7 +1189,7 @@ emit_codes_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* _
   double err;
   const double* A = pinv64 + int64_t(seed - 1) * (P * kC);
   const uint32_t* Ub = ub + int64_t(seed - 1) * basis_words(K, P);
-  if constexpr (complement_dims(P) > 0)
+  if constexpr (many_survivors(P))
     err = exact_eval_f32<P>(w, pinv32 + int64_t(seed - 1) * (P * kC), A, Ub, seed, K, mask, qe, q);
   else
     err = exact_eval<P, false>(w, A, Ub, seed, K, mask, qe, q);
@@ -1172,14 +1240,14 @@ constexpr int64_t kMaxGrid = int64_t(1) << 23;
 //   either way.
 // - 2, at P = 4 below K = 15 ((11,4) on 524 288 blocks 415 -> 335 us, (12,4) on
 //   1 M 1122 -> 950 us, (14,4) 2382 -> 2293 us; (15,4) 3943 -> 3962 us, (16,4)
-//   +2 %, (20,4) +5 % against the rebuilding kernel), at P = 6 ((14,6) 3393 ->
-//   3218 us, (16,6) 8450 -> 8316 us on 524 288 blocks) and at P = 5 below K = 14
-//   ((12,5) on 524 288 blocks 704 -> 596 us; (16,5) +4 %): there the survivors'
-//   registers and not the fragments' loads bound the walk. At P <= 3 two tiles
-//   are 4-14 % slower.
+//   +2 %, (20,4) +5 % against the rebuilding kernel) and at P >= 5 ((14,6) 3393
+//   -> 3218 us, (16,6) 8450 -> 8316 us on 524 288 blocks; (16,5) on 523 776 5.97
+//   ms with 4 tiles, which spill, 4.5 ms with 2): there the survivors' registers
+//   and not the fragments' loads bound the walk. At P <= 3 two tiles are 4-14 %
+//   slower.
 constexpr int64_t kFewWorkgroups = 6144;
 constexpr bool two_tiles(int K, int P) {
-  return P == 6 || (P == 5 && K < 14) || (P == 4 && K < 15);
+  return P >= 5 || (P == 4 && K < 15);
 }
 
 int64_t env_int(const char* name, int64_t fallback) {
@@ -1203,11 +1271,9 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
   const uint32_t* ub = reinterpret_cast<const uint32_t*>(base + L.off_ub);
   const double* pinv64 = reinterpret_cast<const double*>(base + L.off_pinv64);
   const float* pinv32 =
-      complement_dims(P) > 0 ? reinterpret_cast<const float*>(base + L.off_pinv32) : nullptr;
+      many_survivors(P) ? reinterpret_cast<const float*>(base + L.off_pinv32) : nullptr;
   const half8* pi16 =
       reinterpret_cast<const half8*>(base + (complement_dims(P) > 0 ? L.off_nc16 : L.off_pi16));
-  const double gamma = std::sqrt(double(P)) * 0x1p-10 * (1.0 + 0x1p-6) + 0x1p-14;
-  const float one_minus_gamma = float(1.0 - gamma);
   unsigned long long* keys = reinterpret_cast<unsigned long long*>(d_q);
   const unsigned threads = kWaves * 64;
   const unsigned per_block = unsigned((nblocks + threads - 1) / threads);
@@ -1248,7 +1314,7 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
   auto walk = [&](auto kern) {
     for (; rule.first < rule.rmin; rule.first += int32_t(step))
       hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(threads), 0, stream, d_W, nblocks, d_list,
-                         d_off, rung, K, mask, ub, pinv32, pinv64, pi16, L.ntiles, one_minus_gamma,
+                         d_off, rung, K, mask, ub, pinv32, pinv64, pi16, L.ntiles,
                          rule, keys);
   };
   if (nt == 1) {
@@ -1258,7 +1324,7 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
   } else if constexpr (P == 4) {
     walk(search_mfma_remat_kernel<P>);
   } else {
-    if constexpr (P != 6) walk(search_mfma_kernel<P, kNB>);
+    if constexpr (P < 4) walk(search_mfma_kernel<P, kNB>);
   }
   hipLaunchKernelGGL(emit_codes_kernel<P>, dim3(per_block), dim3(threads), 0, stream, d_W, nblocks,
                      d_list, d_off, rung, K, mask, ub, pinv32, pinv64, d_seed, d_exp, keys, d_err);
