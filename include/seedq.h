@@ -336,8 +336,9 @@ int seedq_decompress_stream(const uint32_t* d_stream, size_t stream_bytes,
  * motivation, section 1; per the appendix on cost the decoder regenerates the
  * LFSR states and does P multiply-adds for each weight). Every weight is the one
  * seedq_decompress_stream would write; the products are accumulated in fp32:
- * for 1, 2 or 4 vectors each lane over every 64th block of the row, then a tree
- * across the lanes; for 8 on the matrix core, each 64-block step of the row
+ * for 1, 2 or 4 vectors each lane over every 64th block of a run of the row (the
+ * row, its halves or its quarters), then a tree across the lanes and the runs in
+ * order; for 8 on the matrix core, each 64-block step of the row
  * split in 16 shares of 4 blocks, a share's products in 8 chained four-term
  * accumulations, the steps added share by share, then the 16 shares summed in
  * a fixed order.

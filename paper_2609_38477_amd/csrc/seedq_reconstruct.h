@@ -75,6 +75,69 @@ __device__ __forceinline__ void block_acc_q(uint32_t s, int K, int P, uint32_t m
   }
 }
 
+// a.i16[kHi] * b.i16[0] + c (one instruction, either half of a register).
+template <int kHi>
+__device__ __forceinline__ int32_t mad_i16(uint32_t a, int32_t b, int32_t c) {
+  int32_t d;
+  if constexpr (kHi)
+    asm("v_mad_i32_i16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  else
+    asm("v_mad_i32_i16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+
+// The integers of two blocks of one rung with K <= 16, their registers packed in
+// one: a step of both takes four instructions (shift, low bits, their product
+// with the feedback mask, and-xor) where each alone takes three, and a state's
+// product with a mantissa reads its half in place (6.1 ns a state and SIMD for
+// one register, 4.6 packed: shifts and bitwise operations issue in two cycles,
+// products and three-operand forms in four). q0, q1: mantissa j in bits 4j..4j+3.
+// K < 16 starts the sums at -2^(K-1) sum_j q_j; at K = 16 a state does not fit a
+// signed half, so the registers hold x - 2^15 (x with its top bit flipped), whose
+// step flips its two top bits more: the feedback term is then 0xC000 or 0xC000 ^
+// mask, base + bit * delta either way.
+__device__ __forceinline__ void block_acc_pair(uint32_t s0, uint32_t s1, uint32_t q0, uint32_t q1,
+                                               int K, int P, uint32_t mask, int32_t (&a0)[kC],
+                                               int32_t (&a1)[kC]) {
+  typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+  const bool top = K == 16;
+  const uint32_t b1 = top ? 0xC000u : 0u, d1 = ((mask ^ b1) - b1) & 0xFFFFu;
+  const ushort2v base = __builtin_bit_cast(ushort2v, b1 | b1 << 16);
+  const ushort2v delta = __builtin_bit_cast(ushort2v, d1 | d1 << 16);
+  uint32_t x = (s0 | s1 << 16) ^ (top ? 0x80008000u : 0u);
+  const uint32_t used = (1u << (4 * P)) - 1u;
+  const int32_t c = top ? 0 : -(int32_t(1) << (K - 1));
+  const int32_t c0 = __mul24(c, __builtin_amdgcn_sdot8(int32_t(q0 & used), 0x11111111, 0, false));
+  const int32_t c1 = __mul24(c, __builtin_amdgcn_sdot8(int32_t(q1 & used), 0x11111111, 0, false));
+  auto step = [&]() __attribute__((always_inline)) {
+    const ushort2v t = __builtin_bit_cast(ushort2v, x & 0x00010001u) * delta + base;
+    // 0x6A: (a and b) xor c; the mask drops the bit that crosses into the low half
+    x = uint32_t(__builtin_amdgcn_bitop3_b32(int(x >> 1), 0x7FFF7FFF, __builtin_bit_cast(int, t),
+                                             0x6A));
+  };
+  // the first coefficient is peeled so that the sums need no set-up
+  {
+    const int32_t m0 = __builtin_amdgcn_sbfe(int32_t(q0), 0, 4);
+    const int32_t m1 = __builtin_amdgcn_sbfe(int32_t(q1), 0, 4);
+#pragma unroll
+    for (int i = 0; i < kC; ++i) {
+      a0[i] = mad_i16<0>(x, m0, c0);
+      a1[i] = mad_i16<1>(x, m1, c1);
+      step();
+    }
+  }
+  for (int j = 1; j < P; ++j) {
+    const int32_t m0 = __builtin_amdgcn_sbfe(int32_t(q0), 4 * j, 4);
+    const int32_t m1 = __builtin_amdgcn_sbfe(int32_t(q1), 4 * j, 4);
+#pragma unroll
+    for (int i = 0; i < kC; ++i) {
+      a0[i] = mad_i16<0>(x, m0, a0[i]);
+      a1[i] = mad_i16<1>(x, m1, a1[i]);
+      step();
+    }
+  }
+}
+
 // q_j is the signed byte j of qw (bytes 0-3 in qw.x, 4-7 in qw.y).
 __device__ __forceinline__ void block_acc(uint32_t s, int K, int P, uint2 qw, int32_t (&acc)[kC]) {
   block_acc_q(s, K, P, lfsr_mask(K), [&](int j) {

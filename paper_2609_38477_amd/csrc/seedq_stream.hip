@@ -6,20 +6,27 @@
 //
 // Layout: blocks in row-major order; inside a block the seed (K bits), the
 // exponent (4 bits) and the mantissas q_0 .. q_{P-1} (4 bits each, two's
-// complement), every field least-significant bit first at increasing stream
-// bit positions; stream bit n is bit n % 32 of 32-bit word n / 32; the payload
-// is padded with zero bits to a whole word.
+// complement), every field least-significant bit first at increasing stream bit
+// positions; stream bit n is bit n % 32 of 32-bit word n / 32; the payload is
+// padded with zero bits to a whole word.
 //
-// Every kernel walks the blocks in chunks of 2048 (one workgroup each): a first
-// pass sums the lengths of every chunk, one workgroup turns the sums into the
-// bit offset of every chunk, and the chunk's workgroup then finds each block's
-// offset with one workgroup prefix sum over the rung lengths of all its eight
-// 256-block iterations at once (eight 16-bit fields in two 64-bit words), so
-// neighbouring threads handle neighbouring blocks, every global access is
-// coalesced and a chunk needs two barriers. Rung constants come from a small
-// table in LDS. The packer assembles its chunk in LDS and stores whole words;
-// only the two words a chunk may share with its neighbours are merged with
-// atomic ORs (they are cleared by the offset pass).
+// Offsets. The blocks are cut into units (2048 blocks for the packer and the
+// parsers, one row for the decode-GEMV). With one rung a unit's bit offset is a
+// product. Otherwise a first pass writes the bits of every unit and of every
+// group of 16 units, and the workgroup that needs an offset adds up the groups
+// and units before it itself (at most 1024 group sums, 4 loads a thread, from
+// L2), which replaced a one-workgroup scan between the passes (4.3-12.7 us of a
+// 23-290 us decode-GEMV). Above kMaxGroups groups that sum would grow with the
+// square of the tensor, and the scan runs.
+//
+// Decoding (fetch_step, use_step). A wave decodes 128 consecutive blocks a step, two per
+// lane. Neighbouring blocks mostly share a rung (an encoder sorts the channels
+// by importance): when all 128 do, offsets are products, the rung's constants
+// are wave-uniform, and for K <= 16 the lane's two LFSRs run packed in one
+// register (block_acc_pair). Otherwise a prefix sum over the lanes gives the
+// offsets and every lane steps its own register. The packer assembles a chunk
+// in LDS; the workgroup in whose chunk a word begins writes that word, so
+// every word is stored once, whole.
 #include <algorithm>
 
 #include "seedq_reconstruct.h"
@@ -28,139 +35,134 @@ namespace seedq {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kIters = 8;
-constexpr int kChunk = kThreads * kIters;  // blocks per workgroup
+constexpr int kWaveBlocks = 512;                 // blocks of a chunk per wave
+constexpr int kChunk = 4 * kWaveBlocks;          // blocks per workgroup
 constexpr int kMaxBlockBits = SEEDQ_MAX_K + 4 + 4 * SEEDQ_MAX_P;
-// bit 31 + every bit of a chunk, plus the two words a code may spill into
-constexpr int kStageWords = (31 + kChunk * kMaxBlockBits) / 32 + 3;
+constexpr int kGroup = 16;                       // units per group
+constexpr int64_t kMaxGroups = 1024;
+constexpr int64_t kMaxUnitBlocks = int64_t(1) << 26;   // a unit's bits fit 32 bits
 
-// Exclusive prefix sums over the workgroup of eight 16-bit fields at once
-// (fields 0-3 in v.x, 4-7 in v.y, field k in bits 16(k mod 4) and up). Every
-// field's workgroup total stays below 2^16 (kThreads codes of at most
-// kMaxBlockBits bits), so the 64-bit sums never carry from one field into the
-// next. *total receives the workgroup totals.
-static_assert(kThreads * kMaxBlockBits < 65536, "a 16-bit field holds one iteration's bits");
-__device__ ulonglong2 wg_exclusive_scan8(ulonglong2 v, ulonglong2* total) {
-  __shared__ unsigned long long wsum[2][kThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned long long a = v.x, b = v.y;
+// The rungs of a stream, with the code lengths of rungs 0..7 as bytes (0 for
+// rungs >= n) for four lookups in one byte permutation.
+struct StreamRungs {
+  RungTable rt;
+  uint32_t len_lo, len_hi;
+};
+
+// Where the bit offset of a unit comes from.
+enum OffsetMode : int32_t { kProduct, kGroups, kScanned };
+struct Offsets {
+  int32_t mode;
+  int64_t unit_bits;          // kProduct: bits of every unit
+  const uint32_t* bits;       // kGroups: bits of every unit
+  const int64_t* sums;        // kGroups: bits of every group; kScanned: offset of every unit
+};
+
+__device__ __forceinline__ int64_t wave_sum(int64_t v) {
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned long long ya = __shfl_up(a, d, 64), yb = __shfl_up(b, d, 64);
-    if (lane >= d) {
-      a += ya;
-      b += yb;
+  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t v) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+
+// Sum of a value over the workgroup (every thread takes part).
+template <int kWavesOfGroup>
+__device__ __forceinline__ int64_t wg_sum(int64_t v) {
+  __shared__ int64_t part[kWavesOfGroup];
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int64_t t = 0;
+#pragma unroll
+  for (int w = 0; w < kWavesOfGroup; ++w) t += part[w];
+  return t;
+}
+
+// This thread's share of the bits before unit u (kGroups).
+__device__ __forceinline__ int64_t groups_share(const Offsets& o, int64_t u) {
+  const int64_t g = u / kGroup;
+  int64_t s = 0;
+  for (int64_t k = threadIdx.x; k < g; k += blockDim.x) s += o.sums[k];
+  const int64_t v = g * kGroup + threadIdx.x;
+  if (threadIdx.x < kGroup && v < u) s += o.bits[v];
+  return s;
+}
+
+// Bits of 8 consecutive blocks from their rung bytes: four lengths per byte
+// permutation (8-byte loads where the run is whole and aligned and every byte
+// below 8, byte loads otherwise).
+__device__ __forceinline__ uint32_t bits_of_8(const uint8_t* __restrict__ rung,
+                                              const StreamRungs& sr, int64_t b0, int64_t b1) {
+  uint32_t sum = 0;
+  if (b0 + 8 <= b1 && (reinterpret_cast<uintptr_t>(rung + b0) & 7u) == 0) {
+    const uint2 v = *reinterpret_cast<const uint2*>(rung + b0);
+    if (((v.x | v.y) & 0xF8F8F8F8u) == 0u) {
+      sum = __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(sr.len_hi, sr.len_lo, v.x), 0u, 0u);
+      return __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(sr.len_hi, sr.len_lo, v.y), 0u, sum);
     }
   }
-  if (lane == 63) {
-    wsum[0][wave] = a;
-    wsum[1][wave] = b;
-  }
-  __syncthreads();
-  unsigned long long ba = 0, bb = 0, ta = 0, tb = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
-    const unsigned long long sa = wsum[0][w], sb = wsum[1][w];
-    ba += (w < wave) ? sa : 0ull;
-    bb += (w < wave) ? sb : 0ull;
-    ta += sa;
-    tb += sb;
-  }
-  __syncthreads();
-  *total = make_ulonglong2(ta, tb);
-  return make_ulonglong2(ba + a - v.x, bb + b - v.y);
-}
-
-__device__ __forceinline__ uint32_t field16(ulonglong2 v, int k) {
-  return uint32_t(((k < 4 ? v.x : v.y) >> (16 * (k & 3))) & 0xFFFFu);
-}
-
-// Lengths of 8 consecutive blocks from their rung bytes (8-byte loads where
-// the run is whole and aligned, byte loads at a ragged end).
-__device__ __forceinline__ uint32_t bits_of_8(const uint8_t* __restrict__ rung, const uint4* tab,
-                                              uint32_t nr, int64_t b0, int64_t nblocks) {
-  if (!rung) {
-    const int64_t n = min(int64_t(8), nblocks - b0);
-    return n > 0 ? uint32_t(n) * tab[0].w : 0u;
-  }
-  uint32_t sum = 0;
-  if (b0 + 8 <= nblocks && (reinterpret_cast<uintptr_t>(rung + b0) & 7u) == 0) {
-    const uint2 v = *reinterpret_cast<const uint2*>(rung + b0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sum += tab[table_index((v.x >> (8 * i)) & 0xFFu, nr)].w;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sum += tab[table_index((v.y >> (8 * i)) & 0xFFu, nr)].w;
-  } else {
-    for (int64_t b = b0; b < min(b0 + 8, nblocks); ++b) sum += tab[table_index(rung[b], nr)].w;
+  for (int64_t b = b0; b < min(b0 + 8, b1); ++b) {
+    const uint32_t r = rung[b];
+    if (r < 8u) sum += ((r < 4u ? sr.len_lo : sr.len_hi) >> (8u * (r & 3u))) & 0xFFu;
   }
   return sum;
 }
 
-// The 64 stream bits from bit pos on, as (lo, hi); false when the len bits at
-// pos are not all inside the stream (then lo and hi are untouched). Bits past
-// len belong to the next block, or are zero past the stream's end.
-__device__ __forceinline__ bool read_window(const uint32_t* __restrict__ stream, int64_t nwords,
-                                            int64_t pos, uint32_t len, uint32_t& lo, uint32_t& hi) {
-  if (len == 0u || pos + int64_t(len) > (nwords << 5)) return false;
-  const int64_t wi = pos >> 5;
-  const uint32_t* sp = stream + wi;
-  uint32_t a, b, c;
-  if (wi + 2 < nwords) {
-    a = sp[0];
-    b = sp[1];
-    c = sp[2];
-  } else {
-    a = sp[0];
-    b = wi + 1 < nwords ? sp[1] : 0u;
-    c = 0u;
-  }
-  const uint32_t sh = uint32_t(pos) & 31u;
-  lo = __builtin_amdgcn_alignbit(b, a, sh);
-  hi = __builtin_amdgcn_alignbit(c, b, sh);
-  return true;
+// Bits of blocks [b0, b1) over one wave, in every lane.
+__device__ __forceinline__ int64_t wave_bits(const uint8_t* __restrict__ rung,
+                                             const StreamRungs& sr, int64_t b0, int64_t b1) {
+  int64_t sum = 0;
+  for (int64_t b = b0 + 8 * int64_t(threadIdx.x & 63); b < b1; b += 512)
+    sum += bits_of_8(rung, sr, b, b1);
+  return wave_sum(sum);
 }
 
+// One workgroup of 16 waves per group: the bits of its 16 units (unit_blocks
+// blocks each), one per wave, and their sum.
+__global__ void __launch_bounds__(64 * kGroup)
+unit_bits_kernel(const uint8_t* __restrict__ rung, StreamRungs sr, int64_t nblocks,
+                 int64_t unit_blocks, uint32_t* __restrict__ bits, int64_t* __restrict__ sums) {
+  const int64_t u = int64_t(blockIdx.x) * kGroup + (threadIdx.x >> 6);
+  const int64_t b0 = u * unit_blocks;
+  const int64_t n = b0 < nblocks ? wave_bits(rung, sr, b0, min(nblocks, b0 + unit_blocks)) : 0;
+  if (b0 < nblocks && (threadIdx.x & 63) == 0) bits[u] = uint32_t(n);
+  const int64_t total = wg_sum<kGroup>((threadIdx.x & 63) == 0 ? n : 0);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+// kScanned, one wave per unit: off[u] = bits of unit u.
 __global__ void __launch_bounds__(kThreads)
-chunk_bits_kernel(const uint8_t* __restrict__ rung, RungTable rt, int64_t nblocks,
-                  int64_t* __restrict__ chunk) {
-  __shared__ uint4 tab[kRungTable];
-  fill_rung_table(tab, rt);
-  __syncthreads();
-  const int64_t b0 = int64_t(blockIdx.x) * kChunk + int64_t(threadIdx.x) * kIters;
-  uint32_t v = bits_of_8(rung, tab, uint32_t(rt.n), b0, nblocks);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  __shared__ uint32_t wsum[kThreads / 64];
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t tot = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) tot += wsum[w];
-    chunk[blockIdx.x] = tot;
-  }
+unit_bits64_kernel(const uint8_t* __restrict__ rung, StreamRungs sr, int64_t nblocks,
+                   int64_t unit_blocks, int64_t nunits, int64_t* __restrict__ off) {
+  const int64_t u = int64_t(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
+  if (u >= nunits) return;
+  const int64_t b0 = u * unit_blocks;
+  const int64_t n = wave_bits(rung, sr, b0, min(nblocks, b0 + unit_blocks));
+  if ((threadIdx.x & 63) == 0) off[u] = n;
 }
 
-// One workgroup: chunk[c] (bits of chunk c) -> chunk[c] = bit offset of chunk c,
-// chunk[nchunks] = total bits, in place. With a stream, also clears the words
-// that hold a chunk boundary, the only words two chunks both write. Each of the
-// 1024 threads owns a contiguous run of chunks and reads it 8 values at a time
-// with independent loads, so the pass is not one load latency per chunk.
+// One workgroup: off[u] (bits of unit u) -> bit offset of unit u, in place. Each
+// of the 1024 threads owns a contiguous run of units and reads it 8 values at a
+// time with independent loads, so the pass is not one load latency per unit.
 constexpr int kScanThreads = 1024;
 constexpr int kScanBatch = 8;
 
 __global__ void __launch_bounds__(kScanThreads)
-chunk_offsets_kernel(int64_t* __restrict__ chunk, int64_t nchunks, uint32_t* __restrict__ stream,
-                     int64_t nwords) {
+unit_offsets_kernel(int64_t* __restrict__ off, int64_t nunits) {
   __shared__ int64_t part[kScanThreads / 64];
-  const int64_t per = (nchunks + kScanThreads - 1) / kScanThreads;
-  const int64_t c0 = min(nchunks, int64_t(threadIdx.x) * per);
-  const int64_t c1 = min(nchunks, c0 + per);
+  const int64_t per = (nunits + kScanThreads - 1) / kScanThreads;
+  const int64_t c0 = min(nunits, int64_t(threadIdx.x) * per);
+  const int64_t c1 = min(nunits, c0 + per);
   int64_t s = 0;
   for (int64_t c = c0; c < c1; c += kScanBatch) {
     int64_t v[kScanBatch];
 #pragma unroll
-    for (int k = 0; k < kScanBatch; ++k) v[k] = c + k < c1 ? chunk[c + k] : 0;
+    for (int k = 0; k < kScanBatch; ++k) v[k] = c + k < c1 ? off[c + k] : 0;
 #pragma unroll
     for (int k = 0; k < kScanBatch; ++k) s += v[k];
   }
@@ -175,100 +177,309 @@ chunk_offsets_kernel(int64_t* __restrict__ chunk, int64_t nchunks, uint32_t* __r
   }
   if (lane == 63) part[wave] = x;
   __syncthreads();
-  int64_t run = x - s, tot = 0;
+  int64_t run = x - s;
 #pragma unroll
-  for (int w = 0; w < kScanThreads / 64; ++w) {
-    run += w < wave ? part[w] : 0;
-    tot += part[w];
-  }
-  if (threadIdx.x == 0) chunk[nchunks] = tot;
+  for (int w = 0; w < kScanThreads / 64; ++w) run += w < wave ? part[w] : 0;
   for (int64_t c = c0; c < c1; c += kScanBatch) {
     int64_t v[kScanBatch];
 #pragma unroll
-    for (int k = 0; k < kScanBatch; ++k) v[k] = c + k < c1 ? chunk[c + k] : 0;
+    for (int k = 0; k < kScanBatch; ++k) v[k] = c + k < c1 ? off[c + k] : 0;
 #pragma unroll
     for (int k = 0; k < kScanBatch; ++k) {
       if (c + k < c1) {
-        chunk[c + k] = run;
-        if (stream && (run >> 5) < nwords) stream[run >> 5] = 0u;
+        off[c + k] = run;
         run += v[k];
       }
     }
   }
-  if (stream && threadIdx.x == 0 && (tot >> 5) < nwords) stream[tot >> 5] = 0u;
 }
 
-// Table index of every block of this thread's eight (8 bits each) and their
-// code lengths as 16-bit fields for wg_exclusive_scan8; blocks past the end
-// take the invalid entry (length 0).
-__device__ __forceinline__ void chunk_lengths(const uint8_t* __restrict__ rung, const uint4* tab,
-                                              uint32_t nr, int64_t base, int64_t nblocks,
-                                              unsigned long long& idx, ulonglong2& len) {
-  idx = 0ull;
-  len = make_ulonglong2(0ull, 0ull);
+// Bit offset of this wave's first block in a chunk of the packer and the
+// parsers (every thread of the 256 takes part; one barrier), and of the chunk.
+__device__ __forceinline__ int64_t chunk_wave_offset(const Offsets& o, const uint8_t* rung,
+                                                     const StreamRungs& sr, int64_t base,
+                                                     int64_t nblocks, int64_t* chunk_off) {
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  if (o.mode == kProduct) {
+    const int64_t len = sr.len_lo & 0xFFu;   // one rung
+    *chunk_off = int64_t(blockIdx.x) * o.unit_bits;
+    return *chunk_off + wave * (kWaveBlocks * len);
+  }
+  // bits of this wave's blocks, and its share of the bits before the chunk
+  const int64_t b0 = base + wave * kWaveBlocks;
+  const uint32_t mine = b0 < nblocks ? uint32_t(wave_bits(rung, sr, b0, min(nblocks, b0 + kWaveBlocks)))
+                                     : 0u;
+  __shared__ uint32_t bits[kThreads / 64];
+  __shared__ int64_t part[kThreads / 64];
+  const int64_t share = o.mode == kGroups ? wave_sum(groups_share(o, blockIdx.x)) : 0;
+  if ((threadIdx.x & 63) == 0) {
+    bits[wave] = mine;
+    part[wave] = share;
+  }
+  __syncthreads();
+  int64_t off = o.mode == kScanned ? o.sums[blockIdx.x] : 0, before = 0;
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) {
-    const int64_t b = base + it * kThreads + threadIdx.x;
-    const uint32_t r = b < nblocks ? table_index(rung ? uint32_t(rung[b]) : 0u, nr) : nr;
-    idx |= (unsigned long long)r << (8 * it);
-    const unsigned long long l = (unsigned long long)tab[r].w << (16 * (it & 3));
-    if (it < 4) len.x |= l;
-    else len.y |= l;
+  for (int w = 0; w < kThreads / 64; ++w) {
+    off += part[w];
+    before += w < wave ? bits[w] : 0u;
+  }
+  *chunk_off = off;
+  return off + before;
+}
+
+// Exclusive prefix sum over the wave and its total, of 32-bit values: shifts
+// within rows of 16 lanes, then the rows' last lanes broadcast to the rows after
+// them (data-parallel primitives: no LDS).
+__device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t v, uint32_t* total) {
+  uint32_t x = v;
+  x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x111, 0xF, 0xF, true));   // row_shr:1
+  x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x112, 0xF, 0xF, true));   // row_shr:2
+  x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x114, 0xF, 0xF, true));   // row_shr:4
+  x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x118, 0xF, 0xF, true));   // row_shr:8
+  x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x142, 0xA, 0xF, false));  // row_bcast:15
+  x += uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x143, 0xC, 0xF, false));  // row_bcast:31
+  *total = uint32_t(__builtin_amdgcn_readlane(int(x), 63));
+  return x - v;
+}
+
+// A code, parsed.
+struct Code {
+  uint32_t seed, q;   // q: mantissa j in bits 4j..4j+3
+  int e;
+  bool ok;            // inside the stream, of a rung of the table
+};
+
+__device__ __forceinline__ Code parse_code(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t bit, int K,
+                                           bool ok) {
+  const uint32_t lo = __builtin_amdgcn_alignbit(w1, w0, bit);
+  const uint32_t hi = __builtin_amdgcn_alignbit(w2, w1, bit);
+  Code c;
+  c.seed = lo & ((1u << K) - 1u);
+  c.e = int((lo >> K) & 15u);
+  c.q = __builtin_amdgcn_alignbit(hi, lo, uint32_t(K + 4));
+  c.ok = ok;
+  return c;
+}
+
+// A wave step: blocks lane and 64 + lane from a place on, two per lane, the three
+// stream words that hold each code and the bit it starts at in them.
+struct Step {
+  uint32_t w[2][3];
+  uint32_t bit[2];
+  uint32_t r[2];      // table index
+  bool ok[2];
+  bool one;           // wave-uniform: all 128 blocks share rung r0, inside the stream
+  uint32_t r0;
+};
+
+// A wave-uniform value that the compiler does not see to be one.
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  return int64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(v)))) |
+         int64_t(__builtin_amdgcn_readfirstlane(int(v >> 32))) << 32;
+}
+
+// Fetches a step: rp = rung bytes from its first block on (null for one rung),
+// left = blocks of the run from there on, run = its first bit, which moves past
+// the step.
+__device__ __forceinline__ Step fetch_step(const uint32_t* __restrict__ stream, int64_t nwords,
+                                           const uint4* tab, uint32_t nr,
+                                           const uint8_t* __restrict__ rp, int64_t left,
+                                           int64_t& run) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t n = uint32_t(left < 128 ? left : 128);
+  Step s;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    s.r[i] = 64 * i + lane < n ? (rp ? table_index(uint32_t(rp[64 * i + lane]), nr) : 0u) : nr;
+  s.r0 = uint32_t(__builtin_amdgcn_readfirstlane(int(s.r[0])));
+  const uint32_t len = uint32_t(__builtin_amdgcn_readfirstlane(int(tab[s.r0].w)));
+  s.one = __builtin_amdgcn_ballot_w64(s.r[0] != s.r0 || s.r[1] != s.r0) == 0ull && len != 0u &&
+          run + int64_t(128 * len) + 96 <= (nwords << 5);
+  if (s.one) {
+    const uint32_t at = uint32_t(run) & 31u;
+    const uint32_t* base = stream + (run >> 5);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      s.bit[i] = at + uint32_t(64 * i + lane) * len;
+      const uint32_t* sp = base + (s.bit[i] >> 5);
+      s.w[i][0] = sp[0];
+      s.w[i][1] = sp[1];
+      s.w[i][2] = sp[2];
+      s.ok[i] = true;
+    }
+    run += int64_t(128 * len);
+    return s;
+  }
+  const uint32_t l0 = tab[s.r[0]].w, l1 = tab[s.r[1]].w;
+  // 64 codes of at most kMaxBlockBits bits fit 16 bits: both sums in one scan
+  static_assert(64 * kMaxBlockBits < 65536, "16 bits hold 64 codes");
+  uint32_t tot;
+  const uint32_t ex = wave_exclusive_scan(l0 | l1 << 16, &tot);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t l = i ? l1 : l0;
+    const int64_t pos = run + int64_t((ex >> (16 * i)) & 0xFFFFu);
+    run += int64_t((tot >> (16 * i)) & 0xFFFFu);
+    s.bit[i] = uint32_t(pos) & 31u;
+    s.ok[i] = l != 0u && pos + int64_t(l) <= (nwords << 5);
+    s.w[i][0] = s.w[i][1] = s.w[i][2] = 0u;
+    if (s.ok[i]) {
+      // words past the stream's end hold no bit of the code
+      const int64_t wi = pos >> 5;
+      const uint32_t* sp = stream + wi;
+      s.w[i][0] = sp[0];
+      if (wi + 1 < nwords) s.w[i][1] = sp[1];
+      if (wi + 2 < nwords) s.w[i][2] = sp[2];
+    }
+  }
+  return s;
+}
+
+// Decodes a fetched step. pair(a, b, K, P, mask) gets both codes of the lane when
+// all 128 blocks share one rung with K <= 16; single(i, c, info) gets block i of
+// the lane otherwise (info = its table entry; c.ok false for a code that is not
+// there).
+template <typename Pair, typename Single>
+__device__ __forceinline__ void use_step(const Step& s, const uint4* tab, Pair&& pair,
+                                         Single&& single) {
+  if (s.one) {
+    const uint4 t0 = tab[s.r0];
+    const int K = __builtin_amdgcn_readfirstlane(int(t0.x)), P = __builtin_amdgcn_readfirstlane(int(t0.y));
+    const uint32_t mask = uint32_t(__builtin_amdgcn_readfirstlane(int(t0.z)));
+    const Code a = parse_code(s.w[0][0], s.w[0][1], s.w[0][2], s.bit[0] & 31u, K, true);
+    const Code b = parse_code(s.w[1][0], s.w[1][1], s.w[1][2], s.bit[1] & 31u, K, true);
+    if (K <= kPackedMaxK) {
+      pair(a, b, K, P, mask);
+    } else {
+      const uint4 info = make_uint4(uint32_t(K), uint32_t(P), mask, 0u);
+      single(0, a, info);
+      single(1, b, info);
+    }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint4 info = tab[s.r[i]];
+    single(i, parse_code(s.w[i][0], s.w[i][1], s.w[i][2], s.bit[i], int(info.x), s.ok[i]), info);
   }
 }
+
+// 2^-(K-1+e), the factor of a block's integers (exact: between 2^-38 and 2^-7),
+// or NaN for a code that is not valid.
+__device__ __forceinline__ float code_scale(int K, int e, bool ok) {
+  return ok ? __builtin_amdgcn_ldexpf(1.0f, 1 - K - e) : __int_as_float(0x7fc00000);
+}
+
+// The integers of both blocks of a lane, unscaled and converted, and their
+// factors. A seed 0 is never emitted: NaN.
+__device__ __forceinline__ void pair_values(const Code& a, const Code& b, int K, int P,
+                                            uint32_t mask, float (&fa)[kC], float& sa,
+                                            float (&fb)[kC], float& sb) {
+  int32_t xa[kC], xb[kC];
+  block_acc_pair(a.seed, b.seed, a.q, b.q, K, P, mask, xa, xb);
+#pragma unroll
+  for (int i = 0; i < kC; ++i) {
+    fa[i] = __int2float_rn(xa[i]);
+    fb[i] = __int2float_rn(xb[i]);
+  }
+  sa = code_scale(K, a.e, a.seed != 0u);
+  sb = code_scale(K, b.e, b.seed != 0u);
+}
+
+__device__ __forceinline__ void one_value(const Code& c, const uint4& info, float (&f)[kC],
+                                          float& s) {
+  const bool ok = c.ok && c.seed != 0u;
+  int32_t x[kC];
+  block_acc_q(ok ? c.seed : 1u, int(info.x), int(info.y), info.z,
+              [&](int j) { return __builtin_amdgcn_sbfe(int32_t(c.q), 4 * j, 4); }, x);
+#pragma unroll
+  for (int i = 0; i < kC; ++i) f[i] = __int2float_rn(x[i]);
+  s = code_scale(int(info.x), c.e, ok);
+}
+
+// The code bits of a block: seed, exponent, the P mantissas (bytes of qw) as
+// nibbles.
+__device__ __forceinline__ uint64_t code_bits(uint32_t seed, uint32_t e, uint2 qw, int K, int P) {
+  auto nibbles = [](uint32_t x) {
+    x &= 0x0F0F0F0Fu;
+    x = (x | x >> 4) & 0x00FF00FFu;
+    return (x | x >> 8) & 0xFFFFu;
+  };
+  const uint32_t q = (nibbles(qw.x) | nibbles(qw.y) << 16) & ((1u << (4 * P)) - 1u);
+  return uint64_t(seed & ((1u << K) - 1u)) | uint64_t((e & 15u) | q << 4) << K;
+}
+
+// ORs a code into the words staged in LDS, from bit pos.
+__device__ __forceinline__ void stage_code(uint32_t* stage, uint32_t pos, uint64_t code) {
+  const int wi = int(pos >> 5), sh = int(pos & 31);
+  const uint64_t lo = code << sh;
+  const uint32_t hi = sh ? uint32_t(code >> (64 - sh)) : 0u;
+  atomicOr(&stage[wi], uint32_t(lo));
+  if (uint32_t(lo >> 32)) atomicOr(&stage[wi + 1], uint32_t(lo >> 32));
+  if (hi) atomicOr(&stage[wi + 2], hi);
+}
+
+// bit 31 + every bit of a chunk, the words that a code may spill into, and the
+// codes that complete the last word (at most 64 blocks past it at a time)
+constexpr int kStageWords = (31 + (kChunk + 64) * kMaxBlockBits) / 32 + 3;
 
 __global__ void __launch_bounds__(kThreads)
 pack_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__ expo,
-            const int8_t* __restrict__ q, const uint8_t* __restrict__ rung, RungTable rt,
-            int64_t nblocks, const int64_t* __restrict__ chunk, uint32_t* __restrict__ stream,
-            int64_t nwords) {
+            const int8_t* __restrict__ q, const uint8_t* __restrict__ rung, StreamRungs sr,
+            int64_t nblocks, Offsets o, uint32_t* __restrict__ stream, int64_t nwords) {
   __shared__ uint32_t stage[kStageWords];
   __shared__ uint4 tab[kRungTable];
-  fill_rung_table(tab, rt);
+  __shared__ int64_t end_s;
+  fill_rung_table(tab, sr.rt);
   const int64_t base = int64_t(blockIdx.x) * kChunk;
-  const int64_t off0 = chunk[blockIdx.x], off1 = chunk[blockIdx.x + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < kStageWords; i += kThreads) stage[i] = 0u;
+  int64_t off0;
+  int64_t run = chunk_wave_offset(o, rung, sr, base, nblocks, &off0);
+  __syncthreads();
   const int64_t w0 = off0 >> 5;
-  const uint32_t shift = uint32_t(off0 & 31);
-  const int nw = int((off1 - (w0 << 5) + 31) >> 5);
-  for (int i = threadIdx.x; i < nw; i += kThreads) stage[i] = 0u;
-  __syncthreads();
-  unsigned long long idx;
-  ulonglong2 len;
-  chunk_lengths(rung, tab, uint32_t(rt.n), base, nblocks, idx, len);
-  ulonglong2 tot;
-  const ulonglong2 ex = wg_exclusive_scan8(len, &tot);
-  uint32_t run = shift;  // bit position inside stage
-#pragma unroll
-  for (int it = 0; it < kIters; ++it) {
-    const int64_t b = base + it * kThreads + threadIdx.x;
-    const uint4 in = tab[(idx >> (8 * it)) & 0xFFu];
-    const uint32_t pos = run + field16(ex, it);
-    run += field16(tot, it);
-    if (in.w) {
-      const int K = int(in.x), P = int(in.y);
-      uint64_t code = uint64_t(seed[b] & ((1u << K) - 1u)) | (uint64_t(expo[b] & 15u) << K);
-      const uint2 qw = reinterpret_cast<const uint2*>(q)[b];
-      for (int j = 0; j < P; ++j) {
-        const uint32_t word = j < 4 ? qw.x : qw.y;
-        code |= uint64_t((word >> (8 * (j & 3))) & 15u) << (K + 4 + 4 * j);
-      }
-      const int wi = int(pos >> 5), sh = int(pos & 31);
-      const uint64_t lo = code << sh;
-      const uint32_t hi = sh ? uint32_t(code >> (64 - sh)) : 0u;
-      atomicOr(&stage[wi], uint32_t(lo));
-      if (uint32_t(lo >> 32)) atomicOr(&stage[wi + 1], uint32_t(lo >> 32));
-      if (hi) atomicOr(&stage[wi + 2], hi);
+  const uint32_t nr = uint32_t(sr.rt.n);
+  // 64 blocks from b0 on, of which those below b1 exist; returns their bits
+  auto put = [&](int64_t b0, int64_t b1, int64_t from) __attribute__((always_inline)) {
+    const int64_t b = b0 + lane;
+    const uint32_t r = b < b1 ? (rung ? table_index(uint32_t(rung[b]), nr) : 0u) : nr;
+    const uint4 in = tab[r];
+    const uint32_t r0 = __builtin_amdgcn_readfirstlane(r);
+    uint32_t ex, tot;
+    if (__builtin_amdgcn_ballot_w64(r != r0) == 0ull) {
+      ex = uint32_t(lane) * in.w;
+      tot = 64u * __builtin_amdgcn_readfirstlane(in.w);
+    } else {
+      ex = wave_exclusive_scan(in.w, &tot);
     }
+    if (in.w)
+      stage_code(stage, uint32_t(from - (w0 << 5)) + ex,
+                 code_bits(seed[b], expo[b], reinterpret_cast<const uint2*>(q)[b], int(in.x),
+                           int(in.y)));
+    return tot;
+  };
+  const int64_t b1 = min(nblocks, base + kChunk);
+  for (int64_t b = base + wave * kWaveBlocks; b < min(b1, base + (wave + 1) * kWaveBlocks); b += 64)
+    run += put(b, b1, run);
+  // the last wave that has blocks completes the chunk's last word from the
+  // blocks that follow (two codes, unless blocks without bits come between)
+  if (wave == int((b1 - base - 1) / kWaveBlocks)) {
+    if (lane == 0) end_s = run;
+    const int64_t word_end = (run + 31) & ~int64_t(31);
+    for (int64_t b = b1; b < nblocks && run < word_end; b += 64) run += put(b, nblocks, run);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < nw; i += kThreads) {
-    const int64_t gw = w0 + i;
-    if (gw < nwords) {
-      const bool shared = (i == 0 && shift != 0) || (i == nw - 1 && (off1 & 31) != 0);
-      if (shared) atomicOr(&stream[gw], stage[i]);
-      else stream[gw] = stage[i];
-    }
-  }
+  // the words that begin inside the chunk
+  const int64_t off1 = end_s, g0 = (off0 + 31) >> 5, g1 = min(nwords, (off1 + 31) >> 5);
+  for (int64_t gw = g0 + threadIdx.x; gw < g1; gw += kThreads) stream[gw] = stage[gw - w0];
+}
+
+// Four mantissa nibbles as sign-extended bytes.
+__device__ __forceinline__ uint32_t nibbles_to_bytes(uint32_t n) {
+  uint32_t t = (n | n << 8) & 0x00FF00FFu;
+  t = (t | t << 4) & 0x0F0F0F0Fu;
+  const uint32_t s = t & 0x08080808u;
+  return t | ((s << 5) - (s << 1));   // 0xF0 where the nibble is negative
 }
 
 // One-pass parse of a chunk: MODE 0 writes the codes (seed, exponent, the P
@@ -278,294 +489,305 @@ pack_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__ expo,
 template <int MODE>
 __global__ void __launch_bounds__(kThreads)
 parse_kernel(const uint32_t* __restrict__ stream, int64_t nwords, const uint8_t* __restrict__ rung,
-             RungTable rt, int64_t nblocks, const int64_t* __restrict__ chunk,
-             uint32_t* __restrict__ seed_out, uint8_t* __restrict__ exp_out,
-             int8_t* __restrict__ q_out, float* __restrict__ W_hat) {
+             StreamRungs sr, int64_t nblocks, Offsets o, uint32_t* __restrict__ seed_out,
+             uint8_t* __restrict__ exp_out, int8_t* __restrict__ q_out, float* __restrict__ W_hat) {
   __shared__ uint4 tab[kRungTable];
-  fill_rung_table(tab, rt);
-  __syncthreads();
+  fill_rung_table(tab, sr.rt);
   const int64_t base = int64_t(blockIdx.x) * kChunk;
-  unsigned long long idx;
-  ulonglong2 len;
-  chunk_lengths(rung, tab, uint32_t(rt.n), base, nblocks, idx, len);
-  ulonglong2 tot;
-  const ulonglong2 ex = wg_exclusive_scan8(len, &tot);
-  int64_t run = chunk[blockIdx.x];
-  // MODE 1: an iteration's 256 blocks are 8 KB of contiguous weights, staged
-  // in LDS (two buffers, so one barrier per iteration) and stored so that
-  // every store instruction of a wave writes 1 KB without gaps.
-  __shared__ float4 stage[MODE == 1 ? 2 : 1][2 * kThreads];
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  int64_t chunk_off;
+  int64_t run = uniform(chunk_wave_offset(o, rung, sr, base, nblocks, &chunk_off));
+  __syncthreads();
+  const int64_t b0 = base + wave * kWaveBlocks, b1 = min(nblocks, b0 + kWaveBlocks);
+  // MODE 1: 64 blocks are 2 KB of contiguous weights, staged in LDS (one region
+  // per wave, no barrier) and stored so that every store instruction of the wave
+  // writes 1 KB without gaps.
+  __shared__ float4 stage_all[kThreads / 64][MODE == 1 ? 128 : 1];
+  float4* stage = stage_all[wave];
+  auto store = [&](int64_t g0, const float (&f)[kC], float s) __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    stage[2 * lane] = make_float4(f[0] * s, f[1] * s, f[2] * s, f[3] * s);
+    stage[2 * lane + 1] = make_float4(f[4] * s, f[5] * s, f[6] * s, f[7] * s);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    float4* dst = reinterpret_cast<float4*>(W_hat + g0 * kC);
+    const int n = 2 * int(min(int64_t(64), b1 - g0));
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) {
-    const int64_t b = base + it * kThreads + threadIdx.x;
-    const uint4 in = tab[(idx >> (8 * it)) & 0xFFu];
-    const int64_t pos = run + field16(ex, it);
-    run += field16(tot, it);
-    if (MODE == 1 || b < nblocks) {  // MODE 1: every thread, for the barrier
-      const int K = int(in.x), P = int(in.y);
-      uint32_t lo = 0u, hi = 0u;
-      const bool ok = read_window(stream, nwords, pos, in.w, lo, hi);
-      const uint32_t s = ok ? lo & ((1u << K) - 1u) : 0u;
-      const int e = ok ? int((lo >> K) & 15u) : 0;
-      const uint32_t qb = ok ? __builtin_amdgcn_alignbit(hi, lo, uint32_t(K + 4)) : 0u;
-      if constexpr (MODE == 0) {
-        uint32_t qx = 0u, qy = 0u;
-        for (int j = 0; j < P; ++j) {
-          const uint32_t byte = uint32_t(__builtin_amdgcn_sbfe(int32_t(qb), 4 * j, 4)) & 0xFFu;
-          if (j < 4) qx |= byte << (8 * j);
-          else qy |= byte << (8 * (j - 4));
-        }
-        seed_out[b] = s;
-        exp_out[b] = uint8_t(e);
-        reinterpret_cast<uint2*>(q_out)[b] = make_uint2(qx, qy);
-      } else {
-        int32_t acc[kC];
-        block_acc_q(ok ? s : 1u, K, P, in.z,
-                    [&](int j) { return __builtin_amdgcn_sbfe(int32_t(qb), 4 * j, 4); }, acc);
-        float o[kC];
-        block_weights(acc, K, e, ok && s != 0u, o);
-        float4* buf = stage[it & 1];
-        buf[2 * threadIdx.x] = make_float4(o[0], o[1], o[2], o[3]);
-        buf[2 * threadIdx.x + 1] = make_float4(o[4], o[5], o[6], o[7]);
-        __syncthreads();
-        const int64_t b0 = base + it * kThreads;
-        const int64_t nlive = nblocks - b0 < kThreads ? nblocks - b0 : kThreads;
-        float4* dst = reinterpret_cast<float4*>(W_hat + b0 * kC);
-        for (int i = threadIdx.x; i < 2 * nlive; i += kThreads) dst[i] = buf[i];
-      }
-    }
+    for (int k = 0; k < 2; ++k)
+      if (64 * k + lane < n) dst[64 * k + lane] = stage[64 * k + lane];
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto code = [&](int64_t g, const Code& c, int P) __attribute__((always_inline)) {
+    const uint32_t q = c.ok ? c.q & ((1u << (4 * P)) - 1u) : 0u;
+    seed_out[g] = c.ok ? c.seed : 0u;
+    exp_out[g] = uint8_t(c.ok ? c.e : 0);
+    reinterpret_cast<uint2*>(q_out)[g] =
+        make_uint2(nibbles_to_bytes(q & 0xFFFFu), nibbles_to_bytes(q >> 16));
+  };
+  auto fetch = [&](int64_t g0) __attribute__((always_inline)) {
+    return fetch_step(stream, nwords, tab, uint32_t(sr.rt.n), rung ? rung + g0 : nullptr, b1 - g0,
+                      run);
+  };
+  if (b0 >= b1) return;
+  // MODE 1: a step's words are loaded one step before they are used
+  Step s = fetch(b0);
+  for (int64_t g0 = b0; g0 < b1; g0 += 128) {
+    Step next;
+    if (MODE == 1 && g0 + 128 < b1) next = fetch(g0 + 128);
+    use_step(
+        s, tab,
+        [&](const Code& a, const Code& b, int K, int P, uint32_t mask)
+            __attribute__((always_inline)) {
+          if constexpr (MODE == 0) {
+            code(g0 + lane, a, P);
+            code(g0 + 64 + lane, b, P);
+          } else {
+            float fa[kC], fb[kC], sa, sb;
+            pair_values(a, b, K, P, mask, fa, sa, fb, sb);
+            store(g0, fa, sa);
+            store(g0 + 64, fb, sb);
+          }
+        },
+        [&](int i, const Code& c, const uint4& info) __attribute__((always_inline)) {
+          const int64_t g = g0 + 64 * i;
+          if constexpr (MODE == 0) {
+            if (g + lane < b1) code(g + lane, c, int(info.y));
+          } else {
+            if (g >= b1) return;   // wave-uniform
+            float f[kC], f2;
+            one_value(c, info, f, f2);
+            store(g, f, f2);
+          }
+        });
+    if (MODE == 1) s = next;
+    else if (g0 + 128 < b1) s = fetch(g0 + 128);
   }
 }
 
 // ---------------------------------------------------------------- decode-GEMV
 // y_v = W_hat x_v for nv right-hand sides, W_hat decoded from the stream on the
 // fly and never stored (the bandwidth motivation of the codec: a GEMV reads
-// l(g)/8 bytes per block instead of 16 for fp16). One wave per row, 256 blocks
-// per wave step as 4 sub-steps of 64 consecutive blocks, one per lane, so the
-// loads of x stay coalesced. The offsets of all four sub-steps come from one
-// wave prefix sum over 64-bit words holding the four bit counts in 16-bit
-// fields (a sub-step holds at most 64 x 52 bits). A block's code is read as
-// one 64-bit window (two funnel shifts of three words); its rung constants (K,
-// P, feedback mask, length) come from a table in LDS. The lane rebuilds the
-// block's integers exactly as seedq_decompress does and forms
+// l(g)/8 bytes per block instead of 16 for fp16). One wave per row, 128 blocks
+// per wave step (decode_step), so the loads of x stay coalesced. The lane
+// rebuilds a block's integers exactly as seedq_decompress does and forms
 // d_v = sum_i fp32(acc_i) x_v[8g + i]; since w_hat_i = fp32(acc_i) 2^-(K-1+e)
-// exactly, d_v 2^-(K-1+e) is the block's partial product up to fp32 rounding.
-// A wave reduction gives y_v[r].
-
-__device__ __forceinline__ uint64_t wave_exclusive_scan64(uint64_t v, uint64_t* total) {
-  const int lane = threadIdx.x & 63;
-  uint64_t x = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
-  }
-  *total = __shfl(x, 63, 64);
-  return x - v;
-}
-
-// Bits of every row (one wave per row), then exclusive row offsets.
-__global__ void __launch_bounds__(kThreads)
-row_bits_kernel(const uint8_t* __restrict__ rung, RungTable rt, int64_t nrows, int64_t G,
-                int64_t* __restrict__ row_off) {
-  __shared__ uint4 tab[kRungTable];
-  fill_rung_table(tab, rt);
-  __syncthreads();
-  const int64_t r = int64_t(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
-  if (r >= nrows) return;
-  const int lane = threadIdx.x & 63;
-  const uint32_t nr = uint32_t(rt.n);
-  int64_t sum = 0;
-  const uint8_t* row = rung ? rung + r * G : nullptr;
-  for (int64_t g = 8 * lane; g < G; g += 8 * 64) sum += bits_of_8(row, tab, nr, g, G);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-  if (lane == 0) row_off[r] = sum;
-}
-
-constexpr int kGemvNB = 4;  // sub-steps of 64 blocks per wave step
-
-// The kernel is bound by issue latency, not bytes: more resident waves hide
-// more of it. One vector fits 64 VGPRs (8 waves per SIMD) and four fit 96 (5
-// waves) without spilling; two keep the compiler's choice. (Eight vectors go
-// to gemv_stream_tile_kernel below.)
+// exactly, d_v 2^-(K-1+e) is the block's partial product up to fp32 rounding. A
+// wave reduction gives y_v[r], with `segs` waves a row each over a run of whole
+// steps and their sums added in order. Bound: the vector ALU regenerating the
+// basis (8P LFSR states a block), not the bytes; 8192 x 28672 at three rungs and
+// 4.0 bits a weight 160 -> 125 us with one vector, 217 -> 159 with four (one
+// block a lane and register, rung constants per lane, one prefix sum a step
+// before).
 template <int NV>
 __global__ void __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(NV == 1 ? 8 : (NV == 4 ? 5 : 1))))
+__attribute__((amdgpu_waves_per_eu(8)))
 gemv_stream_kernel(const uint32_t* __restrict__ stream, int64_t nwords,
-                   const uint8_t* __restrict__ rung, RungTable rt, int64_t nrows, int64_t G,
-                   const int64_t* __restrict__ row_off, const float* __restrict__ x,
-                   int64_t ldx, float* __restrict__ y, int64_t ldy) {
+                   const uint8_t* __restrict__ rung, StreamRungs sr, int64_t nrows, int64_t G,
+                   Offsets o, int segs, const float* __restrict__ x, int64_t ldx,
+                   float* __restrict__ y, int64_t ldy) {
   __shared__ uint4 tab[kRungTable];
-  fill_rung_table(tab, rt);
+  fill_rung_table(tab, sr.rt);
+  constexpr int kWavesPerWG = kThreads / 64;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  // wave = row-in-workgroup * segs + segment of the row
+  const int64_t r0 = int64_t(blockIdx.x) * (kWavesPerWG / segs), r = r0 + wave / segs;
+  const int seg = wave % segs;
+  const int64_t per = ((G + 127) / 128 + segs - 1) / segs * 128;   // blocks per segment
+  const int64_t ga = min(G, seg * per), gb = r < nrows ? min(G, ga + per) : ga;
+  const uint8_t* row = rung && r < nrows ? rung + r * G : nullptr;
+  int64_t run = 0;
+  __shared__ uint32_t seg_bits[kWavesPerWG];
+  __shared__ float seg_sum[NV][kWavesPerWG];
+  if (o.mode == kGroups) {
+    if (segs > 1) {
+      const uint32_t n = row ? uint32_t(wave_bits(row, sr, ga, gb)) : 0u;
+      if (lane == 0) seg_bits[wave] = n;
+    }
+    run = wg_sum<kWavesPerWG>(groups_share(o, r0));
+  }
   __syncthreads();
-  const int64_t r = int64_t(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
-  if (r >= nrows) return;  // wave-uniform
-  const int lane = threadIdx.x & 63;
-  const uint32_t nr = uint32_t(rt.n);
+  if (r < nrows) {
+    if (o.mode == kProduct) {
+      run = r * o.unit_bits + ga * int64_t(sr.len_lo & 0xFFu);
+    } else if (o.mode == kGroups) {
+      for (int64_t k = r0; k < r; ++k) run += o.bits[k];
+      for (int k = 0; k < seg; ++k) run += seg_bits[wave - seg + k];
+    } else {
+      run = o.sums[r];   // one segment
+    }
+  }
+  run = uniform(run);
   float acc[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) acc[v] = 0.f;
-  const uint8_t* row = rung ? rung + r * G : nullptr;
-  int64_t run = row_off[r];
-  for (int64_t g0 = 0; g0 < G; g0 += 64 * kGemvNB) {
-    uint4 info[kGemvNB];
-    uint64_t lbits = 0u;  // bit counts of the lane's blocks, 16 bits per sub-step
+  // the blocks from g0 (wave-uniform) on
+  auto add = [&](int64_t g0, const float (&f)[kC], float s) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < kGemvNB; ++k) {
-      const int64_t g = g0 + 64 * k + lane;
-      info[k] = tab[g < G ? table_index(row ? uint32_t(row[g]) : 0u, nr) : nr];
-      lbits |= uint64_t(info[k].w) << (16 * k);
+    for (int v = 0; v < NV; ++v) {
+      const float4* xv = reinterpret_cast<const float4*>(x + v * ldx + g0 * kC);
+      const float4 x0 = xv[2u * uint32_t(lane)], x1 = xv[2u * uint32_t(lane) + 1u];
+      float d = f[0] * x0.x;
+      d = fmaf(f[1], x0.y, d);
+      d = fmaf(f[2], x0.z, d);
+      d = fmaf(f[3], x0.w, d);
+      d = fmaf(f[4], x1.x, d);
+      d = fmaf(f[5], x1.y, d);
+      d = fmaf(f[6], x1.z, d);
+      d = fmaf(f[7], x1.w, d);
+      acc[v] = fmaf(d, s, acc[v]);   // d s is exact: one rounding
     }
-    uint64_t tot;
-    const uint64_t ex = wave_exclusive_scan64(lbits, &tot);
-#pragma unroll
-    for (int k = 0; k < kGemvNB; ++k) {
-      const int64_t g = g0 + 64 * k + lane;
-      const int64_t pos = run + int64_t((ex >> (16 * k)) & 0xFFFFu);
-      run += int64_t((tot >> (16 * k)) & 0xFFFFu);
-      if (g < G) {
-        const int K = int(info[k].x), P = int(info[k].y);
-        const uint32_t len = info[k].w;
-        uint32_t lo = 0u, hi = 0u;
-        bool ok = read_window(stream, nwords, pos, len, lo, hi);
-        const uint32_t s = lo & ((1u << K) - 1u);
-        const int e = int((lo >> K) & 15u);
-        const uint32_t qb = __builtin_amdgcn_alignbit(hi, lo, uint32_t(K + 4));
-        ok = ok && s != 0u;
-        int32_t a8[kC];
-        block_acc_q(ok ? s : 1u, K, P, info[k].z,
-                    [&](int j) { return __builtin_amdgcn_sbfe(int32_t(qb), 4 * j, 4); }, a8);
-        float f[kC];
-#pragma unroll
-        for (int i = 0; i < kC; ++i) f[i] = __int2float_rn(a8[i]);
-        const int sc = -(K - 1 + e);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const float4* xv = reinterpret_cast<const float4*>(x + v * ldx + g * kC);
-          const float4 x0 = xv[0], x1 = xv[1];
-          float d = f[0] * x0.x;
-          d = fmaf(f[1], x0.y, d);
-          d = fmaf(f[2], x0.z, d);
-          d = fmaf(f[3], x0.w, d);
-          d = fmaf(f[4], x1.x, d);
-          d = fmaf(f[5], x1.y, d);
-          d = fmaf(f[6], x1.z, d);
-          d = fmaf(f[7], x1.w, d);
-          acc[v] += ok ? ldexpf(d, sc) : __int_as_float(0x7fc00000);
-        }
-      }
-    }
+  };
+  for (int64_t g0 = ga; g0 < gb; g0 += 128) {
+    const Step s = fetch_step(stream, nwords, tab, uint32_t(sr.rt.n), row ? row + g0 : nullptr,
+                              gb - g0, run);
+    use_step(
+        s, tab,
+        [&](const Code& a, const Code& b, int K, int P, uint32_t mask)
+            __attribute__((always_inline)) {
+          float fa[kC], fb[kC], sa, sb;
+          pair_values(a, b, K, P, mask, fa, sa, fb, sb);
+          add(g0, fa, sa);
+          add(g0 + 64, fb, sb);
+        },
+        [&](int i, const Code& c, const uint4& info) __attribute__((always_inline)) {
+          const int64_t g = g0 + 64 * i;
+          if (g + lane < gb) {
+            float f[kC], f2;
+            one_value(c, info, f, f2);
+            add(g, f, f2);
+          }
+        });
   }
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     float t = acc[v];
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d, 64);
-    if (lane == 0) y[v * ldy + r] = t;
+    if (segs == 1) {
+      if (lane == 0 && r < nrows) y[v * ldy + r] = t;
+    } else if (lane == 0) {
+      seg_sum[v][wave] = t;
+    }
+  }
+  if (segs > 1) {
+    __syncthreads();
+    if (seg == 0 && lane < NV && r < nrows) {
+      float t = seg_sum[lane][wave];
+      for (int k = 1; k < segs; ++k) t += seg_sum[lane][wave + k];
+      y[lane * ldy + r] = t;
+    }
   }
 }
 
 // Decode-GEMV for eight vectors with the products on the matrix core
 // (v_mfma_f32_16x16x4_f32). A workgroup of 16 waves takes 16 rows, one wave
-// per row decoding 64 consecutive blocks per step exactly as the one-vector
-// kernel does (one block per lane, offsets by a wave prefix sum), into a
-// 16-row tile of weights in LDS (two buffers, one barrier per step). Then
-// wave w multiplies the tile's blocks 4w .. 4w + 3 by the vectors: product m
-// takes A[i][k] = weight m of block 4w + k of row i and B[k][n] = x_n at the
-// same column, so that lane (i, k) reads 8 consecutive weights of the tile and
-// lane (k, n) 8 consecutive entries of x_n. The 16 waves' partial products are
-// summed in a fixed order at the end. Rounding: a product passes through at
-// most 8 matrix-core accumulations of a step (5 + 7 x 4 roundings), one
-// addition per step and the 16-way sum (15). The decode costs the same as in
-// the one-vector kernel, so this pays where that kernel's per-vector
-// multiply-adds outweigh the tile's barrier and LDS traffic: on an 8192 x 28672
-// layer 0.26 against 0.35 ms at eight vectors, but 0.27 against 0.23 at four.
+// per row decoding 128 consecutive blocks per step exactly as the one-vector
+// kernel does, into a 16-row tile of weights in LDS (64 KB: two workgroups per
+// CU). Then wave w multiplies the tile's blocks 4w .. 4w + 3 of either half by
+// the vectors: product m takes A[i][k] = weight m of block 4w + k of row i and
+// B[k][n] = x_n at the same column, so that lane (i, k) reads 8 consecutive
+// weights of the tile and lane (k, n) 8 consecutive entries of x_n. The 16
+// waves' partial products are summed in a fixed order at the end. Rounding: a
+// product passes through at most 8 matrix-core accumulations of its 64 blocks
+// (5 + 7 x 4 roundings), one addition per 64 blocks and the 16-way sum (15). 258
+// -> 204 us on 8192 x 28672; the next step's words are loaded before the products.
 constexpr int kTlRows = 16;
-constexpr int kTlBlocks = 64;                  // blocks per row and step
+constexpr int kTlBlocks = 128;                 // blocks per row and step
 constexpr int kTlStride = kTlBlocks * kC + 4;  // floats per tile row (padded)
 typedef float tl_floatx4 __attribute__((ext_vector_type(4)));
 
 template <int NV>
 __global__ void __launch_bounds__(64 * kTlRows)
 gemv_stream_tile_kernel(const uint32_t* __restrict__ stream, int64_t nwords,
-                        const uint8_t* __restrict__ rung, RungTable rt, int64_t nrows, int64_t G,
-                        const int64_t* __restrict__ row_off, const float* __restrict__ x,
-                        int64_t ldx, float* __restrict__ y, int64_t ldy) {
+                        const uint8_t* __restrict__ rung, StreamRungs sr, int64_t nrows, int64_t G,
+                        Offsets o, const float* __restrict__ x, int64_t ldx, float* __restrict__ y,
+                        int64_t ldy) {
   static_assert(NV >= 1 && NV <= 16, "one B column per vector");
-  static_assert(kTlRows * 4 == kTlBlocks, "each wave multiplies 4 blocks of the tile");
+  static_assert(kTlRows * 8 == kTlBlocks, "each wave multiplies 4 blocks of either half of the tile");
+  static_assert(kTlRows == kGroup, "a workgroup's rows are one group of units");
   __shared__ uint4 tab[kRungTable];
-  __shared__ __attribute__((aligned(16))) float tile[2][kTlRows][kTlStride];
-  fill_rung_table(tab, rt);
-  __syncthreads();
-  const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63);
+  __shared__ __attribute__((aligned(16))) float tile[kTlRows][kTlStride];
+  fill_rung_table(tab, sr.rt);
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = int(threadIdx.x & 63);
   const int i = lane & 15, k = lane >> 4;
-  const int64_t r = int64_t(blockIdx.x) * kTlRows + wave;   // the row this wave decodes
+  const int64_t r0 = int64_t(blockIdx.x) * kTlRows, r = r0 + wave;   // the row this wave decodes
   const bool row_ok = r < nrows;
-  const uint32_t nr = uint32_t(rt.n);
   const uint8_t* row = rung && row_ok ? rung + r * G : nullptr;
-  int64_t run = row_ok ? row_off[r] : 0;
+  int64_t run = o.mode == kGroups ? wg_sum<kTlRows>(groups_share(o, r0)) : 0;
+  __syncthreads();
+  if (row_ok) {
+    if (o.mode == kGroups) run += wave_sum32(lane < wave ? o.bits[r0 + lane] : 0u);
+    else run = o.mode == kProduct ? r * o.unit_bits : o.sums[r];
+  }
   tl_floatx4 sum = {0.f, 0.f, 0.f, 0.f};
-  int buf = 0;
+  auto put = [&](int half, const float (&f)[kC], float s) __attribute__((always_inline)) {
+    float4* dst = reinterpret_cast<float4*>(&tile[wave][(64 * half + lane) * kC]);
+    dst[0] = make_float4(f[0] * s, f[1] * s, f[2] * s, f[3] * s);
+    dst[1] = make_float4(f[4] * s, f[5] * s, f[6] * s, f[7] * s);
+  };
+  const float zero[kC] = {};
+  run = uniform(run);
+  auto fetch = [&](int64_t g0) __attribute__((always_inline)) {
+    return fetch_step(stream, nwords, tab, uint32_t(sr.rt.n), row ? row + g0 : nullptr, G - g0,
+                      run);
+  };
+  Step s;
+  if (row_ok) s = fetch(0);
   for (int64_t g0 = 0; g0 < G; g0 += kTlBlocks) {   // the same trip count in every wave
-    // decode block g0 + lane of row r into the tile
-    const int64_t g = g0 + lane;
-    const bool in = row_ok && g < G;
-    const uint4 info = in ? tab[table_index(row ? uint32_t(row[g]) : 0u, nr)]
-                          : make_uint4(0u, 0u, 0u, 0u);
-    uint64_t tot;
-    const uint64_t ex = wave_exclusive_scan64(uint64_t(info.w), &tot);
-    const int64_t pos = run + int64_t(ex);
-    run += int64_t(tot);
-    float f[kC];
-#pragma unroll
-    for (int e2 = 0; e2 < kC; ++e2) f[e2] = 0.f;
-    if (in) {
-      const int K = int(info.x), P = int(info.y);
-      uint32_t lo = 0u, hi = 0u;
-      bool ok = read_window(stream, nwords, pos, info.w, lo, hi);
-      const uint32_t sd = lo & ((1u << K) - 1u);
-      const int e = int((lo >> K) & 15u);
-      const uint32_t qb = __builtin_amdgcn_alignbit(hi, lo, uint32_t(K + 4));
-      ok = ok && sd != 0u;
-      int32_t a8[kC];
-      block_acc_q(ok ? sd : 1u, K, P, info.z,
-                  [&](int j) { return __builtin_amdgcn_sbfe(int32_t(qb), 4 * j, 4); }, a8);
-      const int sc = -(K - 1 + e);
-#pragma unroll
-      for (int e2 = 0; e2 < kC; ++e2)
-        f[e2] = ok ? ldexpf(__int2float_rn(a8[e2]), sc) : __int_as_float(0x7fc00000);
+    if (row_ok) {
+      use_step(
+          s, tab,
+          [&](const Code& a, const Code& b, int K, int P, uint32_t mask)
+              __attribute__((always_inline)) {
+            float fa[kC], fb[kC], sa, sb;
+            pair_values(a, b, K, P, mask, fa, sa, fb, sb);
+            put(0, fa, sa);
+            put(1, fb, sb);
+          },
+          [&](int half, const Code& c, const uint4& info) __attribute__((always_inline)) {
+            if (g0 + 64 * half + lane < G) {
+              float f[kC], f2;
+              one_value(c, info, f, f2);
+              put(half, f, f2);
+            } else {
+              put(half, zero, 0.f);
+            }
+          });
+      // the next step's words are on their way during the products
+      if (g0 + kTlBlocks < G) s = fetch(g0 + kTlBlocks);
+    } else {
+      put(0, zero, 0.f);
+      put(1, zero, 0.f);
     }
-    float4* dst = reinterpret_cast<float4*>(&tile[buf][wave][lane * kC]);
-    dst[0] = make_float4(f[0], f[1], f[2], f[3]);
-    dst[1] = make_float4(f[4], f[5], f[6], f[7]);
     __syncthreads();
-    // blocks gb = g0 + 4 wave + k of the 16 rows against the vectors
-    const int64_t gb = g0 + 4 * wave + k;
-    const float4* src = reinterpret_cast<const float4*>(&tile[buf][i][(4 * wave + k) * kC]);
-    const float4 a0 = src[0], a1 = src[1];
-    float4 b0 = make_float4(0.f, 0.f, 0.f, 0.f), b1 = b0;
-    if (i < NV && gb < G) {
-      const float4* xv = reinterpret_cast<const float4*>(x + i * ldx + gb * kC);
-      b0 = xv[0];
-      b1 = xv[1];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      // blocks gb = g0 + 64 half + 4 wave + k of the 16 rows against the vectors
+      const int64_t gb = g0 + 64 * half + 4 * wave + k;
+      const float4* src = reinterpret_cast<const float4*>(&tile[i][(64 * half + 4 * wave + k) * kC]);
+      const float4 a0 = src[0], a1 = src[1];
+      float4 b0 = make_float4(0.f, 0.f, 0.f, 0.f), b1 = b0;
+      if (i < NV && gb < G) {
+        const float4* xv = reinterpret_cast<const float4*>(x + i * ldx + gb * kC);
+        b0 = xv[0];
+        b1 = xv[1];
+      }
+      tl_floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, b0.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, b0.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.z, b0.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.w, b0.w, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, b1.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, b1.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.z, b1.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.w, b1.w, acc, 0, 0, 0);
+      sum += acc;
     }
-    tl_floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, b0.x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, b0.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.z, b0.z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.w, b0.w, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, b1.x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, b1.y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.z, b1.z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.w, b1.w, acc, 0, 0, 0);
-    sum += acc;
-    buf ^= 1;
+    __syncthreads();   // the tile is read before the next step writes it
   }
   // lane l of wave w holds rows 4 (l / 16) + v, vector l % 16; the 16 waves'
-  // sums go through the (no longer read) tile
-  __syncthreads();
-  float* part = &tile[0][0][0];
+  // sums go through the tile
+  float* part = &tile[0][0];
 #pragma unroll
   for (int v = 0; v < 4; ++v) part[(wave * 4 + v) * 64 + lane] = sum[v];
   __syncthreads();
@@ -582,52 +804,79 @@ gemv_stream_tile_kernel(const uint32_t* __restrict__ stream, int64_t nwords,
 
 }  // namespace
 
-int64_t stream_chunks(int64_t nblocks) { return (nblocks + kChunk - 1) / kChunk; }
+static int64_t stream_chunks(int64_t nblocks) { return (nblocks + kChunk - 1) / kChunk; }
 
+// One int64 per unit and one more: the sums of kGroups and its 32-bit bits of
+// units, or the offsets of kScanned.
 size_t stream_workspace_bytes(int64_t nblocks, int64_t nrows) {
   const int64_t n = std::max(stream_chunks(nblocks), nrows) + 1;
   return align256(sizeof(int64_t) * size_t(n));
 }
 
-static hipError_t launch_offsets(const uint8_t* d_rung, const RungTable& rt, int64_t nblocks,
-                                 int64_t* chunk, uint32_t* zero_stream, int64_t nwords,
+static StreamRungs stream_rungs(const RungTable& rt) {
+  StreamRungs sr;
+  sr.rt = rt;
+  sr.len_lo = sr.len_hi = 0;
+  for (int r = 0; r < rt.n; ++r)
+    (r < 4 ? sr.len_lo : sr.len_hi) |= uint32_t(rt.K[r] + 4 + 4 * rt.P[r]) << (8 * (r & 3));
+  return sr;
+}
+
+static hipError_t launch_offsets(const uint8_t* d_rung, const StreamRungs& sr, int64_t nblocks,
+                                 int64_t unit_blocks, int64_t nunits, void* d_ws, Offsets* o,
                                  hipStream_t stream) {
-  const int64_t nchunks = stream_chunks(nblocks);
-  if (nchunks > 0)
-    hipLaunchKernelGGL(chunk_bits_kernel, dim3(unsigned(nchunks)), dim3(kThreads), 0, stream, d_rung,
-                       rt, nblocks, chunk);
-  hipLaunchKernelGGL(chunk_offsets_kernel, dim3(1), dim3(kScanThreads), 0, stream, chunk, nchunks,
-                     zero_stream, nwords);
+  o->unit_bits = unit_blocks * int64_t(sr.len_lo & 0xFFu);
+  o->bits = nullptr;
+  o->sums = nullptr;
+  o->mode = kProduct;
+  if (!d_rung || nunits == 0) return hipSuccess;
+  int64_t* sums = static_cast<int64_t*>(d_ws);
+  o->sums = sums;
+  const int64_t ngroups = (nunits + kGroup - 1) / kGroup;
+  if (ngroups <= kMaxGroups && unit_blocks <= kMaxUnitBlocks) {
+    uint32_t* bits = reinterpret_cast<uint32_t*>(sums + ngroups);
+    o->bits = bits;
+    o->mode = kGroups;
+    hipLaunchKernelGGL(unit_bits_kernel, dim3(unsigned(ngroups)), dim3(64 * kGroup), 0, stream, d_rung,
+                       sr, nblocks, unit_blocks, bits, sums);
+  } else {
+    o->mode = kScanned;
+    hipLaunchKernelGGL(unit_bits64_kernel, dim3(unsigned((nunits + 3) / 4)), dim3(kThreads), 0,
+                       stream, d_rung, sr, nblocks, unit_blocks, nunits, sums);
+    hipLaunchKernelGGL(unit_offsets_kernel, dim3(1), dim3(kScanThreads), 0, stream, sums, nunits);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_pack(const uint32_t* d_seed, const uint8_t* d_exp, const int8_t* d_q,
                        const uint8_t* d_rung, const RungTable& rt, int64_t nblocks,
                        uint32_t* d_stream, int64_t nwords, void* d_ws, hipStream_t stream) {
-  int64_t* chunk = static_cast<int64_t*>(d_ws);
-  hipError_t err = launch_offsets(d_rung, rt, nblocks, chunk, d_stream, nwords, stream);
-  if (err != hipSuccess) return err;
   const int64_t nchunks = stream_chunks(nblocks);
   if (nchunks == 0) return hipSuccess;
+  const StreamRungs sr = stream_rungs(rt);
+  Offsets o;
+  const hipError_t err = launch_offsets(d_rung, sr, nblocks, kChunk, nchunks, d_ws, &o, stream);
+  if (err != hipSuccess) return err;
   hipLaunchKernelGGL(pack_kernel, dim3(unsigned(nchunks)), dim3(kThreads), 0, stream, d_seed, d_exp,
-                     d_q, d_rung, rt, nblocks, chunk, d_stream, nwords);
+                     d_q, d_rung, sr, nblocks, o, d_stream, nwords);
   return hipGetLastError();
 }
 
 hipError_t launch_parse(const uint32_t* d_stream, int64_t nwords, const uint8_t* d_rung,
                         const RungTable& rt, int64_t nblocks, void* d_ws, uint32_t* d_seed,
                         uint8_t* d_exp, int8_t* d_q, float* d_W_hat, hipStream_t stream) {
-  int64_t* chunk = static_cast<int64_t*>(d_ws);
-  hipError_t err = launch_offsets(d_rung, rt, nblocks, chunk, nullptr, 0, stream);
-  if (err != hipSuccess) return err;
   const int64_t nchunks = stream_chunks(nblocks);
   if (nchunks == 0) return hipSuccess;
+  const StreamRungs sr = stream_rungs(rt);
+  Offsets o;
+  const hipError_t err = launch_offsets(d_rung, sr, nblocks, kChunk, nchunks, d_ws, &o, stream);
+  if (err != hipSuccess) return err;
   if (d_W_hat)
     hipLaunchKernelGGL(parse_kernel<1>, dim3(unsigned(nchunks)), dim3(kThreads), 0, stream, d_stream,
-                       nwords, d_rung, rt, nblocks, chunk, nullptr, nullptr, nullptr, d_W_hat);
+                       nwords, d_rung, sr, nblocks, o, nullptr, nullptr, nullptr, d_W_hat);
   else
     hipLaunchKernelGGL(parse_kernel<0>, dim3(unsigned(nchunks)), dim3(kThreads), 0, stream, d_stream,
-                       nwords, d_rung, rt, nblocks, chunk, d_seed, d_exp, d_q, nullptr);
+                       nwords, d_rung, sr, nblocks, o, d_seed, d_exp, d_q, nullptr);
   return hipGetLastError();
 }
 
@@ -635,30 +884,39 @@ hipError_t launch_gemv_stream(const uint32_t* d_stream, int64_t nwords, const ui
                               const RungTable& rt, int64_t nrows, int64_t ncols, void* d_ws,
                               const float* d_x, int64_t ldx, float* d_y, int64_t ldy, int nv,
                               hipStream_t stream) {
-  int64_t* row_off = static_cast<int64_t*>(d_ws);
   const int64_t G = ncols / kC;
-  const unsigned grid = unsigned((nrows + kThreads / 64 - 1) / (kThreads / 64));
-  hipLaunchKernelGGL(row_bits_kernel, dim3(grid), dim3(kThreads), 0, stream, d_rung, rt, nrows, G,
-                     row_off);
-  hipLaunchKernelGGL(chunk_offsets_kernel, dim3(1), dim3(kScanThreads), 0, stream, row_off, nrows,
-                     nullptr, int64_t(0));
+  const StreamRungs sr = stream_rungs(rt);
+  Offsets o;
+  const hipError_t err = launch_offsets(d_rung, sr, nrows * G, G, nrows, d_ws, &o, stream);
+  if (err != hipSuccess) return err;
+  // Waves per row. A row's wave goes through its steps one after the other, so
+  // few rows leave the chip waiting: 4096 x 4096 (four steps a row) with one
+  // vector 19.6, 19.4 and 24.0 us at 1, 2 and 4 waves a row, 4096 x 14336 46.8,
+  // 42.2 and 45.1, 8192 x 28672 130, 128 and 130, 200 rows of 2000 blocks 20.1,
+  // 13.1 and 13.3; four vectors, whose waves do more between their loads, 57,
+  // 63 and 66 us on 4096 x 14336.
+  const int segs = o.mode == kScanned ? 1
+                   : nrows < 2048     ? 4
+                   : nrows < 4096     ? (nv == 4 ? 2 : 4)
+                                      : (nv == 4 ? 1 : 2);
+  const unsigned grid = unsigned((nrows * segs + kThreads / 64 - 1) / (kThreads / 64));
   switch (nv) {
     case 1:
       hipLaunchKernelGGL(gemv_stream_kernel<1>, dim3(grid), dim3(kThreads), 0, stream, d_stream,
-                         nwords, d_rung, rt, nrows, G, row_off, d_x, ldx, d_y, ldy);
+                         nwords, d_rung, sr, nrows, G, o, segs, d_x, ldx, d_y, ldy);
       break;
     case 2:
       hipLaunchKernelGGL(gemv_stream_kernel<2>, dim3(grid), dim3(kThreads), 0, stream, d_stream,
-                         nwords, d_rung, rt, nrows, G, row_off, d_x, ldx, d_y, ldy);
+                         nwords, d_rung, sr, nrows, G, o, segs, d_x, ldx, d_y, ldy);
       break;
     case 4:
       hipLaunchKernelGGL(gemv_stream_kernel<4>, dim3(grid), dim3(kThreads), 0, stream, d_stream,
-                         nwords, d_rung, rt, nrows, G, row_off, d_x, ldx, d_y, ldy);
+                         nwords, d_rung, sr, nrows, G, o, segs, d_x, ldx, d_y, ldy);
       break;
     case 8:
       hipLaunchKernelGGL(gemv_stream_tile_kernel<8>, dim3(unsigned((nrows + kTlRows - 1) / kTlRows)),
-                         dim3(64 * kTlRows), 0, stream, d_stream, nwords, d_rung, rt, nrows, G,
-                         row_off, d_x, ldx, d_y, ldy);
+                         dim3(64 * kTlRows), 0, stream, d_stream, nwords, d_rung, sr, nrows, G, o,
+                         d_x, ldx, d_y, ldy);
       break;
     default:
       return hipErrorInvalidValue;

@@ -1,0 +1,80 @@
+"""The stream kernels where neighbouring blocks share a rung (wave steps of 128 blocks with one
+rung, two packed registers for K <= 16), at the edges of such runs, across blocks without bits, and
+with the offsets taken from group sums or from the scan. Packed words, codes and weights are
+bit-exact; the decode-GEMV is held to its fp32 bound."""
+import numpy as np
+import pytest
+
+from oracle import stream as ostream
+from test_gpu_stream import _codes, _t, _words, sq  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# every P and the registers at the edges of the packed path (8, 15, 16 | 17, 24)
+RUNGS = [(8, 1), (9, 2), (15, 3), (16, 4), (16, 5), (12, 6), (17, 3), (24, 6)]
+
+
+def _check(sq, oq, rob, rungs, nrows, ncols, nvecs=(1, 4, 8)):
+    rng = np.random.default_rng(len(rob) + nrows)
+    seed, exp, q = _codes(rng, rob, rungs)
+    valid = rob < len(rungs)
+    ref = ostream.pack(seed[valid], exp[valid], q[valid], rob[valid], rungs)
+    cnt = np.bincount(rob[valid], minlength=len(rungs))
+    d = _t(rob) if len(rungs) > 1 else None
+    w = sq.pack(_t(seed.view(np.int32)), _t(exp), _t(q), rungs, nrows, ncols, d, cnt)
+    assert np.array_equal(_words(w), ref)
+    s, e, qq = (t.cpu().numpy() for t in sq.unpack(w, rungs, nrows, ncols, d))
+    assert np.array_equal(s.view(np.uint32)[valid], seed[valid]) and np.all(s[~valid] == 0)
+    assert np.array_equal(e[valid], exp[valid]) and np.array_equal(qq[valid], q[valid])
+    Wh = sq.decompress_stream(w, rungs, nrows, ncols, d).cpu().numpy()
+    K = np.array([rungs[r][0] if r < len(rungs) else 8 for r in rob])
+    P = np.array([rungs[r][1] if r < len(rungs) else 1 for r in rob])
+    want, _ = oq.decompress(seed[valid], exp[valid], q[valid], K[valid], P[valid])
+    got = Wh.reshape(-1, 8)
+    assert np.array_equal(got[valid], np.asarray(want, dtype=np.float32).reshape(-1, 8))
+    assert np.isnan(got[~valid]).all()
+    G = ncols // 8
+    x = rng.normal(0, 1, (8, ncols)).astype(np.float32)
+    exact = np.where(np.isnan(Wh), 0, Wh).astype(np.float64) @ x.T.astype(np.float64)
+    size = np.abs(np.where(np.isnan(Wh), 0, Wh)).astype(np.float64) @ np.abs(x.T).astype(np.float64)
+    bad = np.isnan(Wh).any(1)
+    for nv in nvecs:
+        y = sq.gemv_stream(w, rungs, nrows, ncols, _t(x[:nv]), d).cpu().numpy().T
+        # a lane's chain of at most 8 products a block over every 64th block, the
+        # lanes' and the segments' sums; the matrix-core kernel's shares
+        n = 8 * -(-G // 64) + 58
+        assert np.all(np.abs(y - exact[:, :nv])[~bad] <= n * 2.0 ** -24 * size[:, :nv][~bad])
+        assert np.isnan(y[bad]).all()
+
+
+@pytest.mark.parametrize("nrows,G", [(1, 128), (3, 300), (17, 1031), (2, 2048), (40, 257)])
+def test_runs_of_one_rung(sq, oq, nrows, G):  # noqa: F811
+    # rungs in runs of 1 to 700 blocks across rows, so that wave steps fall inside
+    # a run, on its edge and across several
+    rng = np.random.default_rng(G)
+    rob = np.concatenate([np.full(int(rng.integers(1, 700)), r % len(RUNGS), np.uint8)
+                          for r in rng.permutation(3 * (nrows * G // 100 + 8))])[:nrows * G]
+    _check(sq, oq, rob, RUNGS, nrows, 8 * G)
+
+
+@pytest.mark.parametrize("K,P", RUNGS)
+def test_one_rung_without_rung_bytes(sq, oq, K, P):  # noqa: F811
+    # offsets are products; 2100 blocks a row: a ragged last step and chunk
+    _check(sq, oq, np.zeros(2 * 2100, np.uint8), [(K, P)], 2, 8 * 2100)
+
+
+def test_words_across_blocks_without_bits(sq, oq):  # noqa: F811
+    # a word's codes may lie in chunks far apart: thousands of blocks without bits
+    # between two codes, whole chunks of them, and at both ends
+    rob = np.full(5 * 2048 + 77, 255, np.uint8)
+    rob[[5, 6, 2047, 2048, 2049, 7000, 7001, 7002, 9000, 10239, 10240]] = [0, 1, 0, 1, 0, 1, 1, 0, 1, 0, 0]
+    rob[4096:4200] = 1
+    _check(sq, oq, rob, [(8, 1), (9, 2)], 1, 8 * len(rob), nvecs=())
+
+
+def test_more_rows_than_group_sums_reach(sq, oq):  # noqa: F811
+    # above 1024 groups of 16 rows the decode-GEMV takes its offsets from the scan
+    nrows, G = 16 * 1024 + 9, 3
+    rng = np.random.default_rng(4)
+    _check(sq, oq, rng.integers(0, 3, nrows * G).astype(np.uint8), [(8, 1), (16, 3), (20, 4)], nrows,
+           8 * G)
