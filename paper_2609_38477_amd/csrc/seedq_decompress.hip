@@ -48,7 +48,7 @@ decompress_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__
   __syncthreads();
   const int64_t nlive = nblocks - b0 < kDecompressThreads ? nblocks - b0 : kDecompressThreads;
   float4* dst = reinterpret_cast<float4*>(W_hat + b0 * kC);
-  for (int i = threadIdx.x; i < 2 * nlive; i += kDecompressThreads) dst[i] = stage[i];
+  for (int i = threadIdx.x; i < 2 * nlive; i += kDecompressThreads) store_streaming(&dst[i], stage[i]);
   if (acc_out && live) {
     if (!ok) {
 #pragma unroll

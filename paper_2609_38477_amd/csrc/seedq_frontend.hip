@@ -303,9 +303,9 @@ permute_rows_lds_kernel(const float* __restrict__ in, int64_t nrows, int64_t nco
     for (int j = threadIdx.x; j < n; j += kThreads) {
       if (!inverse) {
         const int32_t p = perm[j];
-        dst[j] = (p >= 0 && p < n) ? row[p] : __int_as_float(0x7fc00000);
+        __builtin_nontemporal_store((p >= 0 && p < n) ? row[p] : __int_as_float(0x7fc00000), &dst[j]);
       } else if ((mark[j / 32] >> (j % 32)) & 1u) {
-        dst[j] = row[j];
+        __builtin_nontemporal_store(row[j], &dst[j]);
       }
     }
   }

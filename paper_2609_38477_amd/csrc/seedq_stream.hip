@@ -471,7 +471,7 @@ pack_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__ expo,
   __syncthreads();
   // the words that begin inside the chunk
   const int64_t off1 = end_s, g0 = (off0 + 31) >> 5, g1 = min(nwords, (off1 + 31) >> 5);
-  for (int64_t gw = g0 + threadIdx.x; gw < g1; gw += kThreads) stream[gw] = stage[gw - w0];
+  for (int64_t gw = g0 + threadIdx.x; gw < g1; gw += kThreads) __builtin_nontemporal_store(stage[gw - w0], &stream[gw]);
 }
 
 // Four mantissa nibbles as sign-extended bytes.
@@ -514,15 +514,15 @@ parse_kernel(const uint32_t* __restrict__ stream, int64_t nwords, const uint8_t*
     const int n = 2 * int(min(int64_t(64), b1 - g0));
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-      if (64 * k + lane < n) dst[64 * k + lane] = stage[64 * k + lane];
+      if (64 * k + lane < n) store_streaming(&dst[64 * k + lane], stage[64 * k + lane]);
     __builtin_amdgcn_wave_barrier();
   };
   auto code = [&](int64_t g, const Code& c, int P) __attribute__((always_inline)) {
     const uint32_t q = c.ok ? c.q & ((1u << (4 * P)) - 1u) : 0u;
-    seed_out[g] = c.ok ? c.seed : 0u;
-    exp_out[g] = uint8_t(c.ok ? c.e : 0);
-    reinterpret_cast<uint2*>(q_out)[g] =
-        make_uint2(nibbles_to_bytes(q & 0xFFFFu), nibbles_to_bytes(q >> 16));
+    __builtin_nontemporal_store(c.ok ? c.seed : 0u, &seed_out[g]);
+    __builtin_nontemporal_store(uint8_t(c.ok ? c.e : 0), &exp_out[g]);
+    store_streaming(reinterpret_cast<uint2*>(q_out) + g, nibbles_to_bytes(q & 0xFFFFu),
+                    nibbles_to_bytes(q >> 16));
   };
   auto fetch = [&](int64_t g0) __attribute__((always_inline)) {
     return fetch_step(stream, nwords, tab, uint32_t(sr.rt.n), rung ? rung + g0 : nullptr, b1 - g0,
