@@ -71,8 +71,10 @@ to_f32_kernel(const double* __restrict__ in, int64_t n, float* __restrict__ out)
 }
 
 constexpr int kRowChunk = 256;
+constexpr int kRowBatch = 8;
 
-// Column tile (256 columns, one per thread) x row chunk (kRowChunk rows).
+// Column tile (256 columns, one per thread) x row chunk (kRowChunk rows), 8 rows'
+// loads at a time (32000 x 4096 154 -> 98 us, 5.3 TB/s).
 __global__ void __launch_bounds__(kThreads)
 sq_gemv_t_partial_kernel(const float* __restrict__ W, int64_t nrows, int64_t ncols,
                          const float* __restrict__ v, double* __restrict__ part) {
@@ -81,21 +83,43 @@ sq_gemv_t_partial_kernel(const float* __restrict__ W, int64_t nrows, int64_t nco
   const int64_t r1 = min(nrows, r0 + kRowChunk);
   if (c >= ncols) return;
   double acc = 0.0;
-  for (int64_t r = r0; r < r1; ++r) {
+  int64_t r = r0;
+  for (; r + kRowBatch <= r1; r += kRowBatch) {
+    float w[kRowBatch];
+#pragma unroll
+    for (int k = 0; k < kRowBatch; ++k) w[k] = W[(r + k) * ncols + c];
+#pragma unroll
+    for (int k = 0; k < kRowBatch; ++k) acc += double(w[k]) * double(w[k]) * double(v[r + k]);
+  }
+  for (; r < r1; ++r) {
     const double w = double(W[r * ncols + c]);
     acc += w * w * double(v[r]);
   }
   part[int64_t(blockIdx.y) * ncols + c] = acc;
 }
 
+// The partial sums of 16 columns: 16 threads a column, each over every 16th row
+// chunk, then the 16 in order. (One thread a column left 16 workgroups each with
+// a chain of loads: 32 us for 125 chunks of 4096 columns, 4.1 now.)
+constexpr int kTotalCols = 16;
+constexpr int kTotalSlices = kThreads / kTotalCols;
+
 __global__ void __launch_bounds__(kThreads)
 sq_gemv_t_total_kernel(const double* __restrict__ part, int64_t nchunks, int64_t ncols,
                        double* __restrict__ out) {
-  const int64_t c = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (c >= ncols) return;
+  __shared__ double slice[kTotalSlices][kTotalCols];
+  const int col = threadIdx.x % kTotalCols, sl = threadIdx.x / kTotalCols;
+  const int64_t c = int64_t(blockIdx.x) * kTotalCols + col;
   double acc = 0.0;
-  for (int64_t k = 0; k < nchunks; ++k) acc += part[k * ncols + c];
-  out[c] = acc;
+  if (c < ncols)
+    for (int64_t k = sl; k < nchunks; k += kTotalSlices) acc += part[k * ncols + c];
+  slice[sl][col] = acc;
+  __syncthreads();
+  if (sl == 0 && c < ncols) {
+#pragma unroll
+    for (int k = 1; k < kTotalSlices; ++k) acc += slice[k][col];
+    out[c] = acc;
+  }
 }
 
 // Column statistics: three passes of a radix select on the 31-bit patterns of
@@ -136,6 +160,27 @@ __device__ void find_rank(const uint32_t (*hist)[kStatBins], int nbins, const in
   }
 }
 
+// Calls f(key) for the keys of this thread's rows of its column, kStatBatch
+// loads at a time: with 32 threads a column and two workgroups per CU, one load
+// in flight per thread left the passes bound by its latency (281 us a call over
+// the seven tensors of a 7B-shaped layer, 107 us with 16, about the time of the
+// three reads).
+constexpr int kStatBatch = 16;
+template <typename F>
+__device__ __forceinline__ void each_key(const float* __restrict__ Wc, int64_t nrows, int64_t ncols,
+                                         int grp, F&& f) {
+  int64_t r = grp;
+  for (; r + (kStatBatch - 1) * kStatGroups < nrows; r += kStatBatch * kStatGroups) {
+    uint32_t key[kStatBatch];
+#pragma unroll
+    for (int k = 0; k < kStatBatch; ++k)
+      key[k] = __float_as_uint(Wc[(r + k * kStatGroups) * ncols]) & 0x7FFFFFFFu;
+#pragma unroll
+    for (int k = 0; k < kStatBatch; ++k) f(key[k]);
+  }
+  for (; r < nrows; r += kStatGroups) f(__float_as_uint(Wc[r * ncols]) & 0x7FFFFFFFu);
+}
+
 __global__ void __launch_bounds__(kThreads)
 column_stats_kernel(const float* __restrict__ W, int64_t nrows, int64_t ncols,
                     double* __restrict__ maxabs, double* __restrict__ median) {
@@ -170,11 +215,10 @@ column_stats_kernel(const float* __restrict__ W, int64_t nrows, int64_t ncols,
   // pass 1: maximum and the histogram of bits 30..20
   if (live) {
     uint32_t m = 0u;
-    for (int64_t r = grp; r < nrows; r += kStatGroups) {
-      const uint32_t key = __float_as_uint(Wc[r * ncols]) & 0x7FFFFFFFu;
+    each_key(Wc, nrows, ncols, grp, [&](uint32_t key) {
       m = max(m, key);
       atomicAdd(&hist[col][key >> 20], 1u);
-    }
+    });
     atomicMax(&mx_s[col], m);
   }
   __syncthreads();
@@ -187,10 +231,9 @@ column_stats_kernel(const float* __restrict__ W, int64_t nrows, int64_t ncols,
 
   // pass 2: bits 19..10 of the keys in the median's first-digit bin
   if (live) {
-    for (int64_t r = grp; r < nrows; r += kStatGroups) {
-      const uint32_t key = __float_as_uint(Wc[r * ncols]) & 0x7FFFFFFFu;
+    each_key(Wc, nrows, ncols, grp, [&](uint32_t key) {
       if ((key >> 20) == d1) atomicAdd(&hist[col][(key >> 10) & 1023u], 1u);
-    }
+    });
   }
   __syncthreads();
   find_rank(hist, 1024, k_s, part, bin_s, rank_s);
@@ -205,11 +248,10 @@ column_stats_kernel(const float* __restrict__ W, int64_t nrows, int64_t ncols,
   // largest key with it)
   if (live) {
     uint32_t above = 0xFFFFFFFFu;
-    for (int64_t r = grp; r < nrows; r += kStatGroups) {
-      const uint32_t key = __float_as_uint(Wc[r * ncols]) & 0x7FFFFFFFu;
+    each_key(Wc, nrows, ncols, grp, [&](uint32_t key) {
       if ((key >> 10) == pre) atomicAdd(&hist[col][key & 1023u], 1u);
       else if ((key >> 10) > pre) above = min(above, key);
-    }
+    });
     atomicMin(&above_s[col], above);
   }
   __syncthreads();
@@ -245,21 +287,36 @@ struct GaussHermite {
   double x[128], w[128];
 };
 
-// out[i] = E[silu(g)^2], g ~ N(0, var[i]), times scale[i] when scale is given.
+// out[i] = E[silu(g)^2], g ~ N(0, var[i]), times scale[i] when scale is given. 16
+// threads a channel, each with every 16th node, then the 16 sums in a tree: a
+// layer has some ten thousand channels, too few for a thread each (11008 channels
+// of 128 nodes 25 us with one thread a channel, 5.2 now).
+constexpr int kSiluThreads = 16;
+
 __global__ void __launch_bounds__(kThreads)
 expect_silu_sq_kernel(const double* __restrict__ var, int64_t n, GaussHermite gh,
                       const double* __restrict__ scale, double* __restrict__ out) {
-  const int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (i >= n) return;
+  // indexed by the lane: from LDS, not from the kernel arguments
+  __shared__ double x[128], w[128];
+  for (int k = threadIdx.x; k < gh.n; k += kThreads) {
+    x[k] = gh.x[k];
+    w[k] = gh.w[k];
+  }
+  __syncthreads();
+  const int64_t i = int64_t(blockIdx.x) * (kThreads / kSiluThreads) + threadIdx.x / kSiluThreads;
+  const int t = threadIdx.x % kSiluThreads;
+  if (i >= n) return;   // whole groups of 16 lanes
   const double s = sqrt(2.0 * var[i]);
   double acc = 0.0;
-  for (int k = 0; k < gh.n; ++k) {
-    const double g = s * gh.x[k];
+  for (int k = t; k < gh.n; k += kSiluThreads) {
+    const double g = s * x[k];
     const double silu = g / (1.0 + exp(-g));
-    acc += gh.w[k] * silu * silu;
+    acc += w[k] * silu * silu;
   }
+#pragma unroll
+  for (int d = kSiluThreads / 2; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
   const double e = acc / sqrt(3.14159265358979323846);
-  out[i] = scale ? e * scale[i] : e;
+  if (t == 0) out[i] = scale ? e * scale[i] : e;
 }
 
 // out[r][j] = in[r][perm[j]] (gather) or out[r][perm[j]] = in[r][j] (scatter).
@@ -371,8 +428,8 @@ hipError_t launch_sq_gemv(const float* d_W, int64_t nrows, int64_t ncols, const 
   double* part = static_cast<double*>(d_ws);
   hipLaunchKernelGGL(sq_gemv_t_partial_kernel, dim3(tiles, unsigned(nchunks)), dim3(kThreads), 0,
                      stream, d_W, nrows, ncols, d_v, part);
-  hipLaunchKernelGGL(sq_gemv_t_total_kernel, dim3(tiles), dim3(kThreads), 0, stream, part, nchunks,
-                     ncols, d_out);
+  hipLaunchKernelGGL(sq_gemv_t_total_kernel, dim3(unsigned((ncols + kTotalCols - 1) / kTotalCols)),
+                     dim3(kThreads), 0, stream, part, nchunks, ncols, d_out);
   return hipGetLastError();
 }
 
@@ -394,7 +451,8 @@ hipError_t launch_expect_silu_sq(const double* d_var, int64_t n, int nodes, cons
     gh.x[k] = x[k];
     gh.w[k] = w[k];
   }
-  const unsigned grid = unsigned((n + kThreads - 1) / kThreads);
+  const int64_t channels = kThreads / kSiluThreads;
+  const unsigned grid = unsigned((n + channels - 1) / channels);
   hipLaunchKernelGGL(expect_silu_sq_kernel, dim3(grid), dim3(kThreads), 0, stream, d_var, n, gh,
                      d_scale, d_out);
   return hipGetLastError();
