@@ -9,14 +9,16 @@
 // Ladder (eq. (ladder)): a block of importance v sits at hull position
 // |{j : fl(lambda / s_j) <= v}|.
 //
-// Instead of bisecting on lambda, the planner sweeps the exact breakpoints of
-// that ladder: for every distinct importance v and hull step j, the largest
-// double lambda with fl(lambda / s_j) <= v. Walking the breakpoints from the
-// largest down promotes whole groups of equally important blocks; the first
-// group that does not fit is the tied group of the tie pass: its blocks are
-// lowered one rung, earliest first in row-major order, until the total fits
-// the budget (Algorithm 2 lowers T_t of them). The result equals bisection plus the tie
-// pass (Everett's theorem), without floating-point search.
+// The planner looks for the largest double lambda at which the ladder exceeds
+// the budget: the total only changes at the breakpoints of blocks, so this is
+// the breakpoint of the group of the tie pass, whose blocks are lowered one
+// rung, earliest first in row-major order, until the total fits the budget
+// (Algorithm 2 lowers T_t of them). The total at a lambda needs the number of
+// blocks with importance at least fl(lambda / s_j): a histogram over the leading
+// bits of the importances bounds it, a bisection over the bit patterns of lambda
+// (the doubles order like them) on those bounds leaves a few buckets, and the
+// values in them make the last bisection exact. The result is the exact
+// arithmetic one (Everett's theorem with the tie pass).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -27,20 +29,6 @@
 
 namespace seedq {
 namespace {
-
-struct Breakpoint {
-  double lam;
-  int cls;   // importance class
-  int step;  // hull step j (promotion from position j to j + 1)
-};
-
-// The sweep's order: larger lambda first, then the lower class, then the
-// lower step.
-bool before(const Breakpoint& a, const Breakpoint& b) {
-  if (a.lam != b.lam) return a.lam > b.lam;
-  if (a.cls != b.cls) return a.cls < b.cls;
-  return a.step < b.step;
-}
 
 // Runs f(t, begin, end) on nt threads over [0, n) in contiguous chunks (the
 // planner's large-input loops; every chunk's work is independent, so the
@@ -59,105 +47,22 @@ void parallel_chunks(int64_t n, int nt, F&& f) {
   for (auto& x : th) x.join();
 }
 
+// A thread for every 2^17 blocks (a few tens of microseconds to start, 0.1 ms of
+// work or more), at most 16.
 int planner_threads(int64_t n) {
-  if (n < (int64_t(1) << 18)) return 1;
-  const unsigned hc = std::thread::hardware_concurrency();
-  return int(std::max(1u, std::min(hc, 16u)));
+  const int64_t hc = std::max(1u, std::thread::hardware_concurrency());
+  return int(std::max<int64_t>(1, std::min<int64_t>({hc, 16, n >> 17})));
 }
 
-// Indices 0..n-1 ordered by v ascending, equal values by index (and the values
-// in that order, in sorted_v). Large inputs take a stable LSD radix sort on the
-// bit patterns of v (the values are positive and finite, so their bits order
-// like them), 11 bits per pass (a bucket table that stays in cache), passes
-// whose digit every key shares skipped, each pass split over threads (per-thread
-// counts, offsets in thread order, so the scatter stays stable); small inputs
-// std::sort.
-std::vector<int64_t> order_by_value(const std::vector<double>& v, std::vector<double>& sorted_v) {
-  const int64_t n = int64_t(v.size());
-  std::vector<int64_t> idx(n);
-  sorted_v.resize(size_t(n));
-  if (n < (int64_t(1) << 16)) {
-    for (int64_t i = 0; i < n; ++i) idx[i] = i;
-    std::sort(idx.begin(), idx.end(), [&](int64_t a, int64_t b) {
-      return v[a] < v[b] || (v[a] == v[b] && a < b);
-    });
-    for (int64_t k = 0; k < n; ++k) sorted_v[k] = v[idx[k]];
-    return idx;
-  }
-  const int nt = planner_threads(n);
-  std::vector<uint64_t> key(n), key2(n);
-  std::vector<int64_t> idx2(n);
-  parallel_chunks(n, nt, [&](int, int64_t b, int64_t e) {
-    for (int64_t i = b; i < e; ++i) {
-      std::memcpy(&key[i], &v[i], sizeof(double));
-      idx[i] = i;
-    }
-  });
-  constexpr int kBits = 11, kBuckets = 1 << kBits;
-  constexpr uint64_t kMask = kBuckets - 1;
-  std::vector<int64_t> cnt(size_t(nt) * kBuckets);
-  for (int shift = 0; shift < 64; shift += kBits) {
-    std::fill(cnt.begin(), cnt.end(), 0);
-    parallel_chunks(n, nt, [&](int t, int64_t b, int64_t e) {
-      int64_t* c = cnt.data() + size_t(t) * kBuckets;
-      for (int64_t i = b; i < e; ++i) ++c[(key[i] >> shift) & kMask];
-    });
-    const uint64_t d0 = (key[0] >> shift) & kMask;
-    int64_t same = 0;
-    for (int t = 0; t < nt; ++t) same += cnt[size_t(t) * kBuckets + d0];
-    if (same == n) continue;   // one digit for all
-    int64_t run = 0;
-    for (int d = 0; d < kBuckets; ++d)
-      for (int t = 0; t < nt; ++t) {
-        int64_t& c = cnt[size_t(t) * kBuckets + d];
-        const int64_t x = c;
-        c = run;
-        run += x;
-      }
-    parallel_chunks(n, nt, [&](int t, int64_t b, int64_t e) {
-      int64_t* c = cnt.data() + size_t(t) * kBuckets;
-      for (int64_t i = b; i < e; ++i) {
-        const int64_t pos = c[(key[i] >> shift) & kMask]++;
-        key2[pos] = key[i];
-        idx2[pos] = idx[i];
-      }
-    });
-    key.swap(key2);
-    idx.swap(idx2);
-  }
-  std::memcpy(sorted_v.data(), key.data(), sizeof(double) * size_t(n));
-  return idx;
-}
-
-// The neighbouring doubles of a non-negative finite x: for these the bit
-// pattern counts the representable values (std::nextafter's result, without
-// the library call).
-double next_up(double x) {
+uint64_t pattern(double x) {
   uint64_t b;
   std::memcpy(&b, &x, sizeof b);
-  ++b;
-  std::memcpy(&x, &b, sizeof b);
-  return x;
+  return b;
 }
-double next_down(double x) {   // x > 0
-  uint64_t b;
-  std::memcpy(&b, &x, sizeof b);
-  --b;
-  std::memcpy(&x, &b, sizeof b);
+double from_pattern(uint64_t b) {
+  double x;
+  std::memcpy(&x, &b, sizeof x);
   return x;
-}
-
-// Largest lambda >= 0 with fl(lambda / s) <= v (v > 0, s > 0).
-double breakpoint(double v, double s) {
-  double lam = v * s;
-  if (!std::isfinite(lam)) lam = std::nextafter(INFINITY, 0.0);
-  while (lam > 0.0 && lam / s > v) lam = next_down(lam);
-  for (;;) {
-    const double up = next_up(lam);
-    if (std::isfinite(up) && up / s <= v) lam = up;
-    else break;
-  }
-  return lam;
 }
 
 // What the encoder and the decoder both derive from the descriptor: block
@@ -170,7 +75,6 @@ struct Prepared {
   std::vector<double> rho;    // per row, unit mean; empty for rho = 1
   std::vector<int> H;         // hull vertices (rung indices), increasing rate
   std::vector<double> slope;  // s_j, bits per weight
-  double imp(int64_t b) const { return rho.empty() ? 1.0 * abar[b % G] : rho[b / G] * abar[b % G]; }
 };
 
 int prepare(const seedq_schedule_desc* d, Prepared& p) {
@@ -259,6 +163,127 @@ int prepare(const seedq_schedule_desc* d, Prepared& p) {
 
 }  // namespace
 
+namespace {
+
+// The importances of a plan (one per block; with rho = 1 one per column group,
+// each standing for a block in every row) and the counts of them at or above a
+// threshold.
+struct Importances {
+  const std::vector<double>& abar;
+  const std::vector<double>& rho;
+  int64_t rows, G, n;
+  double floor = 0.0;
+  // histogram: bucket of v = (pattern(v) >> shift) - base, at most 2^14 of them (or n)
+  int shift = 0;
+  uint64_t base = 0, top = 0;
+  std::vector<int64_t> above;   // above[k]: values in buckets >= k
+
+  Importances(const std::vector<double>& a, const std::vector<double>& r)
+      : abar(a), rho(r), rows(r.empty() ? 1 : int64_t(r.size())), G(int64_t(a.size())),
+        n(rows * G) {
+    const auto am = std::minmax_element(abar.begin(), abar.end());
+    double lo = *am.first, hi = *am.second;
+    if (!rho.empty()) {
+      // rounding is monotone, so these bound every product
+      const auto rm = std::minmax_element(rho.begin(), rho.end());
+      lo *= *rm.first;
+      hi *= *rm.second;
+    }
+    const uint64_t most = uint64_t(std::min<int64_t>(std::max<int64_t>(n, 64), 1 << 14));
+    while ((pattern(hi) >> shift) - (pattern(lo) >> shift) >= most) ++shift;
+    base = pattern(lo) >> shift;
+    const size_t nbuckets = size_t((pattern(hi) >> shift) - base) + 1;
+    top = base + nbuckets - 1;
+    const int nt = planner_threads(n);
+    std::vector<std::vector<int64_t>> part(size_t(nt), std::vector<int64_t>(nbuckets, 0));
+    rows_in_parallel([&](int t, double f, int64_t, const double* ab) {
+      int64_t* h = part[size_t(t)].data();
+      for (int64_t g = 0; g < G; ++g) ++h[(pattern(f * ab[g]) >> shift) - base];
+    });
+    above.assign(nbuckets + 1, 0);
+    for (size_t k = nbuckets; k-- > 0;) {
+      above[k] = above[k + 1];
+      for (const auto& h : part) above[k] += h[k];
+    }
+  }
+
+  // f(thread, row factor, row, abar) for every row
+  template <typename F>
+  void rows_in_parallel(F&& f) const {
+    parallel_chunks(rows, planner_threads(n), [&](int t, int64_t r0, int64_t r1) {
+      for (int64_t r = r0; r < r1; ++r) f(t, rho.empty() ? 1.0 : rho[r], r, abar.data());
+    });
+  }
+
+  size_t bucket(double v) const {   // of a value in the histogram's range, clamped to it
+    const uint64_t b = pattern(v) >> shift;
+    return size_t((b < base ? base : b > top ? top : b) - base);
+  }
+
+  // the values whose bucket is marked, ascending
+  std::vector<double> gather(const std::vector<char>& mark) const {
+    std::vector<std::vector<double>> part(size_t(planner_threads(n)));
+    rows_in_parallel([&](int t, double f, int64_t, const double* ab) {
+      for (int64_t g = 0; g < G; ++g) {
+        const double v = f * ab[g];
+        if (mark[size_t((pattern(v) >> shift) - base)]) part[size_t(t)].push_back(v);
+      }
+    });
+    std::vector<double> all;
+    for (const auto& p : part) all.insert(all.end(), p.begin(), p.end());
+    std::sort(all.begin(), all.end());
+    return all;
+  }
+
+  // value of rank k (0-based, ascending)
+  double ranked(int64_t k) const {
+    size_t b = 0;
+    while (n - above[b + 1] <= k) ++b;
+    std::vector<char> mark(above.size() - 1, 0);
+    mark[b] = 1;
+    return gather(mark)[size_t(k - (n - above[b]))];
+  }
+
+  // bounds on the number of floored values >= t
+  void count_bounds(double t, int64_t* least, int64_t* most) const {
+    if (t <= floor) {
+      *least = *most = n;
+      return;
+    }
+    const uint64_t b = pattern(t) >> shift;   // t > floor >= the smallest value
+    if (b > top) {
+      *least = *most = 0;
+      return;
+    }
+    *least = above[size_t(b - base) + 1];
+    *most = above[size_t(b - base)];
+  }
+
+  // the number itself, from the sorted values of t's bucket
+  int64_t count(double t, const std::vector<double>& values) const {
+    int64_t least, most;
+    count_bounds(t, &least, &most);
+    if (least == most) return least;
+    const uint64_t next = ((pattern(t) >> shift) + 1) << shift;
+    const auto end = std::lower_bound(values.begin(), values.end(), from_pattern(next));
+    return least + (end - std::lower_bound(values.begin(), end, t));
+  }
+};
+
+// Largest pattern in [lo, hi] for which pred holds, given that it holds at lo and
+// never again once it fails.
+template <typename Pred>
+uint64_t last_true(uint64_t lo, uint64_t hi, Pred&& pred) {
+  while (lo < hi) {
+    const uint64_t mid = lo + (hi - lo + 1) / 2;
+    if (pred(mid)) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+}  // namespace
+
 int plan_schedule(const seedq_schedule_desc* d, uint8_t* rob, seedq_schedule_report* rep) {
   if (!rob) return SEEDQ_EINVAL;
   Prepared pr;
@@ -273,227 +298,154 @@ int plan_schedule(const seedq_schedule_desc* d, uint8_t* rob, seedq_schedule_rep
     return SEEDQ_ERATE;
   const int64_t budget = int64_t(budget_f);
   const std::vector<double>& bits = pr.bits;
-  const std::vector<double>& abar = pr.abar;
-  const std::vector<double>& rho = pr.rho;
-  auto imp_of = [&](int64_t b) -> double { return pr.imp(b); };
+  const std::vector<int>& H = pr.H;
+  const int J = int(H.size());
+  const std::vector<double>& slope = pr.slope;
+  if (double(nb) * bits[H[0]] > double(budget)) return SEEDQ_ERATE;
 
   // ---- floor (section 3.3)
   int64_t kq = int64_t(std::ceil(double(nb) * d->floor_fraction)) - 1;
   if (kq < 0) kq = 0;
   if (kq > nb - 1) kq = nb - 1;
-  double qf;
-  if (rho.empty()) {
-    std::vector<double> sg(abar);
-    std::sort(sg.begin(), sg.end());
-    qf = 1.0 * sg[kq / nrows];
-  } else {
-    std::vector<double> all(nb);
-    parallel_chunks(nrows, planner_threads(nb), [&](int, int64_t r0, int64_t r1) {
-      for (int64_t r = r0; r < r1; ++r)
-        for (int64_t g = 0; g < G; ++g) all[r * G + g] = rho[r] * abar[g];   // = imp_of(r G + g)
-    });
-    std::nth_element(all.begin(), all.begin() + kq, all.end());
-    qf = all[kq];
-  }
+  Importances im(pr.abar, pr.rho);
+  const int64_t weight = pr.rho.empty() ? nrows : 1;   // blocks per value
+  const double qf = im.floor = im.ranked(kq / weight);
 
-  // ---- importance classes: equal floored importance
-  // cls_of_group (rho == 1) or cls_of_block (general); members listed in block order
-  std::vector<double> cls_val;
-  std::vector<int64_t> cls_count;
-  std::vector<int32_t> cls_of;  // per group (rho == 1) or per block
-  {
-    const int64_t n = rho.empty() ? G : nb;
-    auto val = [&](int64_t i) { return std::max(rho.empty() ? 1.0 * abar[i] : imp_of(i), qf); };
-    std::vector<double> v(n);
-    if (rho.empty()) {
-      for (int64_t i = 0; i < n; ++i) v[i] = val(i);
+  // ---- the largest lambda at which the ladder exceeds the budget
+  auto total_at = [&](double lam, auto&& count) {
+    int64_t t = nb * int64_t(bits[H[0]]);
+    for (int j = 0; j + 1 < J; ++j)
+      t += count(lam / slope[j]) * weight * int64_t(bits[H[j + 1]] - bits[H[j]]);
+    return t;
+  };
+  auto least = [&](double t) {
+    int64_t a, b;
+    im.count_bounds(t, &a, &b);
+    return a;
+  };
+  auto most = [&](double t) {
+    int64_t a, b;
+    im.count_bounds(t, &a, &b);
+    return b;
+  };
+  const uint64_t kMaxPattern = pattern(std::nextafter(INFINITY, 0.0));
+  std::vector<double> values;   // of the buckets that the bounds leave open
+  auto exact = [&](double t) { return im.count(t, values); };
+  bool over = total_at(0.0, most) > budget;   // some lambda exceeds the budget
+  double lam_over = 0.0;
+  if (over) {
+    std::vector<char> mark(im.above.size() - 1, 0);
+    uint64_t lo = 0, hi = kMaxPattern;
+    if (im.n <= 4096) {   // few values: all of them, without the coarse bisections
+      mark.assign(mark.size(), 1);
     } else {
-      parallel_chunks(nrows, planner_threads(n), [&](int, int64_t r0, int64_t r1) {
-        for (int64_t r = r0; r < r1; ++r)
-          for (int64_t g = 0; g < G; ++g) v[r * G + g] = std::max(rho[r] * abar[g], qf);   // = val(r G + g)
-      });
+      hi = last_true(0, kMaxPattern,
+                     [&](uint64_t p) { return total_at(from_pattern(p), most) > budget; });
+      if (total_at(0.0, least) > budget)
+        lo = last_true(0, hi, [&](uint64_t p) { return total_at(from_pattern(p), least) > budget; });
+      for (int j = 0; j + 1 < J; ++j)
+        for (size_t b = im.bucket(from_pattern(lo) / slope[j]),
+                    e = im.bucket(from_pattern(hi) / slope[j]); b <= e; ++b)
+          mark[b] = 1;
     }
-    std::vector<double> sv;
-    const std::vector<int64_t> idx = order_by_value(v, sv);
-    // class of every rank (a new class where the value changes), then the
-    // scatter to block order
-    std::vector<int32_t> cls_at(static_cast<size_t>(n));
-    for (int64_t k = 0; k < n; ++k) {
-      if (cls_val.empty() || sv[k] != cls_val.back()) {
-        cls_val.push_back(sv[k]);
-        cls_count.push_back(0);
-      }
-      cls_at[k] = int32_t(cls_val.size() - 1);
-      cls_count.back() += rho.empty() ? nrows : 1;
-    }
-    cls_of.assign(n, -1);
-    parallel_chunks(n, planner_threads(n), [&](int, int64_t k0, int64_t k1) {
-      for (int64_t k = k0; k < k1; ++k) cls_of[idx[k]] = cls_at[k];
-    });
-  }
-  const int ncls = int(cls_val.size());
-
-  const std::vector<int>& H = pr.H;
-  const int J = int(H.size());
-  const std::vector<double>& slope = pr.slope;
-
-  if (double(nb) * bits[H[0]] > double(budget)) return SEEDQ_ERATE;
-
-  // ---- breakpoint sweep
-  // For one step the breakpoint grows with the class value, and the classes
-  // are numbered by increasing value: each step's list comes out in sweep
-  // order by walking the classes downwards (equal breakpoints of neighbouring
-  // classes put back in class order), and the lists are merged.
-  std::vector<int> level(ncls, 0);
-  std::vector<Breakpoint> ev;
-  ev.reserve(size_t(ncls) * (J > 1 ? J - 1 : 0));
-  {
-    std::vector<std::vector<Breakpoint>> lists(J > 1 ? J - 1 : 0);
-    for (int j = 0; j + 1 < J; ++j) {
-      std::vector<Breakpoint>& L = lists[j];
-      L.resize(size_t(ncls));
-      parallel_chunks(ncls, planner_threads(ncls), [&](int, int64_t b, int64_t e) {
-        for (int64_t i = b; i < e; ++i) {
-          const int c = ncls - 1 - int(i);
-          L[size_t(i)] = {breakpoint(cls_val[c], slope[j]), c, j};
-        }
-      });
-      for (size_t a = 0; a < L.size();) {
-        size_t b = a + 1;
-        while (b < L.size() && L[b].lam == L[a].lam) ++b;
-        std::reverse(L.begin() + long(a), L.begin() + long(b));
-        a = b;
-      }
-    }
-    std::vector<size_t> at(lists.size(), 0);
-    for (;;) {
-      int best = -1;
-      for (int j = 0; j < int(lists.size()); ++j)
-        if (at[j] < lists[j].size() && (best < 0 || before(lists[j][at[j]], lists[best][at[best]])))
-          best = j;
-      if (best < 0) break;
-      ev.push_back(lists[best][at[best]++]);
-    }
+    values = im.gather(mark);
+    over = total_at(from_pattern(lo), exact) > budget;
+    if (over)
+      lam_over = from_pattern(last_true(lo, hi, [&](uint64_t p) {
+        return total_at(from_pattern(p), exact) > budget;
+      }));
   }
 
-  int64_t total = nb * int64_t(bits[H[0]]);
-  double lam = 0.0;
-  int64_t T = 0;
-  // tied group (if any): classes promoted at the final threshold, and how many
-  // of their blocks (in block order) keep the lower position
-  std::vector<int> tied_cls;
-  std::vector<int> tied_from;  // position before the threshold, per tied class
-  size_t k = 0;
-  bool done = false;
-  while (k < ev.size() && !done) {
-    size_t k1 = k;
-    while (k1 < ev.size() && ev[k1].lam == ev[k].lam) ++k1;
-    const double lk = ev[k].lam;
-    if (total == budget) {
-      lam = std::nextafter(lk, INFINITY);
-      done = true;
-      break;
-    }
-    int64_t delta = 0;
-    for (size_t t = k; t < k1; ++t) {
-      const int c = ev[t].cls, j = ev[t].step;
-      delta += cls_count[c] * int64_t(bits[H[j + 1]] - bits[H[j]]);
-    }
-    if (total + delta <= budget) {
-      for (size_t t = k; t < k1; ++t) level[ev[t].cls] = ev[t].step + 1;
-      total += delta;
-      k = k1;
-      continue;
-    }
-    // tie pass over the classes promoted at lk
-    std::vector<int> from_of(ncls, -1);
-    for (size_t t = k; t < k1; ++t) {
-      const int c = ev[t].cls;
-      if (from_of[c] < 0) {
-        from_of[c] = level[c];
-        tied_cls.push_back(c);
-      }
-    }
-    std::sort(tied_cls.begin(), tied_cls.end());
-    std::vector<int> to_of(ncls, -1);
-    for (size_t t = k; t < k1; ++t) to_of[ev[t].cls] = std::max(to_of[ev[t].cls], ev[t].step + 1);
-    int64_t cur = total + delta;
-    int64_t members = 0;
-    for (int c : tied_cls) members += cls_count[c];
-    // lower members, earliest block first, until the total fits the budget
-    auto gain = [&](int c) {
-      return int64_t(bits[H[to_of[c]]] - bits[H[from_of[c]]]);
-    };
-    T = 0;
-    if (rho.empty()) {
-      // block order over the tied groups: rows outer, groups inner
-      std::vector<int64_t> groups;
-      for (int64_t g = 0; g < G; ++g)
-        if (from_of[cls_of[g]] >= 0) groups.push_back(g);
-      for (int64_t r = 0; r < nrows && cur > budget; ++r)
-        for (size_t gi = 0; gi < groups.size() && cur > budget; ++gi) {
-          cur -= gain(cls_of[groups[gi]]);
-          ++T;
-        }
-    } else {
-      for (int64_t b = 0; b < nb && cur > budget; ++b) {
-        const int c = cls_of[b];
-        if (from_of[c] >= 0) {
-          cur -= gain(c);
-          ++T;
-        }
-      }
-    }
-    if (T == members) {
-      lam = std::nextafter(lk, INFINITY);
-      T = 0;
-      tied_cls.clear();
-    } else {
-      lam = lk;
-      for (int c : tied_cls) {
-        tied_from.push_back(from_of[c]);
-        level[c] = to_of[c];
-      }
-      total = cur;
-    }
-    done = true;
+  // ---- ladder positions at lambda and just above it
+  const double lam_up = std::nextafter(lam_over, INFINITY);
+  double th[SEEDQ_MAX_RUNGS], th_up[SEEDQ_MAX_RUNGS];
+  for (int j = 0; j + 1 < J; ++j) {
+    th[j] = lam_over / slope[j];
+    th_up[j] = over ? lam_up / slope[j] : th[j];
   }
-  if (!done) lam = 0.0;
-
-  // ---- write the allocation
+  auto position = [&](const double* t, double v) {
+    int pos = 0;
+    for (int j = 0; j + 1 < J; ++j) pos += t[j] <= v ? 1 : 0;
+    return pos;
+  };
+  // the tie pass lowers the tied blocks (whose two positions differ), earliest
+  // first, until the total fits the budget; all of them: lambda lies above
+  double lam = lam_over;
+  int64_t T = 0, members = 0;
+  int64_t cur = over ? total_at(lam_over, exact) : 0;
   int64_t count[SEEDQ_MAX_RUNGS] = {0};
-  std::vector<int> cls_tied_from(ncls, -1);
-  for (size_t t = 0; t < tied_cls.size(); ++t) cls_tied_from[tied_cls[t]] = tied_from[t];
-  int64_t demote_left = T;
-  if (rho.empty()) {
-    // every row has the same rungs; the first T tied blocks in block order
-    // (row-major) take the lower rung
-    std::vector<uint8_t> row(G);
-    for (int64_t g = 0; g < G; ++g) row[g] = uint8_t(H[level[cls_of[g]]]);
-    for (int64_t r = 0; r < nrows; ++r) std::memcpy(rob + r * G, row.data(), size_t(G));
-    for (int64_t g = 0; g < G; ++g) count[row[g]] += nrows;
-    for (int64_t r = 0; r < nrows && demote_left > 0; ++r)
-      for (int64_t g = 0; g < G && demote_left > 0; ++g) {
-        const int c = cls_of[g];
-        if (cls_tied_from[c] < 0) continue;
-        const int rr = H[cls_tied_from[c]];
-        count[rob[r * G + g]] -= 1;
-        rob[r * G + g] = uint8_t(rr);
-        count[rr] += 1;
-        --demote_left;
-      }
-  } else {
-    for (int64_t b = 0; b < nb; ++b) {
-      const int c = cls_of[b];
-      int pos = level[c];
-      if (cls_tied_from[c] >= 0 && demote_left > 0) {
-        pos = cls_tied_from[c];
-        --demote_left;
-      }
-      const int rr = H[pos];
-      rob[b] = uint8_t(rr);
-      count[rr] += 1;
+  auto gain = [&](int from, int to) { return int64_t(bits[H[to]] - bits[H[from]]); };
+  auto lower_all = [&]() { return over && T == members; };
+  if (pr.rho.empty()) {
+    std::vector<uint8_t> row(G), low(G);
+    std::vector<int64_t> tied;
+    for (int64_t g = 0; g < G; ++g) {
+      const double v = std::max(1.0 * pr.abar[g], qf);
+      const int p = position(th, v), pu = position(th_up, v);
+      row[g] = uint8_t(p);
+      low[g] = uint8_t(pu);
+      if (p != pu) tied.push_back(g);
     }
+    members = int64_t(tied.size()) * nrows;
+    // block order over the tied groups: rows outer, groups inner
+    for (int64_t r = 0; r < nrows && cur > budget; ++r)
+      for (size_t i = 0; i < tied.size() && cur > budget; ++i) {
+        cur -= gain(low[tied[i]], row[tied[i]]);
+        ++T;
+      }
+    if (lower_all())
+      for (const int64_t g : tied) row[g] = low[g];
+    std::vector<uint8_t> out(G);
+    for (int64_t g = 0; g < G; ++g) {
+      out[g] = uint8_t(H[row[g]]);
+      count[out[g]] += nrows;
+    }
+    for (int64_t r = 0; r < nrows; ++r) std::memcpy(rob + r * G, out.data(), size_t(G));
+    if (!lower_all()) {
+      int64_t left = T;
+      for (int64_t r = 0; r < nrows && left > 0; ++r)
+        for (size_t i = 0; i < tied.size() && left > 0; ++i, --left) {
+          const int64_t g = tied[i];
+          count[out[g]] -= 1;
+          rob[r * G + g] = uint8_t(H[low[g]]);
+          count[H[low[g]]] += 1;
+        }
+    }
+  } else {
+    struct Tied {
+      int64_t b;
+      uint8_t from, to;
+    };
+    const int nt = planner_threads(nb);
+    std::vector<std::vector<Tied>> part{size_t(nt)};
+    std::vector<std::vector<int64_t>> part_count(size_t(nt), std::vector<int64_t>(SEEDQ_MAX_RUNGS, 0));
+    im.rows_in_parallel([&](int t, double f, int64_t r, const double* ab) {
+      int64_t n[SEEDQ_MAX_RUNGS] = {0};
+      for (int64_t g = 0; g < G; ++g) {
+        const double v = std::max(f * ab[g], qf);
+        const int p = position(th, v), pu = position(th_up, v);
+        rob[r * G + g] = uint8_t(H[p]);
+        ++n[H[p]];
+        if (p != pu) part[size_t(t)].push_back({r * G + g, uint8_t(pu), uint8_t(p)});
+      }
+      for (int k = 0; k < R; ++k) part_count[size_t(t)][size_t(k)] += n[k];
+    });
+    std::vector<Tied> tied;   // in block order: the threads' rows follow each other
+    for (const auto& p : part) tied.insert(tied.end(), p.begin(), p.end());
+    for (const auto& c : part_count)
+      for (int k = 0; k < R; ++k) count[k] += c[size_t(k)];
+    members = int64_t(tied.size());
+    for (; T < members && cur > budget; ++T) cur -= gain(tied[size_t(T)].from, tied[size_t(T)].to);
+    for (int64_t i = 0; i < T; ++i) {
+      const Tied& x = tied[size_t(i)];
+      rob[x.b] = uint8_t(H[x.from]);
+      count[H[x.to]] -= 1;
+      count[H[x.from]] += 1;
+    }
+  }
+  if (lower_all()) {
+    lam = lam_up;
+    T = 0;
   }
   int64_t check_total = 0;
   for (int r = 0; r < R; ++r) check_total += count[r] * int64_t(bits[r]);
@@ -528,9 +480,14 @@ int derive_schedule(const seedq_schedule_desc* d, double lam, double qf, int64_t
   const std::vector<double>& slope = pr.slope;
 
   const double lam_up = std::nextafter(lam, INFINITY);
-  auto position = [&](double l, double v) {
+  double th[SEEDQ_MAX_RUNGS], th_up[SEEDQ_MAX_RUNGS];
+  for (int j = 0; j + 1 < J; ++j) {
+    th[j] = lam / slope[j];
+    th_up[j] = lam_up / slope[j];
+  }
+  auto position = [&](const double* t, double v) {
     int pos = 0;
-    for (int j = 0; j + 1 < J; ++j) pos += (l / slope[j] <= v) ? 1 : 0;
+    for (int j = 0; j + 1 < J; ++j) pos += t[j] <= v ? 1 : 0;
     return pos;
   };
   if (pr.rho.empty()) {
@@ -539,7 +496,7 @@ int derive_schedule(const seedq_schedule_desc* d, double lam, double qf, int64_t
     int64_t ntied = 0;
     for (int64_t g = 0; g < G; ++g) {
       const double v = std::max(1.0 * pr.abar[g], qf);
-      const int p = position(lam, v), pu = position(lam_up, v);
+      const int p = position(th, v), pu = position(th_up, v);
       row[g] = uint8_t(H[p]);
       lower[g] = uint8_t(H[pu]);
       tied[g] = p != pu;
@@ -555,24 +512,24 @@ int derive_schedule(const seedq_schedule_desc* d, double lam, double qf, int64_t
           --left;
         }
   } else {
-    std::vector<uint8_t> pos(nb), pos_up(nb);
-    int64_t ntied = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-      const double v = std::max(pr.imp(b), qf);
-      pos[b] = uint8_t(position(lam, v));
-      pos_up[b] = uint8_t(position(lam_up, v));
-      ntied += pos[b] != pos_up[b] ? 1 : 0;
-    }
+    // tied blocks and their lower rung, in block order
+    std::vector<std::vector<std::pair<int64_t, uint8_t>>> part{size_t(planner_threads(nb))};
+    std::vector<uint8_t> all(static_cast<size_t>(nb));   // rob is written on success only
+    parallel_chunks(nrows, planner_threads(nb), [&](int t, int64_t r0, int64_t r1) {
+      for (int64_t r = r0; r < r1; ++r)
+        for (int64_t g = 0; g < G; ++g) {
+          const double v = std::max(pr.rho[r] * pr.abar[g], qf);
+          const int p = position(th, v), pu = position(th_up, v);
+          all[size_t(r * G + g)] = uint8_t(H[p]);
+          if (p != pu) part[size_t(t)].push_back({r * G + g, uint8_t(H[pu])});
+        }
+    });
+    int64_t ntied = 0, left = T;
+    for (const auto& p : part) ntied += int64_t(p.size());
     if (T > ntied) return SEEDQ_EINVAL;
-    int64_t left = T;
-    for (int64_t b = 0; b < nb; ++b) {
-      int p = pos[b];
-      if (left > 0 && pos_up[b] != p) {
-        p = pos_up[b];
-        --left;
-      }
-      rob[b] = uint8_t(H[p]);
-    }
+    std::memcpy(rob, all.data(), size_t(nb));
+    for (const auto& p : part)
+      for (size_t i = 0; i < p.size() && left > 0; ++i, --left) rob[p[i].first] = p[i].second;
   }
   return SEEDQ_OK;
 }

@@ -101,9 +101,8 @@ def test_derive_errors(sq):
 
 @pytest.mark.parametrize("case", ["random", "tied"])
 def test_planner_large_with_rows_matches_oracle(sq, oq, case):
-    """Above 2^18 blocks the planner sorts its importance classes with a
-    threaded radix sort and merges per-step breakpoint lists: the allocation,
-    lambda and tie count must still be the oracle's."""
+    """Above 2^18 blocks the planner's passes over the blocks are threaded: the
+    allocation, lambda and tie count must still be the oracle's."""
     rng = np.random.default_rng(11 if case == "random" else 12)
     nrows, ncols = 600, 4096
     a = np.exp(rng.normal(0, 1, ncols)).astype(np.float32)
@@ -118,3 +117,22 @@ def test_planner_large_with_rows_matches_oracle(sq, oq, case):
     assert np.array_equal(enc, ref.rung_of_block)
     if case == "tied":
         assert rep["tie_count"] > 0
+
+
+@pytest.mark.parametrize("nrows,G,spread,rows", [(3, 4096, 1.0, False), (3, 4097, 1.0, False),
+                                                 (2, 6000, 15.0, False), (17, 241, 1.0, True),
+                                                 (17, 242, 15.0, True), (90, 300, 0.0, True)])
+def test_planner_histogram_lines_match_oracle(sq, oq, nrows, G, spread, rows):
+    """Up to 4096 importances the planner sorts all of them; above, a histogram
+    leaves the buckets at the thresholds (factors over a few and over 60
+    octaves, and all equal): allocation, lambda and tie count are the oracle's."""
+    rng = np.random.default_rng(G + nrows)
+    a = np.exp(rng.normal(0, spread, 8 * G)).astype(np.float32)
+    rho = np.exp(rng.normal(0, 0.5 * min(spread, 1), nrows)).astype(np.float32) if rows else None
+    enc, rep = sq.plan_schedule(nrows, 8 * G, RUNGS, DAMAGE, 3.875, a, rho, 0.06)
+    ref = oq.schedule(nrows, 8 * G, RUNGS, DAMAGE, 3.875, a, rho, 0.06)
+    assert rep["lam"] == ref.lam and rep["tie_count"] == ref.tie_count
+    assert np.array_equal(enc, ref.rung_of_block)
+    again = sq.derive_schedule(nrows, 8 * G, RUNGS, DAMAGE, a, rep["lam"], rep["floor_q"],
+                               rep["tie_count"], rho)
+    assert np.array_equal(again, enc)
