@@ -578,8 +578,8 @@ def run_steps(wl, steps: int, warmup: int):
     search_ms = float(np.mean(phase["search"]))
     decomp_ms = float(np.mean(phase["decomp"]))
     bases_ms = float(np.mean(phase["bases"]))
-    # dominant kernel: the search (one launch per rung, or per seed chunk of a
-    # K >= 17 rung), timed by the events around seedq_compress on its stream
+    # dominant kernel: the search (a launch per rung and one that emits its
+    # codes), timed by the events around seedq_compress on its stream
     flops = sum(rep_counts[r] * projection_flops(K, P) for r, (K, P) in enumerate(rungs))
     achieved = flops / (search_ms / 1000.0) / 1e12
     roofline = {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP16_MFMA_TFLOPS,
