@@ -227,6 +227,23 @@ __device__ __forceinline__ int64_t chunk_wave_offset(const Offsets& o, const uin
   return off + before;
 }
 
+// The first chunk from u on that has bits (or the number of chunks), 64 a step:
+// the packer's way across blocks without bits, which block by block and from every
+// chunk took a time that grew with the square of their number (4096 x 14336 with
+// bits in the first half only: 53 us, 47 with bits everywhere). Wave-uniform.
+__device__ __forceinline__ int64_t next_unit_with_bits(const Offsets& o, int64_t u, int64_t nblocks) {
+  const int64_t nunits = (nblocks + kChunk - 1) / kChunk;
+  for (; u < nunits; u += 64) {
+    const int64_t v = u + int64_t(threadIdx.x & 63);
+    bool has = v < nunits;
+    if (has && o.mode == kGroups) has = o.bits[v] != 0u;
+    if (has && o.mode == kScanned) has = v + 1 == nunits || o.sums[v + 1] != o.sums[v];
+    const uint64_t m = __builtin_amdgcn_ballot_w64(has);
+    if (m != 0ull) return u + __builtin_ctzll(m);
+  }
+  return nunits;
+}
+
 // Exclusive prefix sum over the wave and its total, of 32-bit values: shifts
 // within rows of 16 lanes, then the rows' last lanes broadcast to the rows after
 // them (data-parallel primitives: no LDS).
@@ -461,12 +478,17 @@ pack_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__ expo,
   const int64_t b1 = min(nblocks, base + kChunk);
   for (int64_t b = base + wave * kWaveBlocks; b < min(b1, base + (wave + 1) * kWaveBlocks); b += 64)
     run += put(b, b1, run);
-  // the last wave that has blocks completes the chunk's last word from the
-  // blocks that follow (two codes, unless blocks without bits come between)
+  // the last wave that has blocks completes the chunk's last word, if that begins in
+  // the chunk, from the blocks that follow (two codes, unless blocks without bits
+  // come between)
   if (wave == int((b1 - base - 1) / kWaveBlocks)) {
     if (lane == 0) end_s = run;
     const int64_t word_end = (run + 31) & ~int64_t(31);
-    for (int64_t b = b1; b < nblocks && run < word_end; b += 64) run += put(b, nblocks, run);
+    if (((off0 + 31) >> 5) < (word_end >> 5))
+      for (int64_t b = b1; b < nblocks && run < word_end; b += 64) {
+        if (b > b1 && b % kChunk == 0) b = next_unit_with_bits(o, b / kChunk, nblocks) * kChunk;
+        if (b < nblocks) run += put(b, nblocks, run);
+      }
   }
   __syncthreads();
   // the words that begin inside the chunk

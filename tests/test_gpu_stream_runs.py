@@ -72,6 +72,36 @@ def test_words_across_blocks_without_bits(sq, oq):  # noqa: F811
     _check(sq, oq, rob, [(8, 1), (9, 2)], 1, 8 * len(rob), nvecs=())
 
 
+def _pack_ms(sq, rob, rungs):
+    import torch
+    nb = len(rob)
+    cnt = np.bincount(rob[rob < len(rungs)], minlength=len(rungs))
+    seed, exp = torch.ones(nb, dtype=torch.int32, device="cuda"), torch.ones(nb, dtype=torch.uint8, device="cuda")
+    args = (seed, exp, torch.ones(nb, 8, dtype=torch.int8, device="cuda"), rungs, 1, 8 * nb, _t(rob), cnt)
+    ms = []
+    for _ in range(6):   # the first one warms up
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        sq.pack(*args)
+        b.record()
+        torch.cuda.synchronize()
+        ms.append(a.elapsed_time(b))
+    return min(ms[1:])
+
+
+def test_long_stretch_without_bits_costs_no_more_than_codes(sq, oq):  # noqa: F811
+    # hundreds of chunks without bits behind an unaligned code, another code after
+    # them: only the word's own chunk looks for its end, and by chunks (38 us against
+    # 27 with every block coded; every chunk going through all blocks after it would
+    # take milliseconds)
+    rungs = [(8, 1), (9, 2)]
+    rob = np.full(400 * 2048 + 131, 255, np.uint8)
+    rob[[0, 2, 3, len(rob) - 3]] = [0, 1, 0, 1]
+    _check(sq, oq, rob, rungs, 1, 8 * len(rob), nvecs=())
+    full = np.resize(np.array([0, 1], np.uint8), len(rob))
+    assert _pack_ms(sq, rob, rungs) < 10 * _pack_ms(sq, full, rungs)
+
+
 def test_more_rows_than_group_sums_reach(sq, oq):  # noqa: F811
     # above 1024 groups of 16 rows the decode-GEMV takes its offsets from the scan
     nrows, G = 16 * 1024 + 9, 3
