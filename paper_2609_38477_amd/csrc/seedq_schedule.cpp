@@ -48,10 +48,12 @@ void parallel_chunks(int64_t n, int nt, F&& f) {
 }
 
 // A thread for every 2^17 blocks (a few tens of microseconds to start, 0.1 ms of
-// work or more), at most 16.
+// work or more), at most 16. The number of cores is only asked for where it
+// matters: the question takes 4 us, a plan of a few blocks 3.
 int planner_threads(int64_t n) {
+  if (n < (int64_t(1) << 18)) return 1;
   const int64_t hc = std::max(1u, std::thread::hardware_concurrency());
-  return int(std::max<int64_t>(1, std::min<int64_t>({hc, 16, n >> 17})));
+  return int(std::min<int64_t>({hc, 16, n >> 17}));
 }
 
 uint64_t pattern(double x) {

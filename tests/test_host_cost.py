@@ -1,0 +1,47 @@
+"""Fixed costs of the host calls, as ratios of calls of the same library measured side by side (the
+best of many repetitions each), and the results where the planner's short way is taken."""
+import time
+
+import numpy as np
+import pytest
+
+from test_decoder_host import sq  # noqa: F401
+
+RUNGS, DAMAGE = [(12, 2), (16, 3), (20, 4)], [4.0, 1.0, 0.25]
+
+
+def _best(*calls, n=300):
+    """The shortest time of each call, the calls taken in turn."""
+    out = [1e9] * len(calls)
+    for _ in range(n):
+        for i, f in enumerate(calls):
+            t = time.perf_counter()
+            f()
+            out[i] = min(out[i], time.perf_counter() - t)
+    return out
+
+
+def _plan(sq, rows, G, rho=False, rungs=RUNGS, damage=DAMAGE, bpw=4.0, f=0.06):
+    rng = np.random.default_rng(rows + G)
+    a = np.exp(rng.normal(0, 1, 8 * G)).astype(np.float32)
+    r = np.exp(rng.normal(0, 0.5, rows)).astype(np.float32) if rho else None
+    desc, keep = sq._schedule_desc(rows, 8 * G, rungs, damage, bpw, a, r, f)
+    rep, out = sq.ScheduleReport(), np.empty(rows * G, np.uint8)
+    sq.seedq_plan_schedule(desc, out, rep)
+
+    def plan():
+        sq.seedq_plan_schedule(desc, out, rep)
+
+    def derive(T=None):
+        sq.seedq_derive_schedule(desc, rep.lambda_, rep.floor_q, rep.tie_count if T is None else T,
+                                 out)
+    return plan, derive, rep, keep
+
+
+def test_row_factors_of_a_small_tensor_cost_nothing_fixed(sq):  # noqa: F811
+    # measured 1.0 times; 2.1 times and more when the number of cores is asked for
+    _, plain, _, k0 = _plan(sq, 1, 1, bpw=3.0)
+    _, rows, _, k1 = _plan(sq, 1, 1, rho=True, bpw=3.0)
+    a, b = _best(plain, rows)
+    assert b < 1.7 * a, (a, b)
+    del k0, k1
