@@ -494,25 +494,25 @@ int derive_schedule(const seedq_schedule_desc* d, double lam, double qf, int64_t
   };
   if (pr.rho.empty()) {
     std::vector<uint8_t> row(G), lower(G);
-    std::vector<char> tied(G);
-    int64_t ntied = 0;
+    int64_t ntied = 0;   // blocks
     for (int64_t g = 0; g < G; ++g) {
       const double v = std::max(1.0 * pr.abar[g], qf);
       const int p = position(th, v), pu = position(th_up, v);
       row[g] = uint8_t(H[p]);
       lower[g] = uint8_t(H[pu]);
-      tied[g] = p != pu;
-      ntied += tied[g] ? nrows : 0;
+      if (p != pu) ntied += nrows;
     }
     if (T > ntied) return SEEDQ_EINVAL;
-    for (int64_t r = 0; r < nrows; ++r) std::memcpy(rob + r * G, row.data(), size_t(G));
-    int64_t left = T;
-    for (int64_t r = 0; r < nrows && left > 0; ++r)
-      for (int64_t g = 0; g < G && left > 0; ++g)
-        if (tied[g]) {
-          rob[r * G + g] = lower[g];
-          --left;
-        }
+    // whole rows of tied blocks on the lower rung, one row split, the rest above
+    const int64_t per_row = ntied / nrows, whole = per_row ? T / per_row : 0;
+    for (int64_t r = 0; r < nrows; ++r)
+      std::memcpy(rob + r * G, r < whole ? lower.data() : row.data(), size_t(G));
+    int64_t left = T - whole * per_row;
+    for (int64_t g = 0; g < G && left > 0; ++g)
+      if (lower[g] != row[g]) {
+        rob[whole * G + g] = lower[g];
+        --left;
+      }
   } else {
     // tied blocks and their lower rung, in block order
     std::vector<std::vector<std::pair<int64_t, uint8_t>>> part{size_t(planner_threads(nb))};
