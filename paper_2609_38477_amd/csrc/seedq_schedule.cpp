@@ -191,8 +191,8 @@ struct Importances {
   int64_t rows, G, n;
   double floor = 0.0;
   // Up to kSortedMax importances are sorted, and that is all: plans of 8 x 16, 256 x
-  // 32 and 512 x 128 blocks 16, 18 and 24 us with the histogram and the bisections over
-  // lambda's patterns, 3.8, 5.5 and 11 without.
+  // 32 and 512 x 128 blocks at three rungs and 3.25 bits 17, 19 and 25 us with the
+  // histogram and the bisections over lambda's patterns, 3.5, 5.5 and 9.4 without.
   static constexpr int64_t kSortedMax = 4096;
   std::vector<double> sorted;
   // above that a histogram: bucket of v = (pattern(v) >> shift) - base, at most 2^14
