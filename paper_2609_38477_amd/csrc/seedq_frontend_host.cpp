@@ -12,41 +12,49 @@
 namespace seedq {
 namespace {
 
+constexpr int kMaxNodes = 256;
+
 // Orthonormal Hermite polynomials for the weight e^{-x^2}:
 // q_0 = pi^{-1/4}, q_j = x sqrt(2/j) q_{j-1} - sqrt((j-1)/j) q_{j-2}.
-// q[i] = q_n(x[i]) and, with sumsq, sumsq[i] = sum_{j<n} q_j(x[i])^2 for m points.
-// The recurrence is one dependent chain per point, so the points go through it
-// eight at a time, with the square roots taken once (one point at a time, and
-// its roots again each time, a rule of 128 nodes took 2.4 ms).
-void hermite_q(int n, const double* x, int64_t m, double* q, double* sumsq) {
-  std::vector<double> ca(size_t(n) + 1), cb(size_t(n) + 1);
-  for (int j = 1; j <= n; ++j) {
-    ca[j] = std::sqrt(2.0 / j);
-    cb[j] = std::sqrt(double(j - 1) / j);
-  }
-  const double q0 = std::pow(M_PI, -0.25);
-  constexpr int kBatch = 8;
-  for (int64_t i0 = 0; i0 < m; i0 += kBatch) {
-    const int k = int(std::min<int64_t>(kBatch, m - i0));
-    double xs[kBatch], a[kBatch], b[kBatch], s[kBatch];
-    for (int i = 0; i < kBatch; ++i) {
-      xs[i] = i < k ? x[i0 + i] : 0.0;
-      a[i] = q0;
-      b[i] = s[i] = 0.0;
+struct Hermite {
+  int n;
+  double q0, ca[kMaxNodes + 1], cb[kMaxNodes + 1];
+
+  explicit Hermite(int nodes) : n(nodes), q0(std::pow(M_PI, -0.25)) {
+    for (int j = 1; j <= n; ++j) {
+      ca[j] = std::sqrt(2.0 / j);
+      cb[j] = std::sqrt(double(j - 1) / j);
     }
-    for (int j = 1; j <= n; ++j)
+  }
+
+  // q[i] = q_n(x[i]) and, with sumsq, sumsq[i] = sum_{j<n} q_j(x[i])^2 for m points.
+  // The recurrence is one dependent chain per point, so the points go through it
+  // eight at a time, with the square roots taken once a rule (one point at a time,
+  // and its roots again each time, a rule of 128 nodes took 2.4 ms).
+  void eval(const double* x, int64_t m, double* q, double* sumsq) const {
+    constexpr int kBatch = 8;
+    for (int64_t i0 = 0; i0 < m; i0 += kBatch) {
+      const int k = int(std::min<int64_t>(kBatch, m - i0));
+      double xs[kBatch], a[kBatch], b[kBatch], s[kBatch];
       for (int i = 0; i < kBatch; ++i) {
-        s[i] += a[i] * a[i];
-        const double qn = xs[i] * ca[j] * a[i] - cb[j] * b[i];
-        b[i] = a[i];
-        a[i] = qn;
+        xs[i] = i < k ? x[i0 + i] : 0.0;
+        a[i] = q0;
+        b[i] = s[i] = 0.0;
       }
-    for (int i = 0; i < k; ++i) {
-      q[i0 + i] = a[i];
-      if (sumsq) sumsq[i0 + i] = s[i];
+      for (int j = 1; j <= n; ++j)
+        for (int i = 0; i < kBatch; ++i) {
+          s[i] += a[i] * a[i];
+          const double qn = xs[i] * ca[j] * a[i] - cb[j] * b[i];
+          b[i] = a[i];
+          a[i] = qn;
+        }
+      for (int i = 0; i < k; ++i) {
+        q[i0 + i] = a[i];
+        if (sumsq) sumsq[i0 + i] = s[i];
+      }
     }
   }
-}
+};
 
 }  // namespace
 
@@ -56,7 +64,8 @@ void hermite_q(int n, const double* x, int64_t m, double* q, double* sumsq) {
 // come from the Christoffel-Darboux identity w_i = 1 / sum_{j<n} q_j(x_i)^2.
 // Nodes ascending.
 int gauss_hermite(int n, double* x, double* w) {
-  if (n < 1 || n > 256 || !x || !w) return SEEDQ_EINVAL;
+  if (n < 1 || n > kMaxNodes || !x || !w) return SEEDQ_EINVAL;
+  const Hermite h(n);
   std::vector<double> pos;  // non-negative roots, ascending
   const double top = std::sqrt(2.0 * n + 1.0) + 1.0;
   const double step = 0.25 / std::sqrt(2.0 * n + 1.0);  // well below the root spacing
@@ -64,7 +73,7 @@ int gauss_hermite(int n, double* x, double* w) {
   std::vector<double> grid{n % 2 == 1 ? step : 0.0};
   while (grid.back() < top) grid.push_back(grid.back() + step);
   std::vector<double> f(grid.size());
-  hermite_q(n, grid.data(), int64_t(grid.size()), f.data(), nullptr);
+  h.eval(grid.data(), int64_t(grid.size()), f.data(), nullptr);
   std::vector<double> lo, hi, flo;
   for (size_t i = 0; i + 1 < grid.size(); ++i)
     if ((f[i] < 0) != (f[i + 1] < 0)) {
@@ -74,6 +83,8 @@ int gauss_hermite(int n, double* x, double* w) {
     }
   std::vector<double> mid, fm;
   std::vector<size_t> open;
+  mid.reserve(lo.size());
+  open.reserve(lo.size());
   for (int it = 0; it < 200; ++it) {
     open.clear();
     mid.clear();
@@ -84,7 +95,7 @@ int gauss_hermite(int n, double* x, double* w) {
       }
     if (open.empty()) break;
     fm.resize(mid.size());
-    hermite_q(n, mid.data(), int64_t(mid.size()), fm.data(), nullptr);
+    h.eval(mid.data(), int64_t(mid.size()), fm.data(), nullptr);
     for (size_t k = 0; k < open.size(); ++k) {
       const size_t i = open[k];
       if ((fm[k] < 0) == (flo[i] < 0)) {
@@ -98,7 +109,7 @@ int gauss_hermite(int n, double* x, double* w) {
   for (size_t i = 0; i < lo.size(); ++i) pos.push_back(0.5 * (lo[i] + hi[i]));
   if (int(pos.size()) != (n + 1) / 2) return SEEDQ_EINVAL;
   std::vector<double> q(pos.size()), s(pos.size());
-  hermite_q(n, pos.data(), int64_t(pos.size()), q.data(), s.data());
+  h.eval(pos.data(), int64_t(pos.size()), q.data(), s.data());
   for (int i = 0; i < int(pos.size()); ++i) {
     const double wi = 1.0 / s[i];
     x[n / 2 + i] = pos[i];
