@@ -67,3 +67,23 @@ def test_channel_order_rejects_non_finite_importance():
         with pytest.raises(sq.SeedqError) as e:
             sq.seedq_channel_order(a)
         assert e.value.code == -1
+
+
+HIPCC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not found")
+def test_channel_order_without_memory_for_its_words(tmp_path):
+    # the sort's scratch may not be there; it needed none that it could not do without
+    import subprocess
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    csrc = os.path.join(root, "paper_2609_38477_amd", "csrc")
+    exe = str(tmp_path / "scarce_memory_driver")
+    b = subprocess.run([HIPCC, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__",
+                        "-I" + os.path.join(root, "include"), "-I" + csrc,
+                        os.path.join(csrc, "seedq_frontend_host.cpp"),
+                        os.path.join(root, "tests", "scarce_memory_driver.cpp"), "-o", exe],
+                       capture_output=True, text=True, timeout=600)
+    assert b.returncode == 0, b.stderr[-3000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0 and "failures 0" in r.stdout, (r.returncode, r.stdout, r.stderr[-500:])
