@@ -582,12 +582,14 @@ hipError_t launch_column_stats(const float* d_W, int64_t nrows, int64_t ncols, d
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kRegThreads), 0, stream, d_W, nrows, ncols, d_max,
                        d_median);
   };
-  if (nrows <= 32 * kRegGroups) regs(column_stats_regs_kernel<32>);
-  else if (nrows <= 64 * kRegGroups) regs(column_stats_regs_kernel<64>);
-  else if (nrows <= 96 * kRegGroups) regs(column_stats_regs_kernel<96>);
-  else
+  // the register kernels' 1024 threads for 8 columns must be fewer than 2^32
+  const bool wide = grid >= (int64_t(1) << 32) / kRegThreads;
+  if (wide || nrows > 96 * kRegGroups)
     hipLaunchKernelGGL(column_stats_kernel, dim3(grid), dim3(kThreads), 0, stream, d_W, nrows, ncols,
                        d_max, d_median);
+  else if (nrows <= 32 * kRegGroups) regs(column_stats_regs_kernel<32>);
+  else if (nrows <= 64 * kRegGroups) regs(column_stats_regs_kernel<64>);
+  else regs(column_stats_regs_kernel<96>);
   return hipGetLastError();
 }
 

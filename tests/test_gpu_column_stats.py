@@ -35,3 +35,18 @@ def test_order_statistics_at_range_edges(nrows, ncols):
     a = np.abs(W).astype(np.float64)
     assert np.array_equal(mx.cpu().numpy(), a.max(axis=0))
     assert np.array_equal(md.cpu().numpy(), np.median(a, axis=0))
+
+
+def test_more_columns_than_the_register_kernels_grid_holds():
+    # 2^25 columns in groups of 8 by 1024 threads would make 2^32 threads
+    import torch
+
+    import paper_2609_38477_amd as sq
+    ncols = (1 << 25) + 13
+    W = torch.randn(2, ncols, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    mx = torch.full((ncols,), -1.0, dtype=torch.float64, device="cuda")
+    md = torch.full_like(mx, -1.0)
+    sq.seedq_column_stats(W, 2, ncols, mx, md)
+    a = W.abs()
+    assert torch.equal(mx, a.max(0).values.double())
+    assert torch.equal(md, (a[0].double() + a[1].double()) / 2)
