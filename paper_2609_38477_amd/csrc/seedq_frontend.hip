@@ -99,26 +99,30 @@ sq_gemv_t_partial_kernel(const float* __restrict__ W, int64_t nrows, int64_t nco
   part[int64_t(blockIdx.y) * ncols + c] = acc;
 }
 
-// The partial sums of 16 columns: 16 threads a column, each over every 16th row
-// chunk, then the 16 in order. (One thread a column left 16 workgroups each with
-// a chain of loads: 32 us for 125 chunks of 4096 columns, 4.1 now.)
-constexpr int kTotalCols = 16;
-constexpr int kTotalSlices = kThreads / kTotalCols;
+// The partial sums of kCols columns: 256 / kCols threads a column, each over every
+// so many row chunks, then their sums in order. 16 threads a column up to
+// kTotalFew columns (one thread a column left 16 workgroups each with a chain of
+// loads: 32 us for 125 chunks of 4096 columns, 4.1 with 16), one above: there the
+// columns alone fill the chip, and sixteen threads for each of 2^28 columns would
+// be more than the 2^32 that a launch holds.
+constexpr int64_t kTotalFew = int64_t(1) << 17;
 
+template <int kCols>
 __global__ void __launch_bounds__(kThreads)
 sq_gemv_t_total_kernel(const double* __restrict__ part, int64_t nchunks, int64_t ncols,
                        double* __restrict__ out) {
-  __shared__ double slice[kTotalSlices][kTotalCols];
-  const int col = threadIdx.x % kTotalCols, sl = threadIdx.x / kTotalCols;
-  const int64_t c = int64_t(blockIdx.x) * kTotalCols + col;
+  constexpr int kSlices = kThreads / kCols;
+  __shared__ double slice[kSlices][kCols];
+  const int col = threadIdx.x % kCols, sl = threadIdx.x / kCols;
+  const int64_t c = int64_t(blockIdx.x) * kCols + col;
   double acc = 0.0;
   if (c < ncols)
-    for (int64_t k = sl; k < nchunks; k += kTotalSlices) acc += part[k * ncols + c];
+    for (int64_t k = sl; k < nchunks; k += kSlices) acc += part[k * ncols + c];
   slice[sl][col] = acc;
   __syncthreads();
   if (sl == 0 && c < ncols) {
 #pragma unroll
-    for (int k = 1; k < kTotalSlices; ++k) acc += slice[k][col];
+    for (int k = 1; k < kSlices; ++k) acc += slice[k][col];
     out[c] = acc;
   }
 }
@@ -569,8 +573,12 @@ hipError_t launch_sq_gemv(const float* d_W, int64_t nrows, int64_t ncols, const 
   double* part = static_cast<double*>(d_ws);
   hipLaunchKernelGGL(sq_gemv_t_partial_kernel, dim3(tiles, unsigned(nchunks)), dim3(kThreads), 0,
                      stream, d_W, nrows, ncols, d_v, part);
-  hipLaunchKernelGGL(sq_gemv_t_total_kernel, dim3(unsigned((ncols + kTotalCols - 1) / kTotalCols)),
-                     dim3(kThreads), 0, stream, part, nchunks, ncols, d_out);
+  auto total = [&](auto kern, int64_t cols) {
+    hipLaunchKernelGGL(kern, dim3(unsigned((ncols + cols - 1) / cols)), dim3(kThreads), 0, stream,
+                       part, nchunks, ncols, d_out);
+  };
+  if (ncols <= kTotalFew) total(sq_gemv_t_total_kernel<16>, 16);
+  else total(sq_gemv_t_total_kernel<kThreads>, kThreads);
   return hipGetLastError();
 }
 
