@@ -432,34 +432,41 @@ struct GaussHermite {
   double x[128], w[128];
 };
 
-// out[i] = E[silu(g)^2], g ~ N(0, var[i]), times scale[i] when scale is given. 16
-// threads a channel, each with every 16th node, then the 16 sums in a tree: a
-// layer has some ten thousand channels, too few for a thread each (11008 channels
-// of 128 nodes 25 us with one thread a channel, 5.2 now).
+// out[i] = E[silu(g)^2], g ~ N(0, var[i]), times scale[i] when scale is given. T
+// threads a channel, each with every T-th node, then the T sums in a tree: 16 up to
+// kSiluPerNode channels for every node, where a thread for each channel would leave
+// the chip waiting for a few long chains, one above, where 16 only add work (one
+// thread against 16: 11008 channels of 128 nodes 26 and 6.1 us, 200 000 52 and 46,
+// 400 000 83 and 85; 65 536 of 32 8.8 and 8.2, of 16 5.5 and 6.5; 1 000 000 of one
+// 5.2 and 53) and for 2^28 channels are more than the 2^32 that a launch holds.
 constexpr int kSiluThreads = 16;
+constexpr int64_t kSiluPerNode = 2048;
 
+template <int T>
 __global__ void __launch_bounds__(kThreads)
 expect_silu_sq_kernel(const double* __restrict__ var, int64_t n, GaussHermite gh,
                       const double* __restrict__ scale, double* __restrict__ out) {
   // indexed by the lane: from LDS, not from the kernel arguments
-  __shared__ double x[128], w[128];
-  for (int k = threadIdx.x; k < gh.n; k += kThreads) {
-    x[k] = gh.x[k];
-    w[k] = gh.w[k];
+  __shared__ double x[T > 1 ? 128 : 1], w[T > 1 ? 128 : 1];
+  if constexpr (T > 1) {
+    for (int k = threadIdx.x; k < gh.n; k += kThreads) {
+      x[k] = gh.x[k];
+      w[k] = gh.w[k];
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  const int64_t i = int64_t(blockIdx.x) * (kThreads / kSiluThreads) + threadIdx.x / kSiluThreads;
-  const int t = threadIdx.x % kSiluThreads;
-  if (i >= n) return;   // whole groups of 16 lanes
+  const int64_t i = int64_t(blockIdx.x) * (kThreads / T) + threadIdx.x / T;
+  const int t = threadIdx.x % T;
+  if (i >= n) return;   // whole groups of T lanes
   const double s = sqrt(2.0 * var[i]);
   double acc = 0.0;
-  for (int k = t; k < gh.n; k += kSiluThreads) {
-    const double g = s * x[k];
+  for (int k = t; k < gh.n; k += T) {
+    const double g = s * (T > 1 ? x[k] : gh.x[k]);
     const double silu = g / (1.0 + exp(-g));
-    acc += w[k] * silu * silu;
+    acc += (T > 1 ? w[k] : gh.w[k]) * silu * silu;
   }
 #pragma unroll
-  for (int d = kSiluThreads / 2; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
+  for (int d = T / 2; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
   const double e = acc / sqrt(3.14159265358979323846);
   if (t == 0) out[i] = scale ? e * scale[i] : e;
 }
@@ -610,10 +617,14 @@ hipError_t launch_expect_silu_sq(const double* d_var, int64_t n, int nodes, cons
     gh.x[k] = x[k];
     gh.w[k] = w[k];
   }
-  const int64_t channels = kThreads / kSiluThreads;
-  const unsigned grid = unsigned((n + channels - 1) / channels);
-  hipLaunchKernelGGL(expect_silu_sq_kernel, dim3(grid), dim3(kThreads), 0, stream, d_var, n, gh,
-                     d_scale, d_out);
+  const int threads = n <= kSiluPerNode * nodes ? kSiluThreads : 1;
+  auto launch = [&](auto kern) {
+    const int64_t channels = kThreads / threads;
+    hipLaunchKernelGGL(kern, dim3(unsigned((n + channels - 1) / channels)), dim3(kThreads), 0, stream,
+                       d_var, n, gh, d_scale, d_out);
+  };
+  if (threads == kSiluThreads) launch(expect_silu_sq_kernel<kSiluThreads>);
+  else launch(expect_silu_sq_kernel<1>);
   return hipGetLastError();
 }
 
