@@ -590,7 +590,7 @@ parse_kernel(const uint32_t* __restrict__ stream, int64_t nwords, const uint8_t*
 // y_v = W_hat x_v for nv right-hand sides, W_hat decoded from the stream on the
 // fly and never stored (the bandwidth motivation of the codec: a GEMV reads
 // l(g)/8 bytes per block instead of 16 for fp16). One wave per row, 128 blocks
-// per wave step (decode_step), so the loads of x stay coalesced. The lane
+// per wave step (fetch_step, use_step), so the loads of x stay coalesced. The lane
 // rebuilds a block's integers exactly as seedq_decompress does and forms
 // d_v = sum_i fp32(acc_i) x_v[8g + i]; since w_hat_i = fp32(acc_i) 2^-(K-1+e)
 // exactly, d_v 2^-(K-1+e) is the block's partial product up to fp32 rounding. A
@@ -911,16 +911,20 @@ hipError_t launch_gemv_stream(const uint32_t* d_stream, int64_t nwords, const ui
   Offsets o;
   const hipError_t err = launch_offsets(d_rung, sr, nrows * G, G, nrows, d_ws, &o, stream);
   if (err != hipSuccess) return err;
-  // Waves per row. A row's wave goes through its steps one after the other, so
-  // few rows leave the chip waiting: 4096 x 4096 (four steps a row) with one
-  // vector 19.6, 19.4 and 24.0 us at 1, 2 and 4 waves a row, 4096 x 14336 46.8,
-  // 42.2 and 45.1, 8192 x 28672 130, 128 and 130, 200 rows of 2000 blocks 20.1,
-  // 13.1 and 13.3; four vectors, whose waves do more between their loads, 57,
-  // 63 and 66 us on 4096 x 14336.
-  const int segs = o.mode == kScanned ? 1
-                   : nrows < 2048     ? 4
-                   : nrows < 4096     ? (nv == 4 ? 2 : 4)
-                                      : (nv == 4 ? 1 : 2);
+  // Waves per row: the most of 4, 2 and 1 with a step of 128 blocks for each and, with
+  // the rows, no more than 1024 a step of a row and 1024. A row's wave goes through
+  // its steps one after the other, so few rows of many steps leave the chip waiting;
+  // each wave more has its own prologue and sum. Kernel times at 1, 2 and 4 waves a
+  // row, one vector and three rungs in runs (2 and 4 vectors and mixed rungs cross at
+  // the same places within 7 %):
+  //   512 x 1024 (1 step) 5.2/5.7/5.8 us; 1500 x 2048 (2) 7.4/7.0/8.0, 2047 rows
+  //   7.5/7.9/8.9; 1000 x 4096 (4) 9.4/8.0/7.7, 3000 rows 13.2/13.2/15.2, 4096 rows
+  //   15.2/15.8/18.6; 2047 x 8192 (8) 16.4/15.3/15.0, 4096 rows 24.0/23.1/25.8, 8192
+  //   rows 41.4/43.1/48.9; 4096 x 16384 (16) 45.0/42.4/42.9; 4096 x 28672 (28)
+  //   74.3/69.3/68.2.
+  const int64_t steps = (G + 127) / 128;
+  auto fits = [&](int64_t w) { return w <= steps && nrows * w <= 1024 * (steps + 1); };
+  const int segs = o.mode == kScanned ? 1 : fits(4) ? 4 : fits(2) ? 2 : 1;
   const unsigned grid = unsigned((nrows * segs + kThreads / 64 - 1) / (kThreads / 64));
   switch (nv) {
     case 1:

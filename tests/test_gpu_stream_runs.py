@@ -14,15 +14,15 @@ pytestmark = pytest.mark.gpu
 RUNGS = [(8, 1), (9, 2), (15, 3), (16, 4), (16, 5), (12, 6), (17, 3), (24, 6)]
 
 
-def _check(sq, oq, rob, rungs, nrows, ncols, nvecs=(1, 4, 8)):
+def _check(sq, oq, rob, rungs, nrows, ncols, nvecs=(1, 4, 8), many=False):
     rng = np.random.default_rng(len(rob) + nrows)
-    seed, exp, q = _codes(rng, rob, rungs)
+    seed, exp, q = (_many_codes if many else _codes)(rng, rob, rungs)
     valid = rob < len(rungs)
-    ref = ostream.pack(seed[valid], exp[valid], q[valid], rob[valid], rungs)
     cnt = np.bincount(rob[valid], minlength=len(rungs))
     d = _t(rob) if len(rungs) > 1 else None
     w = sq.pack(_t(seed.view(np.int32)), _t(exp), _t(q), rungs, nrows, ncols, d, cnt)
-    assert np.array_equal(_words(w), ref)
+    if not many:   # the oracle's packer is slow
+        assert np.array_equal(_words(w), ostream.pack(seed[valid], exp[valid], q[valid], rob[valid], rungs))
     s, e, qq = (t.cpu().numpy() for t in sq.unpack(w, rungs, nrows, ncols, d))
     assert np.array_equal(s.view(np.uint32)[valid], seed[valid]) and np.all(s[~valid] == 0)
     assert np.array_equal(e[valid], exp[valid]) and np.array_equal(qq[valid], q[valid])
@@ -100,6 +100,52 @@ def test_long_stretch_without_bits_costs_no_more_than_codes(sq, oq):  # noqa: F8
     _check(sq, oq, rob, rungs, 1, 8 * len(rob), nvecs=())
     full = np.resize(np.array([0, 1], np.uint8), len(rob))
     assert _pack_ms(sq, rob, rungs) < 10 * _pack_ms(sq, full, rungs)
+
+
+def _many_codes(rng, rob, rungs):
+    """_codes for many blocks."""
+    n, r = len(rob), np.minimum(rob, len(rungs))
+    K = np.array([k for k, _ in rungs] + [1])[r]
+    P = np.array([p for _, p in rungs] + [0])[r]
+    seed = np.where(r < len(rungs), rng.integers(0, 1 << 30, n) % ((1 << K) - 1) + 1, 0)
+    q = rng.integers(-8, 8, (n, 8)) * (np.arange(8) < P[:, None])
+    return seed.astype(np.uint32), rng.integers(0, 16, n).astype(np.uint8), q.astype(np.int8)
+
+
+# one step of 128 blocks a row, two (the second of 12 blocks), four and nine of them,
+# with row counts at which the waves a row change (1024 (steps + 1) / 2 and / 4) and
+# that leave a workgroup's last rows past the end
+@pytest.mark.parametrize("nrows,G", [(2047, 100), (1535, 140), (1536, 140), (1537, 140),
+                                     (1279, 400), (1280, 400), (1281, 400), (2559, 400), (2560, 400),
+                                     (2561, 400), (4097, 400), (2559, 1030), (2561, 1030)])
+def test_rows_by_several_waves(sq, oq, nrows, G):  # noqa: F811
+    rng = np.random.default_rng(nrows)
+    rob = np.sort(rng.integers(0, 3, (nrows, G)), axis=1).astype(np.uint8)
+    rob[:, G // 3:G // 2] = rng.integers(0, 3, (nrows, G // 2 - G // 3))
+    rob[::97, G - 1] = 255    # rows poisoned by a block without a code, the last one
+    rob[50::89, 3] = 9
+    rob[nrows - 1] = 2
+    _check(sq, oq, rob.ravel(), [(12, 2), (16, 3), (20, 4)], nrows, 8 * G, nvecs=(1, 2, 4),
+           many=True)
+
+
+def test_one_wave_for_each_of_very_many_rows(sq):  # noqa: F811
+    # two waves for each of 2^25 rows would be more threads than a launch holds
+    import torch
+    nrows = (1 << 25) + 3
+    g = torch.Generator(device="cuda").manual_seed(5)
+    seed = torch.randint(1, 256, (nrows,), device="cuda", generator=g, dtype=torch.int32)
+    exp = torch.randint(0, 16, (nrows,), device="cuda", generator=g, dtype=torch.uint8)
+    q = torch.zeros(nrows, 8, dtype=torch.int8, device="cuda")
+    q[:, 0] = torch.randint(-8, 8, (nrows,), device="cuda", generator=g, dtype=torch.int8)
+    w = sq.pack(seed, exp, q, [(8, 1)], nrows, 8)
+    W = sq.decompress(seed, exp, q, [(8, 1)], nrows, 8)[0].double()
+    x = torch.randn(2, 8, device="cuda", generator=g)
+    y = sq.gemv_stream(w, [(8, 1)], nrows, 8, x)
+    for v in range(2):
+        p = W * x[v].double()   # (a matrix product of so many rows comes back cut)
+        want, size = p.sum(1), p.abs().sum(1)
+        assert bool(((y[v].double() - want).abs() <= 16 * 2.0 ** -24 * size).all())
 
 
 def test_more_rows_than_group_sums_reach(sq, oq):  # noqa: F811
