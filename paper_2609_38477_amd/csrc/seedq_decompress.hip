@@ -14,6 +14,7 @@ namespace {
 
 constexpr int kDecompressThreads = 256;
 
+template <bool kPast>
 __global__ void __launch_bounds__(kDecompressThreads)
 decompress_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__ expo,
                   const int8_t* __restrict__ q, const uint8_t* __restrict__ rung, RungTable rt,
@@ -48,7 +49,7 @@ decompress_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__
   __syncthreads();
   const int64_t nlive = nblocks - b0 < kDecompressThreads ? nblocks - b0 : kDecompressThreads;
   float4* dst = reinterpret_cast<float4*>(W_hat + b0 * kC);
-  for (int i = threadIdx.x; i < 2 * nlive; i += kDecompressThreads) store_streaming(&dst[i], stage[i]);
+  for (int i = threadIdx.x; i < 2 * nlive; i += kDecompressThreads) store_result<kPast>(&dst[i], stage[i]);
   if (acc_out && live) {
     if (!ok) {
 #pragma unroll
@@ -68,8 +69,14 @@ hipError_t launch_decompress(const uint32_t* d_seed, const uint8_t* d_exp, const
   if (nblocks == 0) return hipSuccess;
   const int threads = kDecompressThreads;
   const int64_t blocks = (nblocks + threads - 1) / threads;
-  hipLaunchKernelGGL(decompress_kernel, dim3(unsigned(blocks)), dim3(threads), 0, stream, d_seed,
-                     d_exp, d_q, d_rung, rt, nblocks, d_W_hat, d_acc);
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(unsigned(blocks)), dim3(threads), 0, stream, d_seed, d_exp, d_q,
+                       d_rung, rt, nblocks, d_W_hat, d_acc);
+  };
+  if (stores_past_caches((d_rung ? 14 : 13) * nblocks, (d_acc ? 64 : 32) * nblocks))
+    launch(decompress_kernel<true>);
+  else
+    launch(decompress_kernel<false>);
   return hipGetLastError();
 }
 

@@ -17,7 +17,7 @@
 
 #include <hip/hip_fp16.h>
 
-#include "seedq_internal.h"
+#include "seedq_reconstruct.h"
 
 namespace seedq {
 namespace {
@@ -481,6 +481,7 @@ expect_silu_sq_kernel(const double* __restrict__ var, int64_t n, GaussHermite gh
 // take the direct form: one thread per element, grid-stride.
 constexpr int64_t kPermLdsCols = 16384;   // 64 KB of row plus 2 KB of marks
 
+template <bool kPast>
 __global__ void __launch_bounds__(kThreads)
 permute_rows_lds_kernel(const float* __restrict__ in, int64_t nrows, int64_t ncols,
                         const int32_t* __restrict__ perm, int inverse, float* __restrict__ out) {
@@ -512,9 +513,9 @@ permute_rows_lds_kernel(const float* __restrict__ in, int64_t nrows, int64_t nco
     for (int j = threadIdx.x; j < n; j += kThreads) {
       if (!inverse) {
         const int32_t p = perm[j];
-        __builtin_nontemporal_store((p >= 0 && p < n) ? row[p] : __int_as_float(0x7fc00000), &dst[j]);
+        store_result<kPast>(&dst[j], (p >= 0 && p < n) ? row[p] : __int_as_float(0x7fc00000));
       } else if ((mark[j / 32] >> (j % 32)) & 1u) {
-        __builtin_nontemporal_store(row[j], &dst[j]);
+        store_result<kPast>(&dst[j], row[j]);
       }
     }
   }
@@ -676,16 +677,21 @@ hipError_t launch_permute_columns(const float* d_in, int64_t nrows, int64_t ncol
                                   hipStream_t stream) {
   if (ncols <= kPermLdsCols) {
     const size_t lds = size_t(ncols) * 4 + size_t((ncols + 31) / 32) * 4;
-    // more than 64 KB of dynamic LDS must be allowed for the kernel (set on
-    // every call: the attribute belongs to the current device)
-    const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(permute_rows_lds_kernel),
-        hipFuncAttributeMaxDynamicSharedMemorySize, int(kPermLdsCols * 4 + kPermLdsCols / 8));
-    if (attr != hipSuccess) return attr;
-    const int64_t blocks = std::min<int64_t>(nrows, 8192);
-    hipLaunchKernelGGL(permute_rows_lds_kernel, dim3(unsigned(blocks)), dim3(kThreads), lds, stream,
-                       d_in, nrows, ncols, d_perm, inverse, d_out);
-    return hipGetLastError();
+    auto launch = [&](auto kern) {
+      // more than 64 KB of dynamic LDS must be allowed for the kernel (set on
+      // every call: the attribute belongs to the current device)
+      const hipError_t attr = hipFuncSetAttribute(
+          reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+          int(kPermLdsCols * 4 + kPermLdsCols / 8));
+      if (attr != hipSuccess) return attr;
+      const int64_t blocks = std::min<int64_t>(nrows, 8192);
+      hipLaunchKernelGGL(kern, dim3(unsigned(blocks)), dim3(kThreads), lds, stream, d_in, nrows, ncols,
+                         d_perm, inverse, d_out);
+      return hipGetLastError();
+    };
+    const int64_t bytes = 4 * nrows * ncols;
+    return stores_past_caches(bytes, bytes) ? launch(permute_rows_lds_kernel<true>)
+                                            : launch(permute_rows_lds_kernel<false>);
   }
   const int64_t blocks = std::min<int64_t>((nrows * ncols + kThreads - 1) / kThreads, 65536);
   hipLaunchKernelGGL(permute_columns_kernel, dim3(unsigned(blocks)), dim3(kThreads), 0, stream, d_in,

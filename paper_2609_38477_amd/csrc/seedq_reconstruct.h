@@ -8,17 +8,38 @@
 
 namespace seedq {
 
-// Stores of results that are written once and not read by the kernel: past the
-// caches' replacement order, so that a stream of them does not push out what is
-// still to be read (a decode of 8192 x 28672 weights 259 -> 177 us, of 4096 x
-// 4096 from codes 17.6 -> 14.0 us).
-__device__ __forceinline__ void store_streaming(float4* dst, const float4& v) {
-  typedef float f4 __attribute__((ext_vector_type(4)));
-  __builtin_nontemporal_store(f4{v.x, v.y, v.z, v.w}, reinterpret_cast<f4*>(dst));
+// Stores past the caches' replacement order (past = true) or ordinary ones. A call
+// stores past them when what it reads and writes exceeds the 256 MiB memory-side
+// cache (stores_past_caches): its output could not stay there whole, and ordinary
+// stores only push out what the call or the next one reads. Below that the output
+// stays for its reader, which pays for memory otherwise. Measured with the caches
+// flushed before, past them against ordinary, in us:
+//   stream to weights, then a matrix-vector product: 64 MiB of weights 69/61, 172 MiB
+//     155/115, 256 MiB 195/194, 896 MiB 538/560; then the inverse permutation: 64 MiB
+//     114/84, 128 MiB 282/191, 256 MiB 810/799, 896 MiB 3521/3578;
+//   codes to weights, then a product: 64 MiB 64/54, 224 MiB 172/167, 896 MiB 536/544;
+//   the call alone is the same either way (stream to weights, 64 MiB 39/41, 224 MiB
+//     83/84, 896 MiB 266/269), and faster past the caches only where the same call on
+//     the same inputs went before (224 MiB 60/70, 896 MiB 186/266).
+constexpr int64_t kMemorySideCache = int64_t(256) << 20;
+inline bool stores_past_caches(int64_t bytes_read, int64_t bytes_written) {
+  return bytes_read + bytes_written > kMemorySideCache;
 }
-__device__ __forceinline__ void store_streaming(uint2* dst, uint32_t x, uint32_t y) {
+// (a template argument: with a run-time one the compiler makes one ordinary store of both)
+template <bool kPast, typename T>
+__device__ __forceinline__ void store_result(T* dst, T v) {
+  if constexpr (kPast) __builtin_nontemporal_store(v, dst);
+  else *dst = v;
+}
+template <bool kPast>
+__device__ __forceinline__ void store_result(float4* dst, const float4& v) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  store_result<kPast>(reinterpret_cast<f4*>(dst), f4{v.x, v.y, v.z, v.w});
+}
+template <bool kPast>
+__device__ __forceinline__ void store_result(uint2* dst, uint32_t x, uint32_t y) {
   typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-  __builtin_nontemporal_store(u2{x, y}, reinterpret_cast<u2*>(dst));
+  store_result<kPast>(reinterpret_cast<u2*>(dst), u2{x, y});
 }
 
 // Rung constants for per-lane lookups, kept in LDS: entry r = (K, P, LFSR

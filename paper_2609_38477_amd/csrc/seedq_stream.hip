@@ -491,9 +491,13 @@ pack_kernel(const uint32_t* __restrict__ seed, const uint8_t* __restrict__ expo,
       }
   }
   __syncthreads();
-  // the words that begin inside the chunk
+  // the words that begin inside the chunk, past the caches' replacement order: an
+  // eighth of what the call reads, so that its reader pays little for it (a
+  // decode-GEMV of 4096 x 11008 right after 101 us, 99 with ordinary stores), and a
+  // call among others finds more of its inputs (30 us, 37)
   const int64_t off1 = end_s, g0 = (off0 + 31) >> 5, g1 = min(nwords, (off1 + 31) >> 5);
-  for (int64_t gw = g0 + threadIdx.x; gw < g1; gw += kThreads) __builtin_nontemporal_store(stage[gw - w0], &stream[gw]);
+  for (int64_t gw = g0 + threadIdx.x; gw < g1; gw += kThreads)
+    __builtin_nontemporal_store(stage[gw - w0], &stream[gw]);
 }
 
 // Four mantissa nibbles as sign-extended bytes.
@@ -508,7 +512,7 @@ __device__ __forceinline__ uint32_t nibbles_to_bytes(uint32_t n) {
 // mantissas as bytes), MODE 1 the reconstructed weights. A block whose bits
 // are not all inside the stream, or whose rung byte is out of range, decodes
 // to seed 0 (MODE 1: NaN weights).
-template <int MODE>
+template <int MODE, bool kPast>
 __global__ void __launch_bounds__(kThreads)
 parse_kernel(const uint32_t* __restrict__ stream, int64_t nwords, const uint8_t* __restrict__ rung,
              StreamRungs sr, int64_t nblocks, Offsets o, uint32_t* __restrict__ seed_out,
@@ -536,15 +540,15 @@ parse_kernel(const uint32_t* __restrict__ stream, int64_t nwords, const uint8_t*
     const int n = 2 * int(min(int64_t(64), b1 - g0));
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-      if (64 * k + lane < n) store_streaming(&dst[64 * k + lane], stage[64 * k + lane]);
+      if (64 * k + lane < n) store_result<kPast>(&dst[64 * k + lane], stage[64 * k + lane]);
     __builtin_amdgcn_wave_barrier();
   };
   auto code = [&](int64_t g, const Code& c, int P) __attribute__((always_inline)) {
     const uint32_t q = c.ok ? c.q & ((1u << (4 * P)) - 1u) : 0u;
-    __builtin_nontemporal_store(c.ok ? c.seed : 0u, &seed_out[g]);
-    __builtin_nontemporal_store(uint8_t(c.ok ? c.e : 0), &exp_out[g]);
-    store_streaming(reinterpret_cast<uint2*>(q_out) + g, nibbles_to_bytes(q & 0xFFFFu),
-                    nibbles_to_bytes(q >> 16));
+    store_result<kPast>(&seed_out[g], c.ok ? c.seed : 0u);
+    store_result<kPast>(&exp_out[g], uint8_t(c.ok ? c.e : 0));
+    store_result<kPast>(reinterpret_cast<uint2*>(q_out) + g, nibbles_to_bytes(q & 0xFFFFu),
+                        nibbles_to_bytes(q >> 16));
   };
   auto fetch = [&](int64_t g0) __attribute__((always_inline)) {
     return fetch_step(stream, nwords, tab, uint32_t(sr.rt.n), rung ? rung + g0 : nullptr, b1 - g0,
@@ -893,12 +897,14 @@ hipError_t launch_parse(const uint32_t* d_stream, int64_t nwords, const uint8_t*
   Offsets o;
   const hipError_t err = launch_offsets(d_rung, sr, nblocks, kChunk, nchunks, d_ws, &o, stream);
   if (err != hipSuccess) return err;
-  if (d_W_hat)
-    hipLaunchKernelGGL(parse_kernel<1>, dim3(unsigned(nchunks)), dim3(kThreads), 0, stream, d_stream,
-                       nwords, d_rung, sr, nblocks, o, nullptr, nullptr, nullptr, d_W_hat);
-  else
-    hipLaunchKernelGGL(parse_kernel<0>, dim3(unsigned(nchunks)), dim3(kThreads), 0, stream, d_stream,
-                       nwords, d_rung, sr, nblocks, o, d_seed, d_exp, d_q, nullptr);
+  const int64_t bytes_in = 4 * nwords + (d_rung ? nblocks : 0);
+  const bool past = stores_past_caches(bytes_in, (d_W_hat ? 32 : 13) * nblocks);
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(unsigned(nchunks)), dim3(kThreads), 0, stream, d_stream, nwords, d_rung,
+                       sr, nblocks, o, d_seed, d_exp, d_q, d_W_hat);
+  };
+  if (d_W_hat) past ? launch(parse_kernel<1, true>) : launch(parse_kernel<1, false>);
+  else past ? launch(parse_kernel<0, true>) : launch(parse_kernel<0, false>);
   return hipGetLastError();
 }
 
