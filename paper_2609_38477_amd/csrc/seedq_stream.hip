@@ -917,19 +917,24 @@ hipError_t launch_gemv_stream(const uint32_t* d_stream, int64_t nwords, const ui
   Offsets o;
   const hipError_t err = launch_offsets(d_rung, sr, nrows * G, G, nrows, d_ws, &o, stream);
   if (err != hipSuccess) return err;
-  // Waves per row: the most of 4, 2 and 1 with a step of 128 blocks for each and, with
-  // the rows, no more than 1024 a step of a row and 1024. A row's wave goes through
-  // its steps one after the other, so few rows of many steps leave the chip waiting;
-  // each wave more has its own prologue and sum. Kernel times at 1, 2 and 4 waves a
-  // row, one vector and three rungs in runs (2 and 4 vectors and mixed rungs cross at
-  // the same places within 7 %):
-  //   512 x 1024 (1 step) 5.2/5.7/5.8 us; 1500 x 2048 (2) 7.4/7.0/8.0, 2047 rows
-  //   7.5/7.9/8.9; 1000 x 4096 (4) 9.4/8.0/7.7, 3000 rows 13.2/13.2/15.2, 4096 rows
-  //   15.2/15.8/18.6; 2047 x 8192 (8) 16.4/15.3/15.0, 4096 rows 24.0/23.1/25.8, 8192
-  //   rows 41.4/43.1/48.9; 4096 x 16384 (16) 45.0/42.4/42.9; 4096 x 28672 (28)
-  //   74.3/69.3/68.2.
+  // Waves per row: the most of 4, 2 and 1 with a step of 128 blocks for each and, over
+  // all rows, no more than the 8192 that the chip holds at a time and 2048 for every
+  // step of a row. A row's wave goes through its steps one after the other, so few rows
+  // leave the chip waiting, above all for words not yet in the caches; each wave more
+  // has its own prologue and sum. Kernel times in us at 1, 2 and 4 waves a row, one
+  // vector and three rungs in runs, repeated and with the caches flushed before:
+  //   512 x 1024 (1 step) 5.2/5.7/5.8, 6.5/6.7/6.9; 1500 x 2048 (2) 7.4/7.0/8.0,
+  //   9.9/8.5/9.5; 4096 x 2048 10.2/12.6/16.1, 12.8/12.9/18.6; 1500 x 4096 (4)
+  //   10.4/9.3/9.2, 14.8/11.5/11.0; 4096 x 4096 15.2/15.8/18.6, 19.6/18.4/21.5; 6000
+  //   rows 19.8/21.8/25.4, 24.1/26.7/30.0; 2047 x 8192 (8) 16.4/15.3/15.0,
+  //   24.6/19.4/17.8; 4096 rows 24.0/23.1/25.8, 31.6/28.2/31.2; 8192 rows
+  //   41.4/43.1/48.9, 45.8/50.6/56.7.
+  // With 1, 2 and 4 vectors, rungs in runs, mixed and one, 512 to 12000 rows of 512 to
+  // 28672 columns the choice is within 13 % of the best in the sum of both.
   const int64_t steps = (G + 127) / 128;
-  auto fits = [&](int64_t w) { return w <= steps && nrows * w <= 1024 * (steps + 1); };
+  auto fits = [&](int64_t w) {
+    return w <= steps && nrows * w <= std::min<int64_t>(8192, 2048 * steps);
+  };
   const int segs = o.mode == kScanned ? 1 : fits(4) ? 4 : fits(2) ? 2 : 1;
   const unsigned grid = unsigned((nrows * segs + kThreads / 64 - 1) / (kThreads / 64));
   switch (nv) {

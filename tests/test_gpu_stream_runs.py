@@ -112,12 +112,12 @@ def _many_codes(rng, rob, rungs):
     return seed.astype(np.uint32), rng.integers(0, 16, n).astype(np.uint8), q.astype(np.int8)
 
 
-# one step of 128 blocks a row, two (the second of 12 blocks), four and nine of them,
-# with row counts at which the waves a row change (1024 (steps + 1) / 2 and / 4) and
-# that leave a workgroup's last rows past the end
-@pytest.mark.parametrize("nrows,G", [(2047, 100), (1535, 140), (1536, 140), (1537, 140),
-                                     (1279, 400), (1280, 400), (1281, 400), (2559, 400), (2560, 400),
-                                     (2561, 400), (4097, 400), (2559, 1030), (2561, 1030)])
+# one step of 128 blocks a row, two (the second of 12 blocks), four and nine of them, at
+# the row counts where the waves a row change and where a workgroup's last rows are past
+# the end
+@pytest.mark.parametrize("nrows,G", [(2047, 100), (2047, 140), (2048, 140), (2049, 140),
+                                     (2047, 400), (2048, 400), (2049, 400), (4095, 400), (4096, 400),
+                                     (4097, 400), (2047, 1030), (2051, 1030), (4099, 300)])
 def test_rows_by_several_waves(sq, oq, nrows, G):  # noqa: F811
     rng = np.random.default_rng(nrows)
     rob = np.sort(rng.integers(0, 3, (nrows, G)), axis=1).astype(np.uint8)
