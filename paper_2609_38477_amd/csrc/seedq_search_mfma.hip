@@ -469,14 +469,17 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
     float amax = 0.f;
 #pragma unroll
     for (int i = 0; i < kC; ++i) amax = fmaxf(amax, fabsf(w[i]));
-    active[nt] = valid[nt] && amax > 0.f;
-    const int ex = active[nt] ? ilogbf(amax) : 0;
+    const int ex = valid[nt] && amax > 0.f ? ilogbf(amax) : 0;
     float ws[kC], ww = 0.f;
 #pragma unroll
     for (int i = 0; i < kC; ++i) {
       ws[i] = ldexpf(w[i], -ex);
       ww = fmaf(ws[i], ws[i], ww);
     }
+    // a block with a weight that is not finite has no bound that passes, only the
+    // pilot's errors: the first range's, so that its code does not depend on which
+    // range runs first
+    active[nt] = valid[nt] && amax > 0.f && (ww < INFINITY || rg.range == 0);
     thr[nt] = active[nt] ? -INFINITY : INFINITY;
     float base = 0.f;
     if constexpr (M > 0) {
@@ -900,8 +903,13 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
     b_fragment<0>(ws, ww, h, rd);
     b_fragment<1>(ws, ww, h, rd);
     b_fragment<2>(ws, ww, h, rd);
-    const float base = threshold_base<P>(ww, rd);
+    float base = threshold_base<P>(ww, rd);
+    // a block with a weight that is not finite: searched in the first range only, as
+    // in search_mfma_kernel (elsewhere the threshold +inf over an error of 0)
+    const bool skip = valid && !(ww < INFINITY) && rg.range > 0;
+    if (skip) base = INFINITY;
     if (h == 0) {
+      if (skip) best[nt * 32 + n] = 0ull;
       slot_thr[nt * 32 + n] = base;
       slot_ex[nt * 32 + n] = int16_t(ex);
     }

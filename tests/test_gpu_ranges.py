@@ -1,6 +1,8 @@
 """The search's launch rules on both sides of their lines: how many 32-block tiles a wave owns
 (1, 2 or 4, the last one in two kernels) and into how many ranges of seed tiles a rung is cut
 follow the count of blocks, and none of it may show in the codes."""
+import os
+
 import numpy as np
 import pytest
 
@@ -33,3 +35,38 @@ def test_search_same_codes_at_every_tile_count(sq, oq, torch, K, P, line):  # no
     at = np.linspace(0, rows * G - 1, 128).astype(np.int64)
     seed, e, q, err = (t.numpy()[at] for t in whole)
     check_search(oq, W.reshape(-1, 8)[at], K, P, seed.view(np.uint32), e, q, err, f"K{K}P{P}")
+
+
+def _with_ranges(tiles, f):
+    saved = os.environ.pop("SEEDQ_SEED_CHUNK_TILES", None)
+    try:
+        if tiles is not None:
+            os.environ["SEEDQ_SEED_CHUNK_TILES"] = tiles
+        return [t.cpu() for t in f()]
+    finally:
+        os.environ.pop("SEEDQ_SEED_CHUNK_TILES", None)
+        if saved is not None:
+            os.environ["SEEDQ_SEED_CHUNK_TILES"] = saved
+
+
+@pytest.mark.parametrize("K,P", [(12, 1), (12, 3), (13, 4), (16, 4), (12, 5), (12, 6)])
+def test_blocks_that_are_not_finite_do_not_depend_on_the_ranges(sq, torch, K, P):  # noqa: F811
+    # the contract asks for finite weights; a block without them still gets one code,
+    # from the first seed tile, whatever the ranges and the order in which they run
+    W = synthetic.weights(4, 8 * 203, 0.02, key=70 + K + P)
+    b = W.reshape(-1, 8)
+    bad = [3, 40, 41, 300, 555, 811]
+    for n, i in enumerate(bad):
+        b[i, n] = [np.nan, np.inf, -np.inf][n % 3]
+    b[300] = [np.inf, -np.inf] * 4
+    big = np.concatenate([W] * 40)   # and in a call of several block tiles a wave
+    bases = [sq.build_bases(K, P)]
+    first = _with_ranges("0", lambda: sq.compress(_dev(torch, W), bases))
+    assert bool((first[0][bad] <= 32).all()) and bool((first[0][bad] >= 1).all())
+    for v in (None, "8", "8"):
+        for part in (W, big):
+            got = _with_ranges(v, lambda: sq.compress(_dev(torch, part), bases))
+            for a, c in zip(first[:3], got[:3]):
+                n = len(first[0])
+                for k in range(0, len(c), n):
+                    assert torch.equal(a, c[k:k + n]), (K, P, v)
