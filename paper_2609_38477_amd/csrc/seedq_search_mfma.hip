@@ -186,19 +186,25 @@ struct RangeRule {
   int32_t rmin;             // at least so many ranges
   int32_t rlong, target;    // up to rlong of them for `target` workgroups
   int32_t rshort, fill;     // up to rshort of them for `fill` workgroups
+  int32_t emit;             // a walk of one range emits the codes itself
   int32_t first, span;  // ranges of this launch
 };
 struct SeedRange {
   int range, nranges;
   int64_t unit;
 };
+__host__ __device__ inline int range_count(const RangeRule& rule, uint32_t units) {
+  if (units == 0u) return 1;
+  const int t = int(uint32_t(rule.target) / units), f = int(uint32_t(rule.fill) / units);
+  const int a = t < rule.rlong ? t : rule.rlong, b = f < rule.rshort ? f : rule.rshort;
+  const int nr = a > b ? a : b;
+  return nr > rule.rmin ? nr : rule.rmin;
+}
 SEEDQ_INLINE SeedRange seed_range(const RangeRule& rule, int64_t count, int blocks_per_wg) {
   const uint32_t units = uint32_t((count + blocks_per_wg - 1) / blocks_per_wg);
   if (units == 0u) return {1, 1, 0};
   // wave-uniform (the divisions are done in vector registers)
-  const int t = __builtin_amdgcn_readfirstlane(int(uint32_t(rule.target) / units));
-  const int f = __builtin_amdgcn_readfirstlane(int(uint32_t(rule.fill) / units));
-  const int nr = max(rule.rmin, max(min(t, rule.rlong), min(f, rule.rshort)));
+  const int nr = __builtin_amdgcn_readfirstlane(range_count(rule, units));
   const uint32_t r = uint32_t(__builtin_amdgcn_readfirstlane(int(blockIdx.x / units)));
   if (r >= uint32_t(rule.span)) return {nr, nr, 0};
   return {int(r) + rule.first, nr, int64_t(blockIdx.x - r * units)};
@@ -342,6 +348,38 @@ SEEDQ_INLINE void merge_best(unsigned long long* keys, int64_t b, unsigned long 
   }
 }
 
+// Writes the code of block b: seed's, evaluated once more, or, where no seed was ever
+// a candidate (kNoSeed: the weights are all zero), the smallest seed with e = 15,
+// q = 0 and error 0. q_out holds a block's mantissas, q_0 first.
+template <int P>
+SEEDQ_INLINE void emit_code(int64_t b, uint32_t seed, const float (&w)[kC], int K, uint32_t mask,
+                            const uint32_t* __restrict__ ub, const float* __restrict__ pinv32,
+                            const double* __restrict__ pinv64, uint32_t* __restrict__ seed_out,
+                            uint8_t* __restrict__ exp_out, unsigned long long* __restrict__ q_out,
+                            float* __restrict__ err_out) {
+  int qe = 15, q[P] = {};
+  double err = 0.0;
+  if (seed != kNoSeed) {
+    const double* A = pinv64 + int64_t(seed - 1) * (P * kC);
+    const uint32_t* Ub = ub + int64_t(seed - 1) * basis_words(K, P);
+    if constexpr (many_survivors(P))
+      err = exact_eval_f32<P>(w, pinv32 + int64_t(seed - 1) * (P * kC), A, Ub, seed, K, mask, qe, q);
+    else
+      err = exact_eval<P, false>(w, A, Ub, seed, K, mask, qe, q);
+  }
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const uint32_t byte = uint32_t(uint8_t(int8_t(q[p])));
+    if (p < 4) lo |= byte << (8 * p);
+    else hi |= byte << (8 * (p - 4));
+  }
+  seed_out[b] = seed != kNoSeed ? seed : 1u;
+  exp_out[b] = uint8_t(qe);
+  q_out[b] = uint64_t(lo) | uint64_t(hi) << 32;
+  if (err_out) err_out[b] = float(err);
+}
+
 // Number of lanes below this one whose bit is set in mask.
 SEEDQ_INLINE int lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u));
@@ -403,7 +441,8 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
                    const uint32_t* __restrict__ ub, const float* __restrict__ pinv32,
                    const double* __restrict__ pinv64, const half8* __restrict__ pi16,
                    int64_t ntiles, RangeRule rule,
-                   unsigned long long* __restrict__ keys) {
+                   unsigned long long* __restrict__ keys, uint32_t* __restrict__ seed_out,
+                   uint8_t* __restrict__ exp_out, float* __restrict__ err_out) {
   constexpr int kS = NT * 32;   // blocks per wave
   __shared__ unsigned long long best_all[kWaves][kS];
   __shared__ uint32_t sbest_all[kWaves][kS];
@@ -493,7 +532,8 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
       base = threshold_base<P>(ww, rd);
     }
     // a range starts from the best that the others have left so far
-    const unsigned long long bound = valid[nt] ? key_bound(load_key(keys, b)) : ~0ull;
+    const unsigned long long bound =
+        valid[nt] && rg.nranges > 1 ? key_bound(load_key(keys, b)) : ~0ull;
     fresh |= active[nt] && bound == ~0ull;
     if (h == 0) {
       best[nt * 32 + n] = bound;
@@ -819,6 +859,15 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   evaluate(1);
 
   // ---------------------------------------------------------------- results
+  if (rg.nranges == 1) {   // rule.emit: nothing else looks for these blocks' codes
+    for (int slot = lane; slot < kS && wave_base + slot < count; slot += 64) {
+      float w[kC];
+      load_block(W, blk[slot], true, w);
+      emit_code<P>(blk[slot], sbest[slot], w, K, mask, ub, pinv32, pinv64, seed_out, exp_out, keys,
+                   err_out);
+    }
+    return;
+  }
   for (int i = 0; i < kS; i += 64) {
     const bool mine = i + lane < kS && sbest[i + lane] != kNoSeed;
     const int slot = mine ? i + lane : 0;
@@ -840,7 +889,8 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
                    const uint32_t* __restrict__ ub, const float* __restrict__,
                    const double* __restrict__ pinv64, const half8* __restrict__ pi16,
                    int64_t ntiles, RangeRule rule,
-                   unsigned long long* __restrict__ keys) {
+                   unsigned long long* __restrict__ keys, uint32_t* __restrict__,
+                   uint8_t* __restrict__, float* __restrict__) {
   // 40 KB in all: four workgroups per CU
   __shared__ unsigned long long best_all[kWaves][kSlots];
   __shared__ uint32_t sbest_all[kWaves][kSlots];
@@ -1170,17 +1220,16 @@ clear_keys_kernel(unsigned long long* __restrict__ keys, int64_t nblocks) {
   if (b < nblocks) keys[b] = ~0ull;
 }
 
-// The winning seed of every block of the rung, evaluated once more to emit its
-// code (one block per thread). A block without a key is all zero: every seed
-// ties and the smallest wins, whose evaluation gives e = 15, q = 0 and error 0.
+// The codes of the rung's blocks from their keys, one block per thread, unless the
+// walk was of one range and has written them.
 template <int P>
 __global__ void __launch_bounds__(kWaves * 64)
 emit_codes_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* __restrict__ list,
                   const int32_t* __restrict__ off, int rung, int K, uint32_t mask,
                   const uint32_t* __restrict__ ub, const float* __restrict__ pinv32,
-                  const double* __restrict__ pinv64, uint32_t* __restrict__ seed_out,
-                  uint8_t* __restrict__ exp_out, unsigned long long* __restrict__ keys,
-                  float* __restrict__ err_out) {
+                  const double* __restrict__ pinv64, RangeRule rule, int blocks_per_wg,
+                  unsigned long long* __restrict__ keys, uint32_t* __restrict__ seed_out,
+                  uint8_t* __restrict__ exp_out, float* __restrict__ err_out) {
   int64_t begin = 0, count = nblocks;
   if (list) {
     begin = off[rung];
@@ -1188,30 +1237,14 @@ emit_codes_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* _
   }
   const int64_t i = int64_t(blockIdx.x) * (kWaves * 64) + threadIdx.x;
   if (i >= count) return;
+  if (rule.emit &&
+      range_count(rule, uint32_t((count + blocks_per_wg - 1) / blocks_per_wg)) == 1) return;
   const int64_t b = list ? int64_t(list[begin + i]) : i;
   const unsigned long long key = keys[b];
-  const uint32_t seed = key == ~0ull ? 1u : uint32_t(key & kKeySeed);
   float w[kC];
   load_block(W, b, true, w);
-  int qe, q[P];
-  double err;
-  const double* A = pinv64 + int64_t(seed - 1) * (P * kC);
-  const uint32_t* Ub = ub + int64_t(seed - 1) * basis_words(K, P);
-  if constexpr (many_survivors(P))
-    err = exact_eval_f32<P>(w, pinv32 + int64_t(seed - 1) * (P * kC), A, Ub, seed, K, mask, qe, q);
-  else
-    err = exact_eval<P, false>(w, A, Ub, seed, K, mask, qe, q);
-  uint32_t lo = 0, hi = 0;
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const uint32_t byte = uint32_t(uint8_t(int8_t(q[p])));
-    if (p < 4) lo |= byte << (8 * p);
-    else hi |= byte << (8 * (p - 4));
-  }
-  seed_out[b] = seed;
-  exp_out[b] = uint8_t(qe);
-  keys[b] = uint64_t(lo) | uint64_t(hi) << 32;   // the mantissa output, q_0 first
-  if (err_out) err_out[b] = float(err);
+  emit_code<P>(b, key == ~0ull ? kNoSeed : uint32_t(key & kKeySeed), w, K, mask, ub, pinv32, pinv64,
+               seed_out, exp_out, keys, err_out);
 }
 
 // ---------------------------------------------------------------- launch
@@ -1285,20 +1318,18 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
   unsigned long long* keys = reinterpret_cast<unsigned long long*>(d_q);
   const unsigned threads = kWaves * 64;
   const unsigned per_block = unsigned((nblocks + threads - 1) / threads);
-  if (!d_list)
-    hipLaunchKernelGGL(clear_keys_kernel, dim3(per_block), dim3(threads), 0, stream, keys, nblocks);
   // SEEDQ_SEED_CHUNK_TILES fixes the range length (0 = one range; at least 8
   // tiles per range) for testing: the codes are the same for every length.
   const int64_t tiles = env_int("SEEDQ_SEED_CHUNK_TILES", -1);
   const int64_t most = std::max<int64_t>(1, L.ntiles / 8);
-  const int nt = (nblocks + kBlocksPerWG - 1) / kBlocksPerWG * most < kFewWorkgroups ? 1
-                 : two_tiles(K, P)                                                  ? 2
-                                                                                    : kNB;
+  const bool few = (nblocks + kBlocksPerWG - 1) / kBlocksPerWG * most < kFewWorkgroups;
+  const int nt = few ? 1 : two_tiles(K, P) ? 2 : kNB;
   const int64_t units = (nblocks + kWaves * 32 * nt - 1) / (kWaves * 32 * nt);
   RangeRule rule;
   rule.first = 0;
   rule.target = rule.fill = 0;
   rule.rlong = rule.rshort = 1;
+  rule.emit = !(P == 4 && nt == kNB);
   if (tiles >= 0) {
     rule.rmin = int32_t(tiles > 0 ? std::max<int64_t>(1, std::min(most, L.ntiles / tiles)) : 1);
   } else {
@@ -1308,7 +1339,7 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
     rule.rshort = int32_t(most);
     rule.fill = kFillWorkgroups;
   }
-  // a multi-rung call does not know its count of blocks here: the grid holds
+  // a multi-rung call does not know its counts of blocks here: the grid holds
   // every choice that the rule can make, and the workgroups past it return
   int64_t grid = std::max<int64_t>({units * rule.rmin, rule.target, rule.fill});
   int64_t step = rule.rmin;
@@ -1319,11 +1350,17 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
     rule.span = int32_t(step);
     grid = units * step;
   }
+  const int blocks_per_wg = kWaves * 32 * nt;
+  // a single-rung call knows its count of blocks: where the walk is of one range, and
+  // emits, there are no keys to clear and nothing left to do after it
+  const bool done = !d_list && rule.emit && range_count(rule, uint32_t(units)) == 1;
+  if (!d_list && !done)
+    hipLaunchKernelGGL(clear_keys_kernel, dim3(per_block), dim3(threads), 0, stream, keys, nblocks);
   auto walk = [&](auto kern) {
     for (; rule.first < rule.rmin; rule.first += int32_t(step))
       hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(threads), 0, stream, d_W, nblocks, d_list,
                          d_off, rung, K, mask, ub, pinv32, pinv64, pi16, L.ntiles,
-                         rule, keys);
+                         rule, keys, d_seed, d_exp, d_err);
   };
   if (nt == 1) {
     walk(search_mfma_kernel<P, 1>);
@@ -1334,8 +1371,10 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
   } else {
     if constexpr (P < 4) walk(search_mfma_kernel<P, kNB>);
   }
-  hipLaunchKernelGGL(emit_codes_kernel<P>, dim3(per_block), dim3(threads), 0, stream, d_W, nblocks,
-                     d_list, d_off, rung, K, mask, ub, pinv32, pinv64, d_seed, d_exp, keys, d_err);
+  if (!done)
+    hipLaunchKernelGGL(emit_codes_kernel<P>, dim3(per_block), dim3(threads), 0, stream, d_W, nblocks,
+                       d_list, d_off, rung, K, mask, ub, pinv32, pinv64, rule, blocks_per_wg, keys,
+                       d_seed, d_exp, d_err);
   return hipGetLastError();
 }
 

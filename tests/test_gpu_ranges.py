@@ -49,6 +49,30 @@ def _with_ranges(tiles, f):
             os.environ["SEEDQ_SEED_CHUNK_TILES"] = saved
 
 
+@pytest.mark.parametrize("rungs", [[(8, 1)], [(8, 4)], [(9, 5)], [(8, 6)], [(12, 2)], [(12, 3)],
+                                   [(13, 4)], [(12, 5)], [(12, 6)], [(8, 2), (12, 3), (15, 4)]])
+def test_a_walk_of_one_range_emits_the_same_codes(sq, torch, rungs):  # noqa: F811
+    # one range (the walk writes the codes), the rule's ranges and ranges of 8 tiles
+    # (a kernel emits from the keys): the same codes and errors, all-zero blocks and
+    # blocks without any finite weight among them
+    G, rows = 203, 8
+    W = synthetic.weights(rows, 8 * G, 0.02, key=60 + len(rungs) + rungs[0][1], outlier_frac=0.01)
+    b = W.reshape(-1, 8)
+    b[5] = b[700] = 0.0
+    b[6] = b[701] = b[1623] = np.nan
+    bases = [sq.build_bases(K, P) for K, P in rungs]
+    d, rob = _dev(torch, W), None
+    if len(rungs) > 1:
+        rob = _dev(torch, (np.arange(rows * G) * 7 // 5 % len(rungs)).astype(np.uint8))
+    out = {v: _with_ranges(v, lambda: sq.compress(d, bases, rob)) for v in ("0", None, "8")}
+    for v in (None, "8"):
+        for a, c in zip(out["0"], out[v]):
+            assert torch.equal(a, c), (rungs, v)
+    seed, e, q, err = (t.numpy() for t in out["8"])
+    for i in (5, 700, 6, 701, 1623):   # no seed is better than another: the smallest one
+        assert seed[i] == 1 and e[i] == 15 and not q[i].any() and err[i] == 0.0
+
+
 @pytest.mark.parametrize("K,P", [(12, 1), (12, 3), (13, 4), (16, 4), (12, 5), (12, 6)])
 def test_blocks_that_are_not_finite_do_not_depend_on_the_ranges(sq, torch, K, P):  # noqa: F811
     # the contract asks for finite weights; a block without them still gets one code,
