@@ -186,6 +186,7 @@ struct RangeRule {
   int32_t rmin;             // at least so many ranges
   int32_t rlong, target;    // up to rlong of them for `target` workgroups
   int32_t rshort, fill;     // up to rshort of them for `fill` workgroups
+  int32_t even;             // one range where the units fill the CUs evenly (kEvenTiles)
   int32_t emit;             // a walk of one range emits the codes itself
   int32_t first, span;  // ranges of this launch
 };
@@ -195,6 +196,8 @@ struct SeedRange {
 };
 __host__ __device__ inline int range_count(const RangeRule& rule, uint32_t units) {
   if (units == 0u) return 1;
+  if (rule.even && ((units > 460u && units <= 512u) || (units > 690u && units <= 768u)))
+    return rule.rmin;
   const int t = int(uint32_t(rule.target) / units), f = int(uint32_t(rule.fill) / units);
   const int a = t < rule.rlong ? t : rule.rlong, b = f < rule.rshort ? f : rule.rshort;
   const int nr = a > b ? a : b;
@@ -1271,14 +1274,26 @@ constexpr int64_t kRangeTiles = 2048;
 constexpr int64_t kLongTiles = 64;
 constexpr int kTargetWorkgroups = 12288;
 constexpr int kFillWorkgroups = 768;
+// Up to so many seed tiles (K <= 13) units of 4 block tiles go through one range where
+// they put two or three workgroups on nearly every CU: a second range then costs its
+// prologue, pilot and first survivors for nothing ((13,2) on 262 144 blocks 317 us with
+// 4 ranges, 300 with one, 301 before there were ranges; (13,3) 344, 318; at K = 14 and
+// above 2 % either way).
+constexpr int64_t kEvenTiles = 256;
 // Launches above this many workgroups are cut (HIP grids hold 2^32 threads).
 constexpr int64_t kMaxGrid = int64_t(1) << 23;
 
 // Block tiles per wave: 4 share each seed-tile fragment and its load. Fewer:
 // - 1, when units of 512 blocks times all the ranges of 8 tiles would not make
-//   kFewWorkgroups: (12,4) on 32 768 blocks 156 -> 68 us, (12,3) on 131 072
-//   156 -> 137 us, (8,6) on 262 144 144 -> 117 us, (10,2) on 524 288 190 us
-//   either way.
+//   kFewWorkgroups, for calls of up to kFewBlocks: smaller units then even out the
+//   workgroups that do not fill the places twice. One tile against 4, each with its
+//   ranges: (12,2) on 200 000 blocks 159 and 247 us, on 350 000 266 and 310; (13,2) on
+//   140 000 186 and 265, on 230 000 297 and 298; (14,2) on 66 000 167 and 213, on
+//   140 000 310 and 298; (15,3) on 33 000 176 and 293, on 66 000 306 and 316; (16,3) on
+//   16 000 163 and 193, on 50 000 401 and 370; (8,2) on 400 000 98 and 115, on 2.1 M
+//   434 and 367. Against 2: (12,4) on 140 000 182 and 214, on 262 144 287 and 300;
+//   (11,4) on 300 000 237 and 216; (12,5) on 262 144 322 and 349; (14,6) on 140 000 910
+//   and 971, on 600 000 3682 and 3583; (10,6) on 600 000 569 and 598.
 // - 2, at P = 4 below K = 15 ((11,4) on 524 288 blocks 415 -> 335 us, (12,4) on
 //   1 M 1122 -> 950 us, (14,4) 2382 -> 2293 us; (15,4) 3943 -> 3962 us, (16,4)
 //   +2 %, (20,4) +5 % against the rebuilding kernel) and at P >= 5 ((14,6) 3393
@@ -1286,7 +1301,9 @@ constexpr int64_t kMaxGrid = int64_t(1) << 23;
 //   ms with 4 tiles, which spill, 4.5 ms with 2): there the survivors' registers
 //   and not the fragments' loads bound the walk. At P <= 3 two tiles are 4-14 %
 //   slower.
-constexpr int64_t kFewWorkgroups = 6144;
+constexpr int64_t kFewWorkgroups = 12288;
+template <int P>
+constexpr int64_t kFewBlocks = P == 4 ? 262144 : P == 6 ? INT64_MAX : 393216;
 constexpr bool two_tiles(int K, int P) {
   return P >= 5 || (P == 4 && K < 15);
 }
@@ -1322,13 +1339,15 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
   // tiles per range) for testing: the codes are the same for every length.
   const int64_t tiles = env_int("SEEDQ_SEED_CHUNK_TILES", -1);
   const int64_t most = std::max<int64_t>(1, L.ntiles / 8);
-  const bool few = (nblocks + kBlocksPerWG - 1) / kBlocksPerWG * most < kFewWorkgroups;
+  const bool few = (nblocks + kBlocksPerWG - 1) / kBlocksPerWG * most < kFewWorkgroups &&
+                   nblocks <= kFewBlocks<P>;
   const int nt = few ? 1 : two_tiles(K, P) ? 2 : kNB;
   const int64_t units = (nblocks + kWaves * 32 * nt - 1) / (kWaves * 32 * nt);
   RangeRule rule;
   rule.first = 0;
   rule.target = rule.fill = 0;
   rule.rlong = rule.rshort = 1;
+  rule.even = 0;
   rule.emit = !(P == 4 && nt == kNB);
   if (tiles >= 0) {
     rule.rmin = int32_t(tiles > 0 ? std::max<int64_t>(1, std::min(most, L.ntiles / tiles)) : 1);
@@ -1338,6 +1357,7 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
     rule.target = kTargetWorkgroups;
     rule.rshort = int32_t(most);
     rule.fill = kFillWorkgroups;
+    rule.even = nt == kNB && L.ntiles <= kEvenTiles;
   }
   // a multi-rung call does not know its counts of blocks here: the grid holds
   // every choice that the rule can make, and the workgroups past it return

@@ -12,10 +12,14 @@ from test_gpu_parity import _dev, check_search, sq, torch  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# count of blocks from which units of 512 blocks x (2^K / 256) ranges reach 6144 workgroups
-@pytest.mark.parametrize("K,P,line", [(12, 2, 196608), (12, 3, 196608), (12, 4, 196608),
-                                      (15, 4, 24576), (13, 5, 98304), (14, 5, 49152),
-                                      (13, 6, 98304)])
+# counts of blocks around which the tiles a wave change: units of 512 blocks x (2^K / 256)
+# ranges reach 12288 workgroups, or the calls are large (393 216 blocks, 262 144 at P = 4);
+# and (13,2) and (13,3) where the units fill two workgroups on each CU and go through one
+# range
+@pytest.mark.parametrize("K,P,line", [(8, 2, 393216), (8, 5, 393216), (12, 2, 393216),
+                                      (12, 3, 393216), (12, 4, 262144), (15, 4, 49152),
+                                      (13, 5, 196608), (14, 5, 98304), (13, 6, 196608),
+                                      (13, 2, 260900), (13, 3, 260900)])
 def test_search_same_codes_at_every_tile_count(sq, oq, torch, K, P, line):  # noqa: F811
     # one call of a little more than `line` blocks (a ragged last workgroup, an
     # all-zero block) against the same rows in four calls of one tile per wave
@@ -94,3 +98,144 @@ def test_blocks_that_are_not_finite_do_not_depend_on_the_ranges(sq, torch, K, P)
                 n = len(first[0])
                 for k in range(0, len(c), n):
                     assert torch.equal(a, c[k:k + n]), (K, P, v)
+
+
+def _special_blocks(oq, K, P):
+    """Blocks whose seeds all tie (fp32 subnormals), edge scales, and the spans of
+    rank-deficient seeds with and without noise (or of random seeds where there are none)."""
+    rng = np.random.default_rng(11 * K + P)
+    blocks = [np.full(8, 1e-39), np.full(8, 1.4e-45), rng.uniform(-1, 1, 8) * 1e-42,
+              rng.normal(0, 1e-40, 8), np.zeros(8), rng.normal(0, 1e-30, 8),
+              np.eye(8)[0], np.full(8, 0.02), np.full(8, 1e-39),
+              rng.normal(0, 0.02, 8) * np.array([1, 1, 1, 1e3, 1, 1, 1, 1])]
+    U = oq.basis_int_all(K, P).astype(np.float64) * 2.0 ** -(K - 1)
+    s = np.linalg.svd(U, compute_uv=False)
+    deficient = np.nonzero(s[:, -1] <= 2.0 ** -30 * s[:, 0])[0]
+    if len(deficient) == 0:
+        deficient = rng.integers(0, len(U), 3)
+    for i in deficient[:4]:
+        for k in range(4):
+            blocks.append(U[i] @ rng.normal(0, 0.05, P) + (k % 2) * rng.normal(0, 1e-4, 8))
+    return np.asarray(blocks, dtype=np.float32)
+
+
+@pytest.mark.parametrize("K,P,nblocks", [(12, 2, 400000), (13, 3, 300000), (15, 3, 60000),
+                                         (12, 4, 280000), (14, 4, 110000), (15, 4, 55000),
+                                         (12, 5, 400000), (14, 5, 110000), (13, 6, 210000)])
+def test_special_blocks_in_calls_of_several_tiles_a_wave(sq, oq, torch, K, P, nblocks):  # noqa: F811
+    # the same special blocks at every 997th place of a call that takes four tiles a wave
+    # (P <= 3), two, or the rebuilding kernel ((15,4)); alone and through a rung list
+    sp = _special_blocks(oq, K, P)
+    nblocks -= nblocks % 16
+    W = synthetic.weights(16, nblocks // 2, 0.02, key=80 + K + P, outlier_frac=0.001)
+    b = W.reshape(-1, 8)
+    at = np.arange(0, nblocks - 997 * len(sp), 997)
+    where = np.concatenate([at[:len(at) // len(sp) * len(sp)]])
+    b[where] = np.tile(sp, (len(where) // len(sp), 1))
+    bases = [sq.build_bases(K, P), sq.build_bases(8, 1)]
+    d = _dev(torch, W)
+    seed, e, q, err = (t.cpu().numpy() for t in sq.compress(d, bases[:1]))
+    n = len(sp)
+    ref = check_search(oq, sp, K, P, seed[where[:n]].view(np.uint32), e[where[:n]], q[where[:n]],
+                       err[where[:n]], f"special K{K}P{P}")
+    tied = [0, 1, 2, 3, 4, 8]
+    assert np.array_equal(seed[where[:n]][tied], np.ones(len(tied)))
+    assert np.array_equal(seed[where[:n]][tied], ref.seed[tied])
+    for x in (seed, e, q, err):   # the same at every place
+        assert np.array_equal(x[where].reshape(-1, *x[where[:n]].shape),
+                              np.broadcast_to(x[where[:n]], (len(where) // n, *x[where[:n]].shape)))
+    rob = np.zeros(nblocks, np.uint8)
+    rob[1::50] = 1
+    rob[where] = 0
+    got = [t.cpu().numpy() for t in sq.compress(d, bases, _dev(torch, rob))]
+    for a, c in zip((seed, e, q, err), got):
+        assert np.array_equal(a[rob == 0], c[rob == 0])
+
+
+def test_more_workgroups_than_a_launch_holds(sq, torch):  # noqa: F811
+    # 17 M blocks in ranges of 8 tiles: 33 205 units x 256 ranges, above the 2^23
+    # workgroups of a launch, so the ranges go in turn
+    g = torch.Generator(device="cuda").manual_seed(9)
+    W = torch.randn(17 * 1000 * 1000 // 512 + 1, 8 * 512, device="cuda", generator=g) * 0.02
+    bases = [sq.build_bases(16, 2)]
+    a = _with_ranges(None, lambda: sq.compress(W, bases))
+    b = _with_ranges("8", lambda: sq.compress(W, bases))
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+
+
+def test_keys_that_agree_in_their_upper_bits(sq, oq, torch):  # noqa: F811
+    # a block's key holds 28 mantissa bits of its error: blocks whose two best codes, of
+    # seeds in different ranges, agree in them and differ below, with either seed the
+    # better one. w is moved along the difference of the two reconstructions to where
+    # their errors meet, and of its neighbours in fp32 those are taken whose errors
+    # differ by 2^-45 to 2^-29.
+    K, P = 12, 2
+    rng = np.random.default_rng(3)
+    S = (1 << K) - 1
+    U = oq.basis_int_all(K, P).astype(np.float64) * 2.0 ** -(K - 1)
+    pinv = oq.pinv_stack(K, P)
+
+    def codes(w):   # the reconstruction of w at every seed
+        t = pinv @ w
+        e = np.zeros(S, int)
+        for v in range(16):
+            r = np.rint(t * 2.0 ** v)
+            e = np.where(((r >= -8) & (r <= 7)).all(1), v, e)
+        q = np.clip(np.rint(t * 2.0 ** e[:, None]), -8, 7)
+        return np.einsum("sip,sp->si", U, q) * 2.0 ** -e[:, None]
+
+    blocks, orders = [], [0, 0]
+    for _ in range(400):
+        w = rng.normal(0, 0.02, 8)
+        x = codes(w)
+        err = ((w - x) ** 2).sum(1)
+        a, b = np.argsort(err)[:2]
+        if a // 256 == b // 256 or err[b] > 1.02 * err[a]:   # another range (of 8 tiles), close by
+            continue
+        d = x[a] - x[b]
+        meet = w + d * (((w - x[a]) ** 2).sum() - ((w - x[b]) ** 2).sum()) / (2 * (d @ d))
+        near = (meet + rng.integers(-3, 4, (4000, 8)) * 2.0 ** -30).astype(np.float32).astype(np.float64)
+        ea, eb = ((near - x[a]) ** 2).sum(1), ((near - x[b]) ** 2).sum(1)
+        rel = np.abs(ea - eb) / ea
+        same = (ea.view(np.int64) >> 24) == (eb.view(np.int64) >> 24)
+        for i in np.nonzero(same & (rel > 2.0 ** -45))[0]:
+            o = int((ea[i] < eb[i]) == (a < b))   # 1: the smaller seed is the better one
+            xi = codes(near[i])
+            ei = ((near[i] - xi) ** 2).sum(1)
+            if orders[o] < 8 and set(np.argsort(ei)[:2]) == {a, b}:
+                orders[o] += 1
+                blocks.append(near[i])
+                break
+        if min(orders) >= 8:
+            break
+    assert min(orders) >= 4, orders
+    W = np.asarray(blocks, dtype=np.float32)
+    ref = oq.search(W, K, P)
+    for v in ("8", None, "0"):
+        seed, e, q, err = _with_ranges(v, lambda: sq.compress(_dev(torch, W.reshape(1, -1)),
+                                                              [sq.build_bases(K, P)]))
+        assert np.array_equal(seed.numpy().view(np.uint32), ref.seed), v
+        assert np.array_equal(e.numpy(), ref.e) and np.array_equal(q.numpy()[:, :P], ref.q), v
+
+
+def test_time_follows_the_blocks(sq, torch):  # noqa: F811
+    # measured 1.1 times; 1.7 times where 200 000 blocks took units of 512 in two ranges,
+    # a few more workgroups than the chip has places
+    b = [sq.build_bases(12, 2)]
+    g = torch.Generator(device="cuda").manual_seed(4)
+    best = []
+    for nb in (180000, 200000):
+        W = torch.randn(nb // 8, 64, device="cuda", generator=g) * 0.02
+        sq.compress(W, b)
+        ms = []
+        for _ in range(7):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(4):
+                sq.compress(W, b)
+            end.record()
+            torch.cuda.synchronize()
+            ms.append(start.elapsed_time(end))
+        best.append(min(ms))
+    assert best[1] < 1.35 * best[0], best
