@@ -186,8 +186,6 @@ struct RangeRule {
   int32_t rmin;             // at least so many ranges
   int32_t rlong, target;    // up to rlong of them for `target` workgroups
   int32_t rshort, fill;     // up to rshort of them for `fill` workgroups
-  int32_t even;             // one range where the units fill the CUs evenly (kEvenTiles)
-  int32_t emit;             // a walk of one range emits the codes itself
   int32_t first, span;  // ranges of this launch
 };
 struct SeedRange {
@@ -196,8 +194,6 @@ struct SeedRange {
 };
 __host__ __device__ inline int range_count(const RangeRule& rule, uint32_t units) {
   if (units == 0u) return 1;
-  if (rule.even && ((units > 460u && units <= 512u) || (units > 690u && units <= 768u)))
-    return rule.rmin;
   const int t = int(uint32_t(rule.target) / units), f = int(uint32_t(rule.fill) / units);
   const int a = t < rule.rlong ? t : rule.rlong, b = f < rule.rshort ? f : rule.rshort;
   const int nr = a > b ? a : b;
@@ -436,7 +432,10 @@ template <int P>
 constexpr int kRecVecs = half_records(P) ? 2 : 4;
 typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
 
-template <int P, int NT>
+// kOne: a walk known to be of one range, which emits its codes itself; otherwise the keys
+// hold the best and emit_codes_kernel follows. (As a run-time choice its code made the
+// walks of several ranges slower: (12,3) on 8192 blocks 32.5 -> 34.0 us.)
+template <int P, int NT, bool kOne>
 __global__ void __launch_bounds__(kWaves * 64)
 __attribute__((amdgpu_waves_per_eu(3)))
 search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* __restrict__ list,
@@ -536,7 +535,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
     }
     // a range starts from the best that the others have left so far
     const unsigned long long bound =
-        valid[nt] && rg.nranges > 1 ? key_bound(load_key(keys, b)) : ~0ull;
+        !kOne && valid[nt] ? key_bound(load_key(keys, b)) : ~0ull;
     fresh |= active[nt] && bound == ~0ull;
     if (h == 0) {
       best[nt * 32 + n] = bound;
@@ -862,7 +861,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   evaluate(1);
 
   // ---------------------------------------------------------------- results
-  if (rg.nranges == 1) {   // rule.emit: nothing else looks for these blocks' codes
+  if constexpr (kOne) {
     for (int slot = lane; slot < kS && wave_base + slot < count; slot += 64) {
       float w[kC];
       load_block(W, blk[slot], true, w);
@@ -871,7 +870,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
     }
     return;
   }
-  for (int i = 0; i < kS; i += 64) {
+  for (int i = 0; !kOne && i < kS; i += 64) {
     const bool mine = i + lane < kS && sbest[i + lane] != kNoSeed;
     const int slot = mine ? i + lane : 0;
     merge_best(keys, blk[slot], best[slot], sbest[slot], mine,
@@ -1224,13 +1223,13 @@ clear_keys_kernel(unsigned long long* __restrict__ keys, int64_t nblocks) {
 }
 
 // The codes of the rung's blocks from their keys, one block per thread, unless the
-// walk was of one range and has written them.
+// walk was known to be of one range and has written them.
 template <int P>
 __global__ void __launch_bounds__(kWaves * 64)
 emit_codes_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* __restrict__ list,
                   const int32_t* __restrict__ off, int rung, int K, uint32_t mask,
                   const uint32_t* __restrict__ ub, const float* __restrict__ pinv32,
-                  const double* __restrict__ pinv64, RangeRule rule, int blocks_per_wg,
+                  const double* __restrict__ pinv64,
                   unsigned long long* __restrict__ keys, uint32_t* __restrict__ seed_out,
                   uint8_t* __restrict__ exp_out, float* __restrict__ err_out) {
   int64_t begin = 0, count = nblocks;
@@ -1240,8 +1239,6 @@ emit_codes_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* _
   }
   const int64_t i = int64_t(blockIdx.x) * (kWaves * 64) + threadIdx.x;
   if (i >= count) return;
-  if (rule.emit &&
-      range_count(rule, uint32_t((count + blocks_per_wg - 1) / blocks_per_wg)) == 1) return;
   const int64_t b = list ? int64_t(list[begin + i]) : i;
   const unsigned long long key = keys[b];
   float w[kC];
@@ -1278,7 +1275,8 @@ constexpr int kFillWorkgroups = 768;
 // they put two or three workgroups on nearly every CU: a second range then costs its
 // prologue, pilot and first survivors for nothing ((13,2) on 262 144 blocks 317 us with
 // 4 ranges, 300 with one, 301 before there were ranges; (13,3) 344, 318; at K = 14 and
-// above 2 % either way).
+// above 2 % either way). Decided on the host, for calls with one rung: as a part of
+// range_count it cost every workgroup, 32.5 -> 33.5 us for (12,3) on 8192 blocks.
 constexpr int64_t kEvenTiles = 256;
 // Launches above this many workgroups are cut (HIP grids hold 2^32 threads).
 constexpr int64_t kMaxGrid = int64_t(1) << 23;
@@ -1347,8 +1345,6 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
   rule.first = 0;
   rule.target = rule.fill = 0;
   rule.rlong = rule.rshort = 1;
-  rule.even = 0;
-  rule.emit = !(P == 4 && nt == kNB);
   if (tiles >= 0) {
     rule.rmin = int32_t(tiles > 0 ? std::max<int64_t>(1, std::min(most, L.ntiles / tiles)) : 1);
   } else {
@@ -1357,7 +1353,9 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
     rule.target = kTargetWorkgroups;
     rule.rshort = int32_t(most);
     rule.fill = kFillWorkgroups;
-    rule.even = nt == kNB && L.ntiles <= kEvenTiles;
+    // (the count of blocks of a call with one rung is known here)
+    const bool even = (units > 460 && units <= 512) || (units > 690 && units <= 768);
+    if (!d_list && nt == kNB && L.ntiles <= kEvenTiles && even) rule.target = rule.fill = 0;
   }
   // a multi-rung call does not know its counts of blocks here: the grid holds
   // every choice that the rule can make, and the workgroups past it return
@@ -1370,11 +1368,13 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
     rule.span = int32_t(step);
     grid = units * step;
   }
-  const int blocks_per_wg = kWaves * 32 * nt;
-  // a single-rung call knows its count of blocks: where the walk is of one range, and
-  // emits, there are no keys to clear and nothing left to do after it
-  const bool done = !d_list && rule.emit && range_count(rule, uint32_t(units)) == 1;
-  if (!d_list && !done)
+  // one range, known here: a single-rung call's count of blocks is, and of 8 seed tiles
+  // every count makes one. The walk then emits (the rebuilding kernel does not), there
+  // are no keys to clear and nothing is left to do after it.
+  const bool one = !(P == 4 && nt == kNB) &&
+                   (d_list ? std::max({rule.rmin, rule.rlong, rule.rshort}) == 1
+                           : range_count(rule, uint32_t(units)) == 1);
+  if (!d_list && !one)
     hipLaunchKernelGGL(clear_keys_kernel, dim3(per_block), dim3(threads), 0, stream, keys, nblocks);
   auto walk = [&](auto kern) {
     for (; rule.first < rule.rmin; rule.first += int32_t(step))
@@ -1383,18 +1383,19 @@ hipError_t launch_mfma_p(const float* d_W, int64_t nblocks, const int32_t* d_lis
                          rule, keys, d_seed, d_exp, d_err);
   };
   if (nt == 1) {
-    walk(search_mfma_kernel<P, 1>);
+    one ? walk(search_mfma_kernel<P, 1, true>) : walk(search_mfma_kernel<P, 1, false>);
   } else if (nt == 2) {
-    if constexpr (P >= 4) walk(search_mfma_kernel<P, 2>);
+    if constexpr (P >= 4)
+      one ? walk(search_mfma_kernel<P, 2, true>) : walk(search_mfma_kernel<P, 2, false>);
   } else if constexpr (P == 4) {
     walk(search_mfma_remat_kernel<P>);
   } else {
-    if constexpr (P < 4) walk(search_mfma_kernel<P, kNB>);
+    if constexpr (P < 4)
+      one ? walk(search_mfma_kernel<P, kNB, true>) : walk(search_mfma_kernel<P, kNB, false>);
   }
-  if (!done)
+  if (!one)
     hipLaunchKernelGGL(emit_codes_kernel<P>, dim3(per_block), dim3(threads), 0, stream, d_W, nblocks,
-                       d_list, d_off, rung, K, mask, ub, pinv32, pinv64, rule, blocks_per_wg, keys,
-                       d_seed, d_exp, d_err);
+                       d_list, d_off, rung, K, mask, ub, pinv32, pinv64, keys, d_seed, d_exp, d_err);
   return hipGetLastError();
 }
 
