@@ -154,3 +154,50 @@ def test_more_rows_than_group_sums_reach(sq, oq):  # noqa: F811
     rng = np.random.default_rng(4)
     _check(sq, oq, rng.integers(0, 3, nrows * G).astype(np.uint8), [(8, 1), (16, 3), (20, 4)], nrows,
            8 * G)
+
+
+def test_offsets_from_the_scan_of_many_chunks(sq):  # noqa: F811
+    # above 16384 chunks (33.5 M blocks) the packer and the parsers take their offsets
+    # from the scan; a long stretch without bits lies behind an unaligned code. The same
+    # blocks in calls below the line, cut where a word ends
+    import torch
+    rungs = [(8, 1), (12, 4)]   # 16 and 32 bits
+    nb = (1 << 25) + 70001
+    g = torch.Generator(device="cuda").manual_seed(6)
+    rob = torch.randint(0, 2, (nb,), device="cuda", generator=g, dtype=torch.uint8)
+    gap = (9000001, 20000003)
+    rob[gap[0]:gap[1]] = 200
+    cuts = [0, 8000000, 25000000, nb]
+    for c in cuts[1:3]:   # an even number of 16-bit codes before a cut
+        rob[c - 1] = 1
+        if int((rob[:c] == 0).sum()) % 2:
+            rob[c - 2] = 1 - rob[c - 2]
+    rob[gap[0] - 1] = 1
+    if int((rob[:gap[0]] == 0).sum()) % 2 == 0:
+        rob[gap[0] - 2] = 1 - rob[gap[0] - 2]
+    if int((rob[:cuts[2]] == 0).sum()) % 2:
+        rob[cuts[2] - 2] = 1 - rob[cuts[2] - 2]
+    valid = rob < 2
+    P = torch.tensor([1, 4, 0], device="cuda")[rob.clamp(max=2).long()]
+    top = torch.tensor([255, 4095, 1], device="cuda")[rob.clamp(max=2).long()]
+    seed = (torch.randint(1 << 30, (nb,), device="cuda", generator=g) % top + 1).to(torch.int32)
+    seed[~valid] = 0
+    exp = torch.randint(0, 16, (nb,), device="cuda", generator=g, dtype=torch.uint8) * valid
+    q = torch.randint(-8, 8, (nb, 8), device="cuda", generator=g, dtype=torch.int8)
+    q *= torch.arange(8, device="cuda") < P[:, None]
+
+    def count(r):
+        return [int((r == 0).sum()), int((r == 1).sum())]
+
+    words = sq.pack(seed, exp, q, rungs, 1, 8 * nb, rob, count(rob))
+    parts = []
+    for a, b in zip(cuts, cuts[1:]):
+        c = count(rob[a:b])
+        assert c[0] % 2 == 0 or b == nb
+        parts.append(sq.pack(seed[a:b], exp[a:b], q[a:b], rungs, 1, 8 * (b - a), rob[a:b], c))
+    assert torch.equal(words, torch.cat(parts))
+    for x, y in zip(sq.unpack(words, rungs, 1, 8 * nb, rob), (seed, exp, q)):
+        assert torch.equal(x, y)
+    W = sq.decompress_stream(words, rungs, 1, 8 * nb, rob).view(-1, 8)
+    W2 = sq.decompress(seed, exp, q, rungs, 1, 8 * nb, rob)[0].view(-1, 8)
+    assert torch.equal(W[valid], W2[valid]) and bool(W[~valid].isnan().all())

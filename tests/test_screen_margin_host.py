@@ -1,12 +1,42 @@
 """The margin of the search's quadratic-form screen, restated in numpy: with both operands rounded
 to fp16, the form plus the seed's margin must reach the exact form less the block's margin, so that
 a seed whose least-squares residual is at most the best error always passes."""
+import os
+import re
+
 import numpy as np
 import pytest
 
 I, J = np.triu_indices(8)
-SCALE, MARGIN_B, MARGIN_A = 4096.0, 1024.0, 16384.0
-C = {1: 0.9355, 2: 1.2248, 3: 1.3694, 4: 1.4143, 5: 1.4143}
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2609_38477_amd", "csrc")
+
+
+def _source(name):
+    with open(os.path.join(CSRC, name)) as f:
+        return f.read()
+
+
+def constant(name):
+    """A constexpr of the kernels' header."""
+    return float(re.search(r"constexpr \w+ %s = ([0-9.]+)f?;" % name,
+                           _source("seedq_internal.h")).group(1))
+
+
+# the kernels' own constants
+SCALE, MARGIN_B, MARGIN_A = (constant(n) for n in ("kOperandScale", "kMarginScale",
+                                                   "kMarginSeedScale"))
+_c = [float(x) for x in re.search(
+    r"constexpr float c = P == 1 \? ([0-9.]+)f : P == 2 \? ([0-9.]+)f : P == 3 \? ([0-9.]+)f : ([0-9.]+)f;",
+    _source("seedq_search_mfma.hip")).groups()]
+C = {1: _c[0], 2: _c[1], 3: _c[2], 4: _c[3], 5: _c[3]}
+
+
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 5])
+def test_block_constant_is_the_largest_over_ranks(P):
+    # sqrt(r - r^2/8), the Frobenius norm of Pi - (r/8) I for a projector of rank r
+    want = max(np.sqrt(r - r * r / 8) for r in range(1, P + 1))
+    assert want <= C[P] < want * (1 + 1e-4)
 
 
 def _blocks(rng):
