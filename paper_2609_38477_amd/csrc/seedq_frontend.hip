@@ -167,9 +167,8 @@ __device__ void find_rank(const uint32_t (*hist)[kStatBins], int nbins, const in
 
 // Calls f(key) for the keys of this thread's rows of its column, kStatBatch
 // loads at a time: with 32 threads a column and two workgroups per CU, one load
-// in flight per thread left the passes bound by its latency (281 us a call over
-// the seven tensors of a 7B-shaped layer, 107 us with 16, about the time of the
-// three reads).
+// in flight per thread left the passes bound by its latency (4096 x 4096 137 us with
+// one, 59 with 16).
 constexpr int kStatBatch = 16;
 template <typename F>
 __device__ __forceinline__ void each_key(const float* __restrict__ Wc, int64_t nrows, int64_t ncols,
@@ -290,11 +289,11 @@ column_stats_kernel(const float* __restrict__ W, int64_t nrows, int64_t ncols,
 // The same statistics with every key of the workgroup's 8 columns in registers:
 // 1024 threads, 128 per column, NR rows each, so that W is read once. The three
 // digits' histograms come from the registers; the 8 columns' rows of bins are
-// padded so that equal bins of two columns fall in different banks. Bound: that
-// one read and the LDS additions of the first digit; 4096 x 4096
-// 57 -> 36 us against three passes, 11008 x 4096 154 -> 138, 4096 x 11008 188 ->
-// 124, 64 x 256 22 -> 13. Up to 128 x 96 rows; the three-pass kernel above takes
-// longer columns.
+// padded so that equal bins of two columns fall in different banks. Bound: the LDS
+// additions of the first digit, then that one read; 4096 x 4096 59 us by the three
+// passes above, 34 here, 11008 x 4096 123 and 101, 4096 x 11008 164 and 90, 64 x 256 22
+// and 13 (137, 329, 447 and 23 by three passes with one load at a time). Up to 128 x 96
+// rows; the three-pass kernel takes longer columns.
 constexpr int kRegThreads = 1024;
 constexpr int kRegGroups = kRegThreads / kStatCols;   // 128 threads per column
 constexpr int kRegPad = 8;
@@ -302,8 +301,8 @@ constexpr int kRegPad = 8;
 // The bin of h[0, nbins) that holds the element of rank k, and the rank inside
 // it, over one wave (two prefix sums over the lanes; nbins / 64 a power of two, at
 // most 64). Each lane sums its run of bins from another place on, so that the
-// lanes' reads fall in different banks (all in one or two otherwise): column
-// statistics of 4096 x 4096 35.7 -> 34.1 us, of 4096 x 11008 93.5 -> 89.6.
+// lanes' reads fall in different banks (all in one or two otherwise, 4 to 5 % of the
+// column statistics).
 __device__ __forceinline__ void wave_find_rank(const uint32_t* h, int nbins, uint32_t k,
                                                uint32_t* bin, uint32_t* rank) {
   const int lane = threadIdx.x & 63, per = nbins / 64;

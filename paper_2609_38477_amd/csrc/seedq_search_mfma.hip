@@ -449,7 +449,7 @@ search_mfma_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* 
   __shared__ unsigned long long best_all[kWaves][kS];
   __shared__ uint32_t sbest_all[kWaves][kS];
   __shared__ int32_t blk_all[kWaves][kS];
-  __shared__ float thr_base_all[kWaves][kS];   // ||w||^2 (1 - gamma) in accumulator units
+  __shared__ float thr_base_all[kWaves][kS];   // threshold_base, in accumulator units
   // power-of-two scaling of the block: ilogb of its largest |w_i|, down to -149
   // for fp32 subnormals, so 16 bits
   __shared__ int16_t ex_all[kWaves][kS];
@@ -1045,8 +1045,8 @@ search_mfma_remat_kernel(const float* __restrict__ W, int64_t nblocks, const int
     }
   };
 
-  // Records -> queued seeds (P = 4): lane l < 32 takes record base + l of the
-  // top 32 and compares its 16 bounds with the block's current threshold; one
+  // Records -> queued seeds (P = 4): lane l < kRecRound takes record base + l of the
+  // top kRecRound and compares its 16 bounds with the block's current threshold; one
   // ballot per seed row queues the passing seeds, and full batches are
   // evaluated after each round, each evaluation followed at once by rebuild()
   // (block data and the fragments the walk still needs), so that none of the
@@ -1261,7 +1261,7 @@ emit_codes_kernel(const float* __restrict__ W, int64_t nblocks, const int32_t* _
 // - up to kTargetWorkgroups, ranges of kLongTiles or more: about 12 rounds of
 //   the 1024 places even out the last round. 1024 x 4096, three rungs: 14.0,
 //   13.5, 13.0, 12.8 ms at targets of 1024, 4096, 8192, 12288 (18.9 ms with one
-//   launch per 2048 tiles before); 1023 x 4096 (16,5) 6.4, 5.2, 5.2, 5.2 ms.
+//   launch per 2048 tiles before).
 //   Ranges of 32 or 128 tiles instead of 64 are 0-4 % slower ((12,2) on 2.1 M
 //   blocks 1.19 -> 1.21 ms at 32: every range has its own prologue, pilot and
 //   first survivors).
@@ -1295,8 +1295,8 @@ constexpr int64_t kMaxGrid = int64_t(1) << 23;
 // - 2, at P = 4 below K = 15 ((11,4) on 524 288 blocks 415 -> 335 us, (12,4) on
 //   1 M 1122 -> 950 us, (14,4) 2382 -> 2293 us; (15,4) 3943 -> 3962 us, (16,4)
 //   +2 %, (20,4) +5 % against the rebuilding kernel) and at P >= 5 ((14,6) 3393
-//   -> 3218 us, (16,6) 8450 -> 8316 us on 524 288 blocks; (16,5) on 523 776 5.97
-//   ms with 4 tiles, which spill, 4.5 ms with 2): there the survivors' registers
+//   -> 3218 us, (16,6) 8450 -> 8316 us on 524 288 blocks; 4 tiles spill at
+//   P = 5, (16,5) a third slower): there the survivors' registers
 //   and not the fragments' loads bound the walk. At P <= 3 two tiles are 4-14 %
 //   slower.
 constexpr int64_t kFewWorkgroups = 12288;

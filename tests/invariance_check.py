@@ -1,8 +1,8 @@
 """The search of a whole multi-rung layer is a pure function of its inputs (a
 one-off check at full size; the suite checks the same on smaller cases): the
 codes and errors of one compress call over every block are bit-identical to
-those of a second call, of calls with other seed-chunk lengths (one walk, and
-chunks of 512 seed tiles), of the allocation-free entry point, and of the layer
+those of a second call, of calls with other seed ranges (one walk, and ranges
+of 512 seed tiles), of the allocation-free entry point, and of the layer
 streamed from host memory in 7 uneven row tiles.
 
     python3 tests/invariance_check.py [--workload l70b]

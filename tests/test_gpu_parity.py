@@ -125,8 +125,8 @@ def test_search_tiny_full_with_planted(sq, oq, torch):
     assert not q[:, P:].any()
 
 
-# (13, 4) and (14, 4) take the rebuilding kernel's record stage, (10, 4) and
-# (12, 4) the per-seed checks
+# few blocks: one block tile a wave at every rung (calls of several tiles a wave and the
+# rebuilding kernel are in test_gpu_ranges.py)
 @pytest.mark.parametrize("K,P", [(8, 1), (8, 2), (9, 5), (10, 4), (10, 6), (12, 4), (13, 4), (14, 4)])
 def test_search_rungs_small(sq, oq, torch, K, P):
     W = synthetic.weights(7, 8 * 37, 0.02, key=K * 16 + P, outlier_frac=0.01)   # 259 blocks: ragged
@@ -162,7 +162,7 @@ def test_search_edge_blocks(sq, oq, torch):
 
 @pytest.mark.parametrize("K,P", [(10, 5), (10, 6), (12, 5), (12, 6)])
 def test_search_edge_blocks_complement(sq, oq, torch, K, P):
-    # degenerate blocks at the complement-screen rungs, most of them blocks whose
+    # degenerate blocks at the rungs with many survivors, most of them blocks whose
     # seeds all tie exactly (fp32 subnormals: every code is q = 0 and every
     # error is ||w||^2), in whole block tiles: every bound of every record then
     # passes, the largest queue a round of records can fill (16 seeds per
@@ -215,11 +215,11 @@ def test_search_multi_rung_with_schedule(sq, oq, torch):
 
 
 def test_search_every_kernel_variant_in_one_call(sq, oq, torch):
-    # one compress call whose rungs take every search variant: (10,2) the
-    # register-resident walk with records, (12,4) the rebuilding kernel's
-    # per-seed checks, (13,4) its records, (11,5) the lane-mask enqueue, (15,6)
-    # the fp32 residual filter; rungs assigned per block at random, so the
-    # compaction interleaves them arbitrarily (and leaves ragged tails)
+    # one compress call whose rungs take every way of the one-tile walk: (10,2) and
+    # (12,4), (13,4) the quadratic form with fp64 decisions, (11,5) the form with
+    # compacted records and fp32 decisions, (15,6) the complement screen; rungs
+    # assigned per block at random, so the compaction interleaves them arbitrarily
+    # (and leaves ragged tails)
     rungs = ((10, 2), (12, 4), (13, 4), (11, 5), (15, 6))
     nrows, ncols = 5, 8 * 97
     W = synthetic.weights(nrows, ncols, 0.02, key=77, outlier_frac=0.02)
@@ -238,10 +238,8 @@ def test_search_every_kernel_variant_in_one_call(sq, oq, torch):
 
 
 def test_search_without_error_output_gives_the_same_codes(sq, torch):
-    # d_err is optional: with it NULL every kernel variant (register walk,
-    # rebuilding kernel with and without records, lane masks, residual filter,
-    # sequential chunks and the emission pass of split walks) must give the
-    # same codes bit for bit
+    # d_err is optional: with it NULL the walks that emit their codes and the
+    # emission from the keys must give the same codes bit for bit
     cases = [(((10, 2), (13, 4), (11, 5), (15, 6), (17, 3)), 4, 8 * 61),
              (((18, 4),), 2, 8 * 40),
              (((12, 3),), 3, 8 * 97)]
@@ -275,9 +273,8 @@ def test_invalid_rung_index_gets_seed_zero(sq, torch):
 @pytest.mark.parametrize("K,P", [(12, 3), (14, 2), (16, 3), (13, 4), (12, 4), (11, 5), (15, 6),
                                  (17, 3), (18, 4)])
 def test_search_seed_chunks_match_unsplit(sq, torch, K, P):
-    # the seed tiles walked in sequential chunks of SEEDQ_SEED_CHUNK_TILES tiles
-    # (2048 by default, so K >= 17 is chunked), each launch starting from the
-    # best error and seed the one before left: every chunk length must give the
+    # the seed tiles walked in ranges of SEEDQ_SEED_CHUNK_TILES tiles by different
+    # workgroups, which meet in the blocks' keys: every range length must give the
     # single walk's codes bit for bit (including an all-zero block and a ragged
     # tail)
     import os
@@ -312,10 +309,10 @@ def test_search_seed_chunks_match_unsplit(sq, torch, K, P):
 @pytest.mark.parametrize("K,P", [(12, 5), (13, 6)])
 def test_search_seed_chunks_carry_ties(sq, oq, torch, K, P):
     # blocks whose seeds all tie (fp32 subnormals) beside ordinary ones, the
-    # walk cut into chunks of 8 tiles: every later chunk meets the first
-    # chunk's best error exactly again, and the carried best seed must stay the
-    # smallest (seed 1); every chunk length gives the single walk's codes, and
-    # those are the oracle's
+    # walk cut into ranges of 8 tiles: every range meets the others' best error
+    # exactly again, and the best seed must be the smallest (seed 1) in whatever
+    # order they end; every range length gives the single walk's codes, and those
+    # are the oracle's
     import os
     rng = np.random.default_rng(23)
     tie = [np.full(8, 1e-39), rng.uniform(-1, 1, 8) * 1e-42]
@@ -346,9 +343,9 @@ def test_search_seed_chunks_carry_ties(sq, oq, torch, K, P):
 
 @pytest.mark.parametrize("K,P", [(20, 4), (18, 3)])
 def test_search_seed_chunks_match_unsplit_many_blocks(sq, torch, K, P):
-    # the chunked walk at the rungs the multi-rung layers use, on 16 387 blocks
-    # (seven rows of 2341, a ragged last block tile): the default chunks and
-    # chunks of 512 tiles give the single walk's codes and errors bit for bit
+    # the walk in ranges at the rungs the multi-rung layers use, on 16 387 blocks
+    # (seven rows of 2341, a ragged last block tile): the rule's ranges and ranges
+    # of 512 tiles give the single walk's codes and errors bit for bit
     import os
     W = synthetic.weights(7, 8 * 2341, 0.02, key=700 + K, outlier_frac=0.02)
     b = sq.build_bases(K, P)
@@ -373,8 +370,8 @@ def test_search_seed_chunks_match_unsplit_many_blocks(sq, torch, K, P):
 
 
 def test_search_chunks_multi_rung_match_single_walk(sq, torch):
-    # a multi-rung call whose K = 17 rung is walked in sequential chunks through
-    # the compaction lists: the codes must equal those of one walk per rung, bit
+    # a multi-rung call whose K = 17 rung is walked in ranges through the
+    # compaction lists: the codes must equal those of one walk per rung, bit
     # for bit
     import os
     rungs = ((10, 2), (17, 3))
@@ -418,8 +415,8 @@ def test_search_deterministic(sq, torch):
 
 
 def test_search_k20_sampled(sq, oq, torch):
-    # 64 blocks at (20, 4): sequential seed chunks and the
-    # rebuilding kernel's record stage, against the oracle's exhaustive search
+    # 64 blocks at (20, 4) in thousands of seed ranges, against the oracle's
+    # exhaustive search
     K, P = 20, 4
     W = synthetic.weights(1, 8 * 64, 0.02, key=20, outlier_frac=0.02)
     b = sq.build_bases(K, P)
@@ -431,10 +428,10 @@ def test_search_k20_sampled(sq, oq, torch):
 
 @pytest.mark.parametrize("K,P,nb", [(16, 6, 48), (15, 6, 64), (16, 5, 48)])
 def test_search_dense_survivor_rungs(sq, oq, torch, K, P, nb):
-    # rungs where a few percent of all seeds pass the screen: the complement
-    # screen and its records (fp16 at P = 6), the integer basis table in the
-    # exact evaluation; 48 or 64 blocks leave part of a wave's four 32-block
-    # tiles empty; heavy-tailed blocks among them
+    # rungs where a few percent of all seeds pass the screen: their records (fp16
+    # with the complement screen of P = 6), the integer basis table in the exact
+    # evaluation; 48 or 64 blocks leave part of a workgroup's tiles empty;
+    # heavy-tailed blocks among them
     W = synthetic.weights(1, 8 * nb, 0.02, key=60 + K + P, outlier_frac=0.05)
     b = sq.build_bases(K, P)
     seed, e, q, err = sq.compress(_dev(torch, W), [b])
@@ -477,8 +474,8 @@ def test_search_near_rounding_boundaries(sq, oq, torch, K, P):
 def test_search_rank_deficient_seeds_complement(sq, oq, torch, K, P):
     # blocks in (or next to) the column span of the rank-deficient seeds of a
     # P >= 5 rung: their residual at that seed is zero, so the seed must
-    # survive the complement screen, whose vectors span only part of that
-    # seed's larger complement, and the refine takes the minimum-norm solution
+    # survive the screen (at P = 6 by complement vectors, which span only part of
+    # that seed's larger complement), and the refine takes the minimum-norm solution
     U = oq.basis_int_all(K, P).astype(np.float64) * 2.0 ** -(K - 1)
     s = np.linalg.svd(U, compute_uv=False)
     deficient = np.nonzero(s[:, -1] <= 2.0 ** -30 * s[:, 0])[0]
@@ -539,11 +536,10 @@ def _oracle_best_of(oq, w, K, P, seeds):
 
 @pytest.mark.parametrize("P", [1, 3, 4, 5, 6])
 def test_search_widest_register_k24(sq, oq, torch, P):
-    # K = 24: 2^24 - 1 seeds in 256 sequential chunks, seeds filling the 24 bits
-    # the keys and queue entries leave them, integer states at the 24-bit
-    # multiply's limit; every search variant (register walk at P = 1, 3; the
-    # rebuilding kernel with records at 4, lane masks at 5, the residual filter
-    # at 6). Planted codes come back exactly. At P = 1 the whole search is the
+    # K = 24: 2^24 - 1 seeds in ranges, seeds filling the 24 bits the keys and queue
+    # entries leave them, integer states at the 24-bit multiply's limit; the form
+    # with fp64 decisions at P = 1, 3 and 4, with fp32 ones at 5, the complement
+    # screen at 6. Planted codes come back exactly. At P = 1 the whole search is the
     # oracle's; at larger P (the oracle's stack is too slow there) every random
     # block's code is the oracle's quantised least-squares code of its seed, its
     # error is exact, and no seed of a 16384-seed sample does better.

@@ -55,7 +55,7 @@ def _case(key, nrows, ngroups, nrungs):
 def test_noalloc_equals_compress_on_two_calls_in_a_row(sq, oq, torch):
     from test_gpu_parity import check_search
     # first call: 12 rows x 1024 groups = 12288 blocks (six compaction chunks),
-    # three rungs, the K = 17 one walked in sequential seed chunks
+    # three rungs, the K = 17 one walked in several seed ranges
     rungs1 = ((10, 2), (12, 3), (17, 3))
     W1, rob1 = _case(701, 12, 1024, len(rungs1))
     # second call: 485 blocks (a ragged tail), other rungs and another split
