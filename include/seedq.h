@@ -199,9 +199,9 @@ size_t seedq_compress_workspace_bytes(int64_t nrows, int64_t ncols, int32_t C, i
  * A block whose 8 weights are all zero gets seed 1, e = 15, q = 0, err = 0 (every
  * seed ties). Asynchronous on hip_stream.
  * The seeds of a rung (tiles of 32) are searched in ranges by different
- * workgroups, whose number follows the count of blocks; until the call
- * completes, d_q holds each block's best code so far (its error and seed in one
- * 64-bit word; d_q must be 8-byte aligned). The result is the same for every
+ * workgroups, whose number follows the count of blocks. Until the call
+ * completes, d_q holds each block's best so far where there are several ranges
+ * (its error and seed in one 64-bit word; d_q must be 8-byte aligned). The result is the same for every
  * range length: the smallest exact error, ties to the smallest seed. The
  * environment variable SEEDQ_SEED_CHUNK_TILES (tiles per range, 0 = one range),
  * read at each call, overrides the choice (at least 8 seed tiles per range).
